@@ -1245,151 +1245,83 @@ __global__ __launch_bounds__(256) void sbm_face_slab_kernel(int n_faces, const i
 // For the face (a, s) of K with neighbour N and outward normal n_K = (2s-1) e_a:
 //   [u]_K = u_K - u_N,  {du/dn_K} = (du_K/dn_K + du_N/dn_K)/2,
 //   K's rows += int (sigma_F [u]_K - {du/dn_K}) v - 1/2 [u]_K dv/dn_K   (Alg. 2, per side)
+//
+// The face integral is a tensor product too: its Gauss rule is the one of the cell, so the
+// interpolation to the face's points and its transpose multiply out to the 1D mass matrix M
+// along each tangential axis, and the face term of axis a is M x M x (an operator along a that
+// acts on the cell's line and the neighbours' adjoining lines).  With W_a that operator plus
+// the stiffness matrix K,
+//   v_K = h^(d-2) sum_a (M along the other axes) W_a (u_K, u_left, u_right),
+// and no face values are ever interpolated or integrated.
+//
+// Layout: NP = (p+1)^(d-1) threads per cell, one line of p+1 nodes each; every thread forms its
+// line of all d axes straight from global memory (its own and the two neighbours' values: each
+// needs the whole adjoining line for the normal derivative), then
+//   3D: v = M_z (M_y X + M_x Y) + M_y M_x Z,  2D: v = M_y X + M_x Y   (X = W_x u, ...),
+// one LDS tile per term, the lines of every tile padded to an odd length.
+// What bounds it: instruction issue and the latency of its loads.  At 80^3 Q3 FP64 (40,308
+// cells) evaluating the faces one by one (traces, Gauss interpolation, integration and the rows
+// of six faces) took 61.1 us and 22.2 M vector instructions of the wavefronts, 70 % of the issue
+// slots; this form takes 19.0 us and 4.1 M (50 %), 2.4 TB/s of the 46 MB it must move.  32^3 Q5
+// FP32 (2,008 cells): 10.9 -> 6.1 us.
 // ------------------------------------------------------------------------------------
-// Face-by-face form (one group of NP threads per cell walks the 2d faces in turn), for the
-// degrees with more than 128 threads per cell in the parallel form below.
-// BATCH: the kernel serves a batch of applies (items, blk_item as in the batched kernels after
-// apply_impl; the pointer and size arguments are then taken from the workgroup's item).  This
-// form is kept as one kernel rather than a body called by two (as the other kernels are): as
-// an inlined body it compiled to about 6 % more instructions (DG Q5 apply 24.9 against 23.6 us).
-template <typename T, int D, int N1, int EPB, bool BATCH>
-__global__ __launch_bounds__(256) void dg_cell_seq_kernel(int n_cells, const int32_t *__restrict__ nbr,
-                                                      const T *__restrict__ u, const T *__restrict__ fbuf,
-                                                      T *__restrict__ v, KTab<T, N1> tab, KScal sc, T scale,
-                                                      int parts, const BatchItem *__restrict__ items,
-                                                      const int32_t *__restrict__ blk_item) {
-  int blk = xcd_block();
-  if constexpr (BATCH) {
-    const BatchItem *it = items + blk_item[blk];
-    blk -= it->blk0[1];
-    n_cells = it->nc;
-    nbr = it->nbr;
-    u = (const T *)it->u;
-    fbuf = (const T *)it->fbuf;
-    v = (T *)it->v;
-    sc = it->sc;
-    scale = T(D == 3 ? it->sc.h : 1.0);
+template <typename T, int D, int N1>
+struct DgCell {
+  static constexpr int NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB;
+  static constexpr int PITCH = N1 | 1;       // odd: lines along x fall on different LDS banks
+  static constexpr int TILE = NP * PITCH;    // one term of one cell
+  static constexpr bool IN_WAVE = 64 % NP == 0;  // a cell's threads share a wavefront: no barriers
+  // cells per workgroup: up to 256 threads and about 40 KB
+  static constexpr int full() {
+    int e = 256 / NP;
+    if (e < 1) e = 1;
+    while (e > 1 && e * D * TILE * (int)sizeof(T) > 40000) --e;
+    return e;
   }
-  constexpr int NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB, P = N1 - 1;
-  __shared__ T su_all[EPB * NB];
-  __shared__ T sa_all[EPB * NB];
-  __shared__ T sb_all[EPB * NB];
-  __shared__ T sw_all[EPB * NB];
-  __shared__ T f_all[4 * EPB * NP];
-  const int le = threadIdx.x / NP, t = threadIdx.x - le * NP;
-  const int cell = blk * EPB + le;
-  const bool act = cell < n_cells;
-  T *su = su_all + le * NB, *A = sa_all + le * NB, *B = sb_all + le * NB, *sw = sw_all + le * NB;
-  T *f1 = f_all + le * NP, *f2 = f1 + EPB * NP, *f3 = f2 + EPB * NP, *f4 = f3 + EPB * NP;
-  const T h = T(sc.h), sigf = T(sc.sigma_f);
-  const bool use_int = (parts & SBM_PART_CELLS) != 0, use_sbm = (parts & SBM_PART_SBM_FACES) != 0;
+  // few cells: one wavefront (at least one cell)
+  static constexpr int few() { return 64 / NP < 1 ? 1 : (64 / NP < full() ? 64 / NP : full()); }
+  __device__ static __forceinline__ void sync() {
+    if constexpr (IN_WAVE) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  }
+};
 
-  // neighbours of the 2d faces, and the first neighbour's run for this thread: every
-  // neighbour's values are loaded one face ahead, so the loads overlap the previous face
-  int nbs[2 * D];
-#pragma unroll
-  for (int k = 0; k < 2 * D; ++k) nbs[k] = act ? nbr[(int64_t)cell * 2 * D + k] : -1;
-  T nx[N1];
-  if (nbs[0] >= 0) {
-    const T *up = u + (int64_t)nbs[0] * NB + N1 * t;
-#pragma unroll
-    for (int i = 0; i < N1; ++i) nx[i] = up[i];
-  }
-  // own block (contiguous), thread t = run
-  if (act) {
-    const T *up = u + (int64_t)cell * NB + N1 * t;
-#pragma unroll
-    for (int i = 0; i < N1; ++i) su[N1 * t + i] = up[i];
-  }
-  __syncthreads();
-  {
-    T x[N1], out[N1];
-#pragma unroll
-    for (int k = 0; k < N1; ++k) x[k] = su[t + NP * k];
-    kron_cell<T, D, N1>(tab, t, x, A, B, scale, out);
-#pragma unroll
-    for (int i = 0; i < N1; ++i) sw[N1 * t + i] = use_int ? out[i] : T(0);
-  }
-  // ---- interior faces, and the surrogate faces' rows (results of sbm_face_kernel) ----
-  const int jb = (D == 3) ? t % N1 : t, jc = (D == 3) ? t / N1 : 0;
-#pragma unroll
-  for (int code = 0; code < 2 * D; ++code) {
-    const FaceAxes<D, N1> fa(code);
-    const bool has = nbs[code] >= 0;
-    __syncthreads();  // previous users of A (neighbour tile) and f1..f4 are done
-    if (has) {
-#pragma unroll
-      for (int i = 0; i < N1; ++i) A[N1 * t + i] = nx[i];
-    }
-    if (code + 1 < 2 * D && nbs[code + 1] >= 0) {
-      const T *up = u + (int64_t)nbs[code + 1] * NB + N1 * t;
-#pragma unroll
-      for (int i = 0; i < N1; ++i) nx[i] = up[i];
-    }
-    __syncthreads();
-    const T sgn = fa.s ? T(1) : T(-1);
-    const int node_off = jb * fa.Sb + jc * fa.Sc;
-    {
-      T dK = 0, dN = 0;
-#pragma unroll
-      for (int ia = 0; ia < N1; ++ia) {
-        dK += (fa.s ? tab.D1[ia] : tab.D0[ia]) * su[ia * fa.Sa + node_off];
-        dN += (fa.s ? tab.D0[ia] : tab.D1[ia]) * A[ia * fa.Sa + node_off];
-      }
-      const T uK = su[fa.s * P * fa.Sa + node_off];
-      const T uN = A[(1 - fa.s) * P * fa.Sa + node_off];
-      f1[t] = uK - uN;                       // [u]_K at the face nodes
-      f2[t] = T(0.5) * sgn * (dK + dN) / h;  // {du/dn_K} at the face nodes
-    }
-    __syncthreads();
-    T jq, aq;
-    face_interpolate<T, D, N1>(tab, t, f1, f2, f3, f4, jq, aq);
-    T om;
-    if constexpr (D == 3)
-      om = h * h * tab.w[t % N1] * tab.w[t / N1];
-    else
-      om = h * tab.w[t];
-    __syncthreads();
-    f3[t] = om * (sigf * jq - aq);
-    f4[t] = T(-0.5) * om * jq * sgn / h;
-    __syncthreads();
-    T Rv, Rg;
-    face_integrate<T, D, N1>(tab, t, f1, f2, f3, f4, Rv, Rg);
-    const bool sbmf = nbs[code] < -1 && use_sbm;  // surrogate face -2 - nbs[code]
-    if (sbmf) {
-      const int64_t fo = (int64_t)(-2 - nbs[code]) * 2 * NP;
-      Rv = fbuf[fo + t];
-      Rg = fbuf[fo + NP + t];
-    }
-    if ((has && use_int) || sbmf) {
-#pragma unroll
-      for (int ia = 0; ia < N1; ++ia)
-        sw[ia * fa.Sa + node_off] += ((ia == fa.s * P) ? Rv : T(0)) + (fa.s ? tab.D1[ia] : tab.D0[ia]) * Rg;
-    }
-  }
-  __syncthreads();
-  if (act) {
-    T *vp = v + (int64_t)cell * NB + N1 * t;
-#pragma unroll
-    for (int i = 0; i < N1; ++i) vp[i] = sw[N1 * t + i];
-  }
+// y = A x for a centrosymmetric 1D matrix given by its even/odd parts.
+template <typename T, int N1>
+__device__ __forceinline__ void eo_mul(const T *E, const T *O, const T (&x)[N1], T (&y)[N1]) {
+  const EvenOdd<T, N1> ex(x);
+  EOAcc<T, N1> a;
+  eo_acc<T, N1>(E, O, ex, a.ye, a.yo);
+  eo_combine<T, N1>(a.ye, a.yo, T(1), y);
 }
 
-// Thread layout: 2d groups of NP threads per cell, group g evaluates interior face g (code
-// 2 axis + side) with its own neighbour tile and scratch, all faces at once; then the block's
-// first EPB NP threads form the cells' terms (NP per cell; the rest only pass the barriers).
-// Then every row of the cell adds the cell term and the faces' rows in face order (the order
-// of a face-by-face loop); a face without a neighbour contributes the surrogate face's rows.
-template <typename T, int D, int N1>
-constexpr int dg_cells_per_block(bool one_wave) {
-  constexpr int NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB, TPC = 2 * D * NP;
-  // LDS per cell: own tile, 2d neighbour tiles (two of them reused for the cell term), cell
-  // result (NB each); per face 6 NP of scratch and results
-  constexpr int per_cell = ((2 + 2 * D) * NB + 2 * D * 6 * NP) * (int)sizeof(T);
-  int e = (one_wave ? 64 : 256) / TPC;
-  if (e < 1) e = 1;
-  while (e > 1 && e * per_cell > 60000) --e;
-  return e;
+// w = W (x; l, r): the stiffness matrix on the cell's line x plus the SIPG terms of its two end
+// faces against the neighbours' lines l and r (scaled by 1/h^(d-2); sh = sigma_F h).
+template <typename T, int N1>
+__device__ __forceinline__ void dg_line(const KTab<T, N1> &tab, T sh, const T (&x)[N1], bool has_l, const T (&l)[N1],
+                                        bool has_r, const T (&r)[N1], T (&w)[N1]) {
+  constexpr int P = N1 - 1;
+  eo_mul<T, N1>(tab.EK, tab.OK, x, w);
+  T k0 = 0, k1 = 0, n0 = 0, n1 = 0;  // own and neighbours' reference derivatives at both ends
+#pragma unroll
+  for (int i = 0; i < N1; ++i) {
+    k0 += tab.D0[i] * x[i];
+    k1 += tab.D1[i] * x[i];
+    n0 += tab.D1[i] * l[i];
+    n1 += tab.D0[i] * r[i];
+  }
+  const T j0 = x[0] - l[P], j1 = x[P] - r[0];  // jumps [u]_K
+  const T c0 = has_l ? sh * j0 + T(0.5) * (k0 + n0) : T(0), g0 = has_l ? T(0.5) * j0 : T(0);
+  const T c1 = has_r ? sh * j1 - T(0.5) * (k1 + n1) : T(0), g1 = has_r ? T(-0.5) * j1 : T(0);
+#pragma unroll
+  for (int i = 0; i < N1; ++i) w[i] += tab.D0[i] * g0 + tab.D1[i] * g1;
+  w[0] += c0;
+  w[P] += c1;
 }
 
 template <typename T, int D, int N1, int EPB>
@@ -1397,115 +1329,110 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
                                                       const T *__restrict__ u, const T *__restrict__ fbuf,
                                                       T *__restrict__ v, KTab<T, N1> tab, KScal sc, T scale,
                                                       int parts) {
-  constexpr int NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB, P = N1 - 1, NF = 2 * D, TPC = NF * NP;
-  __shared__ T su_all[EPB * NB];           // own tile
-  __shared__ T sn_all[EPB * NF * NB];      // neighbour tiles, one per face (then the cell-term tiles)
-  __shared__ T sw_all[EPB * NB];           // cell term
-  __shared__ T f_all[EPB * NF * 6 * NP];   // per face: f1..f4 scratch, Rv, Rg
-  const int le = threadIdx.x / TPC, r = threadIdx.x - le * TPC;  // cell in block, thread in cell
-  const int g = r / NP, t = r - g * NP;                            // face group, node / run
+  using C = DgCell<T, D, N1>;
+  constexpr int NP = C::NP, NB = C::NB, P = N1 - 1, LP = C::PITCH;
+  __shared__ T tiles[EPB * D * C::TILE];
+  const int le = threadIdx.x / NP, t = threadIdx.x - le * NP;
   const int cell = blk * EPB + le;
   const bool act = cell < n_cells;
-  T *su = su_all + le * NB, *sw = sw_all + le * NB;
-  T *An = sn_all + (le * NF + g) * NB;
-  T *fw = f_all + (le * NF + g) * 6 * NP;
-  T *f1 = fw, *f2 = fw + NP, *f3 = fw + 2 * NP, *f4 = fw + 3 * NP, *fRv = fw + 4 * NP, *fRg = fw + 5 * NP;
-  const T h = T(sc.h), sigf = T(sc.sigma_f);
   const bool use_int = (parts & SBM_PART_CELLS) != 0, use_sbm = (parts & SBM_PART_SBM_FACES) != 0;
-
-  // loads: group 0 the cell's own block (thread t = run), group g the neighbour across face g
-  const int nb = act ? nbr[(int64_t)cell * NF + g] : -1;
-  const bool has = nb >= 0;
-  if (g == 0 && act) {
-    const T *up = u + (int64_t)cell * NB + N1 * t;
+  T *A = tiles + le * D * C::TILE, *B = A + C::TILE, *Z = B + (D == 3 ? C::TILE : 0);
+  const T sh = T(sc.sigma_f * sc.h);
+  int nbs[2 * D];
 #pragma unroll
-    for (int i = 0; i < N1; ++i) su[N1 * t + i] = up[i];
-  }
-  if (has) {
-    const T *up = u + (int64_t)nb * NB + N1 * t;
+  for (int k = 0; k < 2 * D; ++k) nbs[k] = act ? nbr[(int64_t)cell * 2 * D + k] : -1;
+  // line t along axis a: node i at g0 + i * gs in the cell's block, at s0 + i * ss in its tiles
+  const int t0 = (D == 3) ? t % N1 : t, t1 = (D == 3) ? t / N1 : 0;
+  const int g0[3] = {N1 * t, (D == 3) ? t0 + NP * t1 : t, t}, gs[3] = {1, N1, NP};
+  const int s0[3] = {LP * t, (D == 3) ? t0 + LP * N1 * t1 : t, t0 + LP * t1}, ss[3] = {1, LP, LP * N1};
+  T out[N1];
 #pragma unroll
-    for (int i = 0; i < N1; ++i) An[N1 * t + i] = up[i];
-  }
-  __syncthreads();
-  // ---- interior face g: traces, Gauss-point integrands, transposed integration ----
-  {
-    const FaceAxes<D, N1> fa(g);
-    const int jb = (D == 3) ? t % N1 : t, jc = (D == 3) ? t / N1 : 0;
-    const T sgn = fa.s ? T(1) : T(-1);
-    const int node_off = jb * fa.Sb + jc * fa.Sc;
-    T dK = 0, dN = 0;
+  for (int i = 0; i < N1; ++i) out[i] = T(0);
+  if (use_int) {
+    const int64_t own = (int64_t)(act ? cell : 0) * NB;
 #pragma unroll
-    for (int ia = 0; ia < N1; ++ia) {
-      dK += (fa.s ? tab.D1[ia] : tab.D0[ia]) * su[ia * fa.Sa + node_off];
-      dN += (fa.s ? tab.D0[ia] : tab.D1[ia]) * An[ia * fa.Sa + node_off];
-    }
-    const T uK = su[fa.s * P * fa.Sa + node_off];
-    const T uN = An[(1 - fa.s) * P * fa.Sa + node_off];
-    f1[t] = uK - uN;                       // [u]_K at the face nodes
-    f2[t] = T(0.5) * sgn * (dK + dN) / h;  // {du/dn_K} at the face nodes
-    __syncthreads();
-    T jq, aq;
-    face_interpolate<T, D, N1>(tab, t, f1, f2, f3, f4, jq, aq);
-    T om;
-    if constexpr (D == 3)
-      om = h * h * tab.w[t % N1] * tab.w[t / N1];
-    else
-      om = h * tab.w[t];
-    __syncthreads();
-    f3[t] = om * (sigf * jq - aq);
-    f4[t] = T(-0.5) * om * jq * sgn / h;
-    __syncthreads();
-    T Rv, Rg;
-    face_integrate<T, D, N1>(tab, t, f1, f2, f3, f4, Rv, Rg);
-    if (has) {
-      fRv[t] = use_int ? Rv : T(0);
-      fRg[t] = use_int ? Rg : T(0);
-    } else if (nb < -1 && use_sbm) {
-      // surrogate face -2 - nb: its (Rv, Rg) from sbm_face_kernel, rows formed as for the others
-      const int64_t fo = (int64_t)(-2 - nb) * 2 * NP;
-      fRv[t] = fbuf[fo + t];
-      fRg[t] = fbuf[fo + NP + t];
-    } else {
-      fRv[t] = T(0);
-      fRg[t] = T(0);
-    }
-  }
-  // ---- cell term: the block's first EPB * NP threads, NP per cell (whole wavefronts beyond
-  // them only take part in the barriers).  Its two sweep tiles are the cell's first two
-  // neighbour tiles: every neighbour value was read before the face phase's first barrier ----
-  {
-    const int lc = threadIdx.x / NP, tc = threadIdx.x - lc * NP;
-    const bool work = lc < EPB;
-    const int lw = work ? lc : 0;
-    T *A = sn_all + lw * NF * NB, *B = A + NB;
-    T x[N1], out[N1];
+    for (int a = 0; a < D; ++a) {
+      const bool has_l = nbs[2 * a] >= 0, has_r = nbs[2 * a + 1] >= 0;
+      // (a missing neighbour reads the cell itself; what is made of it is dropped)
+      const T *up = u + own + g0[a];
+      const T *lp = u + (has_l ? (int64_t)nbs[2 * a] * NB : own) + g0[a];
+      const T *rp = u + (has_r ? (int64_t)nbs[2 * a + 1] * NB : own) + g0[a];
+      T x[N1], l[N1], r[N1], w[N1];
 #pragma unroll
-    for (int k = 0; k < N1; ++k) x[k] = work ? su_all[lw * NB + tc + NP * k] : T(0);
-    kron_cell<T, D, N1>(tab, tc, x, A, B, scale, out, true, work);
-    if (work) {
-#pragma unroll
-      for (int i = 0; i < N1; ++i) sw_all[lw * NB + N1 * tc + i] = use_int ? out[i] : T(0);
-    }
-  }
-  __syncthreads();
-  // ---- rows: cell term, then each face's rows in face order ----
-  if (act) {
-    for (int i = r; i < NB; i += TPC) {
-      const int ik[3] = {i % N1, (i / N1) % N1, i / (N1 * N1)};
-      T val = sw[i];
-#pragma unroll
-      for (int code = 0; code < NF; ++code) {
-        const int a = code >> 1, s = code & 1;
-        // node index on face `code`: lower tangential coordinate + N1 * upper one
-        const int lo = (a == 0) ? 1 : 0, hi = (a == 2) ? 1 : 2;
-        const int node = (D == 3) ? ik[lo] + N1 * ik[hi] : ik[lo];
-        const int ia = ik[a];
-        const T *fc = f_all + (le * NF + code) * 6 * NP;
-        val += ((ia == s * P) ? fc[4 * NP + node] : T(0)) + (s ? tab.D1[ia] : tab.D0[ia]) * fc[5 * NP + node];
+      for (int i = 0; i < N1; ++i) {
+        x[i] = up[i * gs[a]];
+        l[i] = lp[i * gs[a]];
+        r[i] = rp[i * gs[a]];
       }
-      v[(int64_t)cell * NB + i] = val;
+      dg_line<T, N1>(tab, sh, x, has_l, l, has_r, r, w);
+      T *dst = (a == 0 ? A : (a == 1 ? B : Z)) + s0[a];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) dst[i * ss[a]] = w[i];
+    }
+    C::sync();
+    auto sweep = [&](T *tile, int a) {  // the tile's line t along axis a times M, in place
+      T x[N1], y[N1];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) x[i] = tile[s0[a] + i * ss[a]];
+      eo_mul<T, N1>(tab.EM, tab.OM, x, y);
+#pragma unroll
+      for (int i = 0; i < N1; ++i) tile[s0[a] + i * ss[a]] = y[i];
+    };
+    if constexpr (D == 3) {
+      sweep(A, 1);
+      sweep(B, 0);
+      sweep(Z, 0);
+      C::sync();
+      sweep(Z, 1);
+      T x[N1], y[N1];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) x[i] = A[s0[2] + i * ss[2]] + B[s0[2] + i * ss[2]];
+      eo_mul<T, N1>(tab.EM, tab.OM, x, y);
+      C::sync();
+#pragma unroll
+      for (int i = 0; i < N1; ++i) out[i] = scale * (y[i] + Z[s0[2] + i * ss[2]]);
+    } else {
+      sweep(B, 0);
+      T x[N1], y[N1];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) x[i] = A[s0[1] + i * ss[1]];
+      eo_mul<T, N1>(tab.EM, tab.OM, x, y);
+      C::sync();
+#pragma unroll
+      for (int i = 0; i < N1; ++i) out[i] = scale * (y[i] + B[s0[1] + i * ss[1]]);
     }
   }
+  if (!act) return;
+  // surrogate faces (-2 - nbr): the rows of their (Rv, Rg), in face order.  The thread holds the
+  // line along the last axis, so a face of another axis meets it in one node line of the face.
+  constexpr int aL = D - 1;
+  if (use_sbm) {
+#pragma unroll
+    for (int code = 0; code < 2 * D; ++code) {
+      if (nbs[code] >= -1) continue;
+      const int a = code >> 1, s = code & 1;
+      const T *Rv = fbuf + (int64_t)(-2 - nbs[code]) * 2 * NP, *Rg = Rv + NP;
+      if (a == aL) {
+        const T rv = Rv[t], rg = Rg[t];
+#pragma unroll
+        for (int i = 0; i < N1; ++i) out[i] += (i == s * P ? rv : T(0)) + (s ? tab.D1[i] : tab.D0[i]) * rg;
+      } else {
+        const int ia = a == 0 ? t0 : t1;  // the line's place along the face's normal
+        const int n0 = (D == 3) ? (a == 0 ? t1 : t0) : 0;
+        T dia = T(0);
+#pragma unroll
+        for (int i = 0; i < N1; ++i) dia = i == ia ? (s ? tab.D1[i] : tab.D0[i]) : dia;
+#pragma unroll
+        for (int i = 0; i < N1; ++i) {
+          const int node = (D == 3) ? n0 + N1 * i : i;
+          out[i] += (ia == s * P ? Rv[node] : T(0)) + dia * Rg[node];
+        }
+      }
+    }
+  }
+  T *vp = v + (int64_t)cell * NB + g0[aL];
+#pragma unroll
+  for (int i = 0; i < N1; ++i) vp[i * gs[aL]] = out[i];
 }
 
 template <typename T, int D, int N1, int EPB>
@@ -1603,30 +1530,14 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
     // entities per workgroup: as many as fit, unless that leaves fewer than two workgroups
     // per compute unit; then one wavefront's worth
     if (nc > 0 && (parts & (SBM_PART_CELLS | SBM_PART_SBM_FACES))) {
-      // faces in parallel where a cell needs at most 128 threads (3D p <= 3, 2D): measured 7 %
-      // (FP64) to 20 % (FP32) faster at 3D p=3; at 3D p=5 its 216-thread, 31 KB cells leave the
-      // grid in more than one round and the face-by-face form is faster
-      constexpr int TPC = 2 * D * NP, NBC = Shape<D, N1>::NB;
-      constexpr bool PAR = TPC <= 128 && ((4 + 2 * D) * NBC + 2 * D * 6 * NP + 2 * NBC) * (int)sizeof(T) <= 60000;
-      if constexpr (PAR) {
-        constexpr int E = dg_cells_per_block<T, D, N1>(false), E1 = dg_cells_per_block<T, D, N1>(true);
-        if ((nc + E - 1) / E >= two_per_cu())
-          hipLaunchKernelGGL((dg_cell_kernel<T, D, N1, E>), dim3((nc + E - 1) / E), dim3(E * TPC), 0, s, nc,
-                             c->d_nbr, u, (const T *)fbuf, v, tab, sc, scale, parts);
-        else
-          hipLaunchKernelGGL((dg_cell_kernel<T, D, N1, E1>), dim3((nc + E1 - 1) / E1), dim3(E1 * TPC), 0, s, nc,
-                             c->d_nbr, u, (const T *)fbuf, v, tab, sc, scale, parts);
-      } else {
-        constexpr int E = epb<T, D, N1, 4, 0>(), E1 = epb_one_wave<T, D, N1, 4>();
-        if ((nc + E - 1) / E >= two_per_cu())
-          hipLaunchKernelGGL((dg_cell_seq_kernel<T, D, N1, E, false>), dim3((nc + E - 1) / E), dim3(E * NP), 0, s,
-                             nc, c->d_nbr, u, (const T *)fbuf, v, tab, sc, scale, parts, (const BatchItem *)nullptr,
-                             (const int32_t *)nullptr);
-        else
-          hipLaunchKernelGGL((dg_cell_seq_kernel<T, D, N1, E1, false>), dim3((nc + E1 - 1) / E1), dim3(E1 * NP), 0,
-                             s, nc, c->d_nbr, u, (const T *)fbuf, v, tab, sc, scale, parts,
-                             (const BatchItem *)nullptr, (const int32_t *)nullptr);
-      }
+      using DC = DgCell<T, D, N1>;
+      constexpr int E = DC::full(), E1 = DC::few();
+      if ((nc + E - 1) / E >= two_per_cu())
+        hipLaunchKernelGGL((dg_cell_kernel<T, D, N1, E>), dim3((nc + E - 1) / E), dim3(E * NP), 0, s, nc, c->d_nbr, u,
+                           (const T *)fbuf, v, tab, sc, scale, parts);
+      else
+        hipLaunchKernelGGL((dg_cell_kernel<T, D, N1, E1>), dim3((nc + E1 - 1) / E1), dim3(E1 * NP), 0, s, nc, c->d_nbr,
+                           u, (const T *)fbuf, v, tab, sc, scale, parts);
     }
   }
   return hipGetLastError();
@@ -1649,11 +1560,8 @@ struct BatchShape {
   static constexpr bool SLAB = D == 3 && NB <= 256;
   static constexpr int EFD = SLAB ? 256 / NB : epb<T, D, N1, 1, 0>();
   static constexpr int TFD = SLAB ? EFD * NB : EFD * NP;
-  // DG cells: the parallel-face form where a cell needs at most 128 threads
-  static constexpr int TPC = 2 * D * NP;
-  static constexpr bool PAR = TPC <= 128 && ((4 + 2 * D) * NB + 2 * D * 6 * NP + 2 * NB) * (int)sizeof(T) <= 60000;
-  static constexpr int EC = PAR ? dg_cells_per_block<T, D, N1>(false) : epb<T, D, N1, 4, 0>();
-  static constexpr int TC = PAR ? EC * TPC : EC * NP;
+  static constexpr int EC = DgCell<T, D, N1>::full();  // DG cells per workgroup
+  static constexpr int TC = EC * NP;
 };
 
 template <typename T, int D, int N1>
@@ -1748,14 +1656,8 @@ hipError_t batch_launch_impl(const BatchGroup &g, const unsigned char *base, hip
   } else {
     if (g.nblk[0] > 0)
       hipLaunchKernelGGL((sbm_face_dg_batch_kernel<T, D, N1>), dim3(g.nblk[0]), dim3(S::TFD), 0, s, items, bi[0], tab);
-    if (g.nblk[1] > 0) {
-      if constexpr (S::PAR)
-        hipLaunchKernelGGL((dg_cell_batch_kernel<T, D, N1>), dim3(g.nblk[1]), dim3(S::TC), 0, s, items, bi[1], tab);
-      else
-        hipLaunchKernelGGL((dg_cell_seq_kernel<T, D, N1, S::EC, true>), dim3(g.nblk[1]), dim3(S::TC), 0, s, 0,
-                           (const int32_t *)nullptr, (const T *)nullptr, (const T *)nullptr, (T *)nullptr, tab, KScal{},
-                           T(0), (int)SBM_PART_ALL, items, bi[1]);
-    }
+    if (g.nblk[1] > 0)
+      hipLaunchKernelGGL((dg_cell_batch_kernel<T, D, N1>), dim3(g.nblk[1]), dim3(S::TC), 0, s, items, bi[1], tab);
   }
   return hipGetLastError();
 }
