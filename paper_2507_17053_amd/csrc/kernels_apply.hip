@@ -3,8 +3,9 @@
 //   brick_kernel    CG: one workgroup per brick of BX x BY x BZ background cells.  The
 //                   brick's active cells (Alg. 1) are evaluated into an LDS copy of the
 //                   brick's DoF lattice (a brick whose cells are all active by 1D line
-//                   sweeps over the whole lattice, others cell by cell), then its
-//                   surrogate-boundary faces (Alg. 3); points strictly inside the brick are
+//                   sweeps over the whole lattice, others cell by cell; 3D p <= 3: every
+//                   cell by p + 1 lanes), with the rows of its surrogate-boundary faces
+//                   (Alg. 3); points strictly inside the brick are
 //                   then stored to v directly, points on the brick's boundary (shared with
 //                   neighbouring bricks) go to halo slots that halo_reduce_kernel sums.
 //   sbm_face_cg_kernel  CG surrogate-boundary faces (Alg. 3), before the bricks: (Rv, Rg)
@@ -32,6 +33,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <type_traits>
 
 #include "sbm_internal.h"
 
@@ -78,15 +80,18 @@ inline int two_per_cu() {
 // ((BX p + 1)(BY p + 1)(BZ p + 1) values) stays near 20 KB in FP64.
 template <int D, int P>
 struct BrickDims {
-  // 3D: p=1 8x8x8, p=2 8x4x4, p=3 4x4x4, p=4,5 4x2x2, p=6 2x2x1, p=7 2x2x2, p=8 2x2x1 (at
-  // p=4, 4x2x2 measured faster than 4x4x2, whose LDS allowed 3 workgroups per CU, and than
-  // 2x2x2; at p=6, 2x2x1 faster than 2x2x2 on a 48^3 mesh, which has too few 2x2x2 bricks to
-  // fill the device)
+  // 3D, p <= 3 (cell_lanes): cells that fill whole wavefronts of p + 1 lanes per cell, 128 to 168
+  // of them or 64 at p=3 (shapes of half and twice the size measured within 3 % of these, at
+  // p=2 8 % slower at half the size on a 150^3 mesh: more brick boundary)
+  // 3D, p >= 4: p=4,5 4x2x2, p=6 2x2x1, p=7 2x2x2, p=8 2x2x1 (at p=4, 4x2x2 measured faster than
+  // 4x4x2, whose LDS allowed 3 workgroups per CU, and than 2x2x2; at p=6, 2x2x1 faster than 2x2x2
+  // on a 48^3 mesh, which has too few 2x2x2 bricks to fill the device)
   // 2D: 8x8 up to p=2, 4x4 up to p=7, 3x3 for p=8 (a lattice row must fit 32 points)
-  static constexpr int BX = (D == 2) ? (P <= 2 ? 8 : (P <= 7 ? 4 : 3))
-                                     : (P <= 2 ? 8 : (P <= 5 ? 4 : 2));
-  static constexpr int BY = (D == 2) ? BX : (P == 1 ? 8 : (P <= 3 ? 4 : 2));
-  static constexpr int BZ = (D == 2) ? 1 : (P == 1 ? 8 : (P <= 3 ? 4 : (P <= 5 || P == 7 ? 2 : 1)));
+  static constexpr int S3[9][3] = {{1, 1, 1}, {8, 4, 4}, {7, 6, 4}, {8, 4, 2}, {4, 2, 2},
+                                   {4, 2, 2}, {2, 2, 1}, {2, 2, 2}, {2, 2, 1}};
+  static constexpr int BX = (D == 2) ? (P <= 2 ? 8 : (P <= 7 ? 4 : 3)) : S3[P][0];
+  static constexpr int BY = (D == 2) ? BX : S3[P][1];
+  static constexpr int BZ = (D == 2) ? 1 : S3[P][2];
 };
 
 // XCD-aware block order: the dispatcher hands block b to XCD (b mod 8), so give every XCD
@@ -449,6 +454,7 @@ struct BrickArgs {
   const int32_t *face_off;   // n_bricks + 1
   const int32_t *face_loc;   // lattice offset of each face's cell inside its brick
   const int32_t *face_code;  // per face: 2 axis + side
+  const int32_t *cell_face;  // per cell: 64 x (first face of the cell, from the brick's first) + mask of codes
   const int32_t *row_base;   // n_bricks x rows: DoF id of the first globally present point
   const uint32_t *row_gmask; // bit x: lattice point x of the row is a DoF
   const uint32_t *row_bmask; // bit x: ... and is touched by an active cell of this brick
@@ -477,7 +483,7 @@ struct BatchItem {
 // cells per batch on the per-cell path, and the LDS size (the larger of the two paths,
 // which share one buffer).
 template <typename T, int D, int N1>
-struct BrickCfg {
+struct SweepBrickCfg {
   static constexpr int P = N1 - 1, NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB;
   static constexpr int BX = BrickDims<D, P>::BX, BY = BrickDims<D, P>::BY, BZ = BrickDims<D, P>::BZ;
   static constexpr int LX = BX * P + 1, LY = BY * P + 1, LZ = (D == 3) ? BZ * P + 1 : 1;
@@ -515,6 +521,34 @@ struct BrickCfg {
   static constexpr int SMEM = NL + (TAIL_SWEEP > TAIL_CELLS ? TAIL_SWEEP : TAIL_CELLS);
 };
 
+// The brick kernel of 3D p <= 3 takes p + 1 lanes per cell (cells_body), the others the lattice
+// sweeps (sweeps_body).  The line lies where the cells' results still leave four or more wavefronts
+// per SIMD: at p=4 (FP64 160 registers, 1 KB of LDS per cell) the two forms measured alike (64^3:
+// brick kernel 39.5 against 39.1 us FP64, 25.5 against 24.3 us FP32), at p=3 the lanes are ahead
+// (96^3: 52 against 73 us FP64; 24^3: 11 against 24 us FP32).
+template <int D, int N1>
+constexpr bool cell_lanes() {
+  return D == 3 && N1 <= 4;
+}
+
+template <typename T, int N1>
+struct CellBrickCfg {
+  static constexpr int D = 3, P = N1 - 1, NP = N1 * N1, NB = NP * N1;
+  static constexpr int BX = BrickDims<D, P>::BX, BY = BrickDims<D, P>::BY, BZ = BrickDims<D, P>::BZ;
+  static constexpr int LX = BX * P + 1, LY = BY * P + 1, LZ = BZ * P + 1, NROWS = LY * LZ;
+  static constexpr int MAXC = BX * BY * BZ;
+  static constexpr int CPW = 64 / N1;                    // cells per wavefront
+  static constexpr int NW = (MAXC + CPW - 1) / CPW, NT = 64 * NW;
+  // The transposes between x-runs and y-lines: four planes in flight per wavefront, plane-major,
+  // cells SC apart, the rows of a plane RP apart.  They use the LDS of the wavefront's share of the
+  // cells' (p+1)^3 results, which follow.  (The strides with the fewest LDS bank conflicts.)
+  static constexpr int RP = N1 == 6 ? 7 : N1, SC = N1 == 4 ? 17 : RP * N1;
+  static constexpr int TILE = (NB > 4 * SC ? NB : 4 * SC) | (N1 == 4 ? 0 : 1);
+};
+
+template <typename T, int D, int N1>
+struct BrickCfg : std::conditional_t<cell_lanes<D, N1>(), CellBrickCfg<T, N1>, SweepBrickCfg<T, D, N1>> {};
+
 // Lattice-line segments of a full brick.  A line of B cells has B p + 1 nodes; the segment of
 // cell j is nodes j p .. j p + p, and neighbouring segments share one node.  One lane per
 // segment, the B lanes of a line side by side in a group of G = pow2 >= B lanes of one
@@ -538,10 +572,10 @@ struct LaneGroup {
 };
 
 template <typename T, int D, int N1>
-__device__ __forceinline__ void brick_body(const int blk, BrickArgs br, const T *__restrict__ fbuf,
+__device__ __forceinline__ void sweeps_body(const int blk, BrickArgs br, const T *__restrict__ fbuf,
                                            const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
                                            int nhalo, KTab<T, N1> tab, T scale, int parts) {
-  using C = BrickCfg<T, D, N1>;
+  using C = SweepBrickCfg<T, D, N1>;
   constexpr int P = C::P, NP = C::NP, NB = C::NB, EPB = C::EPB;
   constexpr int BX = C::BX, BY = C::BY, BZ = C::BZ, LX = C::LX, LY = C::LY, LZ = C::LZ;
   constexpr int NL = C::NL, NROWS = C::NROWS;
@@ -878,6 +912,358 @@ __device__ __forceinline__ void brick_body(const int blk, BrickArgs br, const T 
       }
     }
   }
+}
+
+// ------------------------------------------------------------------------------------
+// Bricks of 3D cells of low degree (p <= 3): p + 1 lanes per cell, every cell on its own.
+// Lane j of a cell sweeps x-run j of a plane in registers, turns the plane over through LDS
+// (within its wavefront: no barrier), sweeps y-line j, and keeps the p + 1 planes' z sums of its
+// y-line, (p+1)^2 results, in registers; it adds the rows of the cell's surrogate faces there.  The
+// cells' results go to LDS once, and every lattice point then sums its cells' values as it is
+// stored.
+// What bounds it: the latency of a brick's phases on small meshes, and with the device full half of
+// the HBM rate (150^3 Q2 FP64: 6 M DoFs in 69 us).  The lattice sweeps, which take a brick with a
+// missing cell batch by batch with a barrier for each cell and each face of a batch, spent their
+// time in those bricks: these have up to 168 cells, and small meshes hold no others (brick
+// kernel, 45^3 Q2 FP32: 28.3 -> 9.6 us; 30^3 Q1 FP64: 70 -> 8 us; 96^3 Q3 FP64: 73 -> 52 us; 150^3
+// Q2 FP64: 74 -> 69 us).  The x-runs' first DoFs come from the row descriptors: reading them from
+// the cells' table cost 36 B per cell at p=2, 5 % of the kernel.
+// ------------------------------------------------------------------------------------
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// Keeps the computation of x ahead of the branch that follows (LDS reads would sink into it one by
+// one).
+template <typename T>
+__device__ __forceinline__ void settle(T &x) {
+  asm volatile("" : "+v"(x));
+}
+
+template <typename T, int N1>
+__device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const T *__restrict__ fbuf,
+                                           const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
+                                           int nhalo, KTab<T, N1> tab, T scale, int parts) {
+  using C = CellBrickCfg<T, N1>;
+  constexpr int P = N1 - 1, NP = C::NP, HC = (N1 + 1) / 2, HF = N1 / 2, TS = C::TILE;
+  constexpr int BX = C::BX, BY = C::BY, BZ = C::BZ, LX = C::LX, LY = C::LY, LZ = C::LZ, NROWS = C::NROWS;
+  static_assert(LX <= 32, "row masks hold 32 points");
+  __shared__ T tiles[C::NW * C::CPW * TS];
+  // rows of the lattice, sorted by kind: where the points 0 < x < LX-1 go, halo index, masks, and
+  // 256 x (place of the row in the cells' results) + flags
+  using GlobalT = __attribute__((address_space(1))) T;  // (a pointer read from LDS is generic otherwise)
+  __shared__ T *s_dst[NROWS];
+  __shared__ int32_t s_hbase[NROWS], s_off[NROWS];
+  __shared__ uint32_t s_gmask[NROWS], s_bmask[NROWS];
+  __shared__ int32_t s_base[NROWS];   // by the row's place: id of its first DoF,
+  __shared__ uint32_t s_first[NROWS]; // mask of its DoFs
+  constexpr int kLowY = 1, kHighY = 2, kLowZ = 4, kHighZ = 8, kY0 = 16, kZ0 = 32, kEdge = 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c0 = br.cell_off[brick], nc = br.cell_off[brick + 1] - c0, f0 = br.face_off[brick];
+  const bool full = nc == C::MAXC;
+  const int wc = lane / N1, j = lane - wc * N1, c = wave * C::CPW + wc;
+  const bool on = wc < C::CPW && c < nc;
+  const int loc = on ? br.cell_loc[c0 + c] : 0;
+  const int cface = on ? br.cell_face[c0 + c] : 0;
+  // row kinds, in the order of the tables: y and z inside a cell, z inside and y on a plane between
+  // cells, y inside and z on such a plane, both on planes
+  constexpr int YI = BY * (P - 1), ZI = BZ * (P - 1), YB = BY + 1, ZB = BZ + 1;
+  constexpr int K1 = YI * ZI, K2 = K1 + YB * ZI, K3 = K2 + YI * ZB;
+  static_assert(K3 + YB * ZB == NROWS, "every row once");
+  static_assert(NROWS <= C::NT, "one row per thread");
+  const int r = tid < NROWS ? tid : 0;
+  const bool yb = (r >= K1 && r < K2) || r >= K3, zb = r >= K2;
+  const int rq = r - (r >= K3 ? K3 : (r >= K2 ? K2 : (r >= K1 ? K1 : 0)));
+  const int ny = yb ? YB : (YI > 0 ? YI : 1), riy = rq % ny, riz = rq / ny;
+  constexpr int PI = P > 1 ? P - 1 : 1;
+  const int rcy = yb ? riy : riy / PI, rcz = zb ? riz : riz / PI;
+  const int rly = yb ? 0 : 1 + riy - rcy * PI, rlz = zb ? 0 : 1 + riz - rcz * PI;
+  const int ry = rcy * P + rly, rz = rcz * P + rlz;
+  const int64_t rat = (int64_t)brick * NROWS + ry + LY * rz;
+  const int32_t rbase = br.row_base[rat], rhb = br.row_hbase[rat];
+  const uint32_t rgm = full ? ~0u : br.row_gmask[rat], rbm = full ? ~0u : br.row_bmask[rat];
+  if (tid < NROWS) {
+    s_base[ry + LY * rz] = rbase;
+    s_first[ry + LY * rz] = rgm;
+  }
+  __syncthreads();
+  // the cell's place in the brick, and the lane's x-runs (j, k): the first DoF of each from its row
+  const int lcx = (loc % LX) / P, lcy = (loc / LX % LY) / P, lcz = loc / (LX * LY) / P;
+  int32_t run[N1];
+#pragma unroll
+  for (int k = 0; k < N1; ++k) {
+    const int row = lcy * P + (on ? j : 0) + LY * (lcz * P + k);
+    run[k] = s_base[row] + __popc(s_first[row] & ((1u << (lcx * P)) - 1u));
+  }
+  T lo[N1], hi[N1];  // x-runs of planes k and p - k
+  auto fetch = [&](int k) {
+#pragma unroll
+    for (int i = 0; i < N1; ++i) {
+      lo[i] = u[(int64_t)run[k] + i];
+      hi[i] = 2 * k == P ? T(0) : u[(int64_t)run[P - k] + i];
+    }
+  };
+  if (on && (parts & SBM_PART_CELLS)) fetch(0);
+  if (tid < NROWS) {
+    const bool edge = ry == 0 || ry == LY - 1 || rz == 0 || rz == LZ - 1;
+    const int plane = (ry == 0 ? 2 : 0) | (rz == 0 ? 4 : 0);
+    s_dst[r] = edge ? halo + (int64_t)plane * nhalo + rhb : v + rbase;
+    s_hbase[r] = rhb;
+    s_off[r] = (((rcz * BY + rcy) * BX * TS + (rlz * N1 + rly) * N1) << 8) | (yb && rcy > 0 ? kLowY : 0) |
+               (rcy < BY ? kHighY : 0) | (zb && rcz > 0 ? kLowZ : 0) | (rcz < BZ ? kHighZ : 0) | (ry == 0 ? kY0 : 0) |
+               (rz == 0 ? kZ0 : 0) | (edge ? kEdge : 0);
+    s_gmask[r] = rgm;
+    s_bmask[r] = rbm;
+  }
+  T out[N1][N1];  // [z][y] at x = j
+#pragma unroll
+  for (int z = 0; z < N1; ++z)
+#pragma unroll
+    for (int y = 0; y < N1; ++y) out[z][y] = T(0);
+  if (on) {
+    if (parts & SBM_PART_CELLS) {
+      T *const turn = tiles + wave * (C::CPW * TS) + wc * C::SC;  // plane q at q * CPW * SC
+      constexpr int PL = C::CPW * C::SC;
+      T ye[HC][N1], yo[HF][N1];
+#pragma unroll
+      for (int y = 0; y < N1; ++y) {
+#pragma unroll
+        for (int i = 0; i < HC; ++i) ye[i][y] = T(0);
+#pragma unroll
+        for (int i = 0; i < HF; ++i) yo[i][y] = T(0);
+      }
+      // planes k and p - k together, as their sum and difference (the z operators are
+      // centrosymmetric): x sweep of the lane's run in registers, through LDS to the lane's y-line,
+      // y sweep, and the plane's share of the z sweep.  The next two planes are in flight.
+      auto xsweep = [&](const T (&x)[N1], T *dst) {  // a = M x, b = K x of x-run j
+        const EvenOdd<T, N1> ex(x);
+        EOAcc<T, N1> aa, ab;
+        eo_acc<T, N1>(tab.EM, tab.OM, ex, aa.ye, aa.yo);
+        eo_acc<T, N1>(tab.EK, tab.OK, ex, ab.ye, ab.yo);
+        T a[N1], b[N1];
+        eo_combine<T, N1>(aa.ye, aa.yo, T(1), a);
+        eo_combine<T, N1>(ab.ye, ab.yo, T(1), b);
+#pragma unroll
+        for (int i = 0; i < N1; ++i) {
+          dst[C::RP * j + i] = a[i];
+          dst[PL + C::RP * j + i] = b[i];
+        }
+      };
+      auto ysweep = [&](const T *src, T (&cc)[N1], T (&e)[N1]) {  // c = M a, e = K a + M b of y-line j
+        T a[N1], b[N1];
+#pragma unroll
+        for (int i = 0; i < N1; ++i) {
+          a[i] = src[C::RP * i + j];
+          b[i] = src[PL + C::RP * i + j];
+        }
+        const EvenOdd<T, N1> ea(a), eb(b);
+        EOAcc<T, N1> ac, ae;
+        eo_acc<T, N1>(tab.EM, tab.OM, ea, ac.ye, ac.yo);
+        eo_acc<T, N1>(tab.EK, tab.OK, ea, ae.ye, ae.yo);
+        eo_acc<T, N1>(tab.EM, tab.OM, eb, ae.ye, ae.yo);
+        eo_combine<T, N1>(ac.ye, ac.yo, T(1), cc);
+        eo_combine<T, N1>(ae.ye, ae.yo, T(1), e);
+      };
+#pragma unroll
+      for (int k = 0; k < HC; ++k) {
+        const bool mid = 2 * k == P;
+        T xe[N1], xo[N1];
+#pragma unroll
+        for (int i = 0; i < N1; ++i) {
+          xe[i] = mid ? lo[i] : lo[i] + hi[i];
+          xo[i] = lo[i] - hi[i];
+        }
+        if (k + 1 < HC) fetch(k + 1);
+        xsweep(xe, turn);
+        if (!mid) xsweep(xo, turn + 2 * PL);
+        wave_sync();
+        T cc[N1], e[N1];
+        ysweep(turn, cc, e);
+#pragma unroll
+        for (int i = 0; i < HC; ++i)
+#pragma unroll
+          for (int y = 0; y < N1; ++y) ye[i][y] += tab.EK[i * HC + k] * cc[y] + tab.EM[i * HC + k] * e[y];
+        if (!mid) {
+          ysweep(turn + 2 * PL, cc, e);
+#pragma unroll
+          for (int i = 0; i < HF; ++i)
+#pragma unroll
+            for (int y = 0; y < N1; ++y) yo[i][y] += tab.OK[i * HF + k] * cc[y] + tab.OM[i * HF + k] * e[y];
+        }
+        wave_sync();
+      }
+#pragma unroll
+      for (int i = 0; i < HF; ++i)
+#pragma unroll
+        for (int y = 0; y < N1; ++y) {
+          out[i][y] = scale * (ye[i][y] + yo[i][y]);
+          out[P - i][y] = scale * (ye[i][y] - yo[i][y]);
+        }
+      if constexpr (N1 % 2 == 1) {
+#pragma unroll
+        for (int y = 0; y < N1; ++y) out[HF][y] = scale * ye[HF][y];
+      }
+    }
+    if ((parts & SBM_PART_SBM_FACES) && cface) {
+      // the rows of the cell's surrogate faces, in code order, from their (Rv, Rg) per face node
+      const T *R = fbuf + (int64_t)(f0 + (cface >> 6)) * 2 * NP;
+#pragma unroll
+      for (int code = 0; code < 6; ++code) {
+        if (!((cface >> code) & 1)) continue;
+        const int a = code >> 1, s = code & 1;
+        const T *Rv = R, *Rg = R + NP;
+        R += 2 * NP;
+        if (a == 0) {
+          T dj = T(0);
+#pragma unroll
+          for (int i = 0; i < N1; ++i) dj = i == j ? (s ? tab.D1[i] : tab.D0[i]) : dj;
+          const bool at = j == s * P;
+#pragma unroll
+          for (int z = 0; z < N1; ++z)
+#pragma unroll
+            for (int y = 0; y < N1; ++y) out[z][y] += (at ? Rv[y + N1 * z] : T(0)) + dj * Rg[y + N1 * z];
+        } else {
+#pragma unroll
+          for (int t = 0; t < N1; ++t) {
+            const T rv = Rv[j + N1 * t], rg = Rg[j + N1 * t];
+#pragma unroll
+            for (int i = 0; i < N1; ++i) {
+              T &o = a == 1 ? out[t][i] : out[i][t];
+              o += (i == s * P ? rv : T(0)) + (s ? tab.D1[i] : tab.D0[i]) * rg;
+            }
+          }
+        }
+      }
+    }
+  }
+  // the results lie by the cell's place in the brick (a full brick's cells are in place already); a
+  // missing cell's are zero
+  const int place = (lcz * BY + lcy) * BX + lcx;
+  if (!full) {
+    __syncthreads();
+    for (int i = tid; i < C::MAXC * TS; i += C::NT) tiles[i] = T(0);
+    __syncthreads();
+  }
+  if (on) {
+    T *const tile = tiles + place * TS;
+#pragma unroll
+    for (int z = 0; z < N1; ++z)
+#pragma unroll
+      for (int y = 0; y < N1; ++y) tile[(z * N1 + y) * N1 + j] = out[z][y];
+  }
+  __syncthreads();
+  // Assembly and write-out: every lattice point sums its cells' values (z, then y, then x from the
+  // low side: a fixed order) and is stored once.
+  // the rows' ends, all of them brick-boundary points
+  constexpr int NE = (2 * NROWS + C::NT - 1) / C::NT;
+#pragma unroll
+  for (int m = 0; m < NE; ++m) {
+    const int i = tid + m * C::NT, er = i < 2 * NROWS ? i >> 1 : 0, side = i & 1, o = s_off[er];
+    const int off = (o >> 8) + (side ? (BX - 1) * TS + P : 0);
+    const uint32_t gm = s_gmask[er], bm = i < 2 * NROWS ? s_bmask[er] : 0u;
+    const int32_t hb = s_hbase[er];
+    T sum = T(0);
+#pragma unroll
+    for (int dz = 1; dz >= 0; --dz)
+#pragma unroll
+      for (int dy = 1; dy >= 0; --dy) {
+        const bool in = (o & (dy ? kLowY : kHighY)) && (o & (dz ? kLowZ : kHighZ));
+        const T val = tiles[in ? off - dz * (BY * BX * TS - P * NP) - dy * (BX * TS - P * N1) : 0];
+        sum += in ? val : T(0);
+      }
+    const int x = side ? LX - 1 : 0;
+    // (the row's brick-boundary DoFs follow each other: all of it on the brick's y or z sides,
+    // else the two ends)
+    const uint32_t hgm = (o & kEdge) ? gm : (gm & (1u | (1u << (LX - 1))));
+    const int plane = (side ? 0 : 1) | ((o & kY0) ? 2 : 0) | ((o & kZ0) ? 4 : 0);
+    if ((bm >> x) & 1u) halo[(int64_t)plane * nhalo + hb + __popc(hgm & ((1u << x) - 1u))] = sum;
+  }
+  // the points 0 < x < LX-1: lanes take whole rows, so that a lane's x is fixed, and the rows of one
+  // kind sum equally many cells
+  {
+    constexpr int W = LX - 2, RPW = 64 / W, STEP = C::NW * RPW;
+    static_assert(RPW >= 1, "a wavefront holds at least one row");
+    const int rl = lane / W, x = 1 + lane - rl * W, cx = x / P;
+    const uint32_t below = (1u << x) - 1u;
+    const int xa = cx * TS + (x - cx * P), xb = (cx - 1) * TS + P;
+    const bool two = x == cx * P;  // a point between two cells
+    // (up to four rows per lane at a time, every LDS read before the first store: the row loop one
+    // by one spent its time on the latency of three dependent LDS reads)
+    auto rows = [&](auto r0_, auto r1_, auto yb_, auto zb_) {
+      constexpr int R0 = decltype(r0_)::value, R1 = decltype(r1_)::value;
+      constexpr bool YB_ = decltype(yb_)::value, ZB_ = decltype(zb_)::value;
+      constexpr int NPASS = (R1 - R0 + STEP - 1) / STEP, CH = NPASS < 4 ? NPASS : 4;
+      if constexpr (NPASS > 0) {
+#pragma unroll
+        for (int k0 = 0; k0 < NPASS; k0 += CH) {
+          int o[CH];
+          T *dst[CH];
+          uint32_t gm[CH], bm[CH];
+          T sum[CH];
+#pragma unroll
+          for (int k = 0; k < CH; ++k) {
+            const int r = R0 + wave * RPW + rl + (k0 + k) * STEP;
+            const int rc = r < R1 ? r : R1 - 1;
+            o[k] = s_off[rc];
+            dst[k] = s_dst[rc];
+            gm[k] = s_gmask[rc];
+            bm[k] = r < R1 ? s_bmask[rc] : 0u;
+            sum[k] = T(0);
+          }
+#pragma unroll
+          for (int dz = ZB_ ? 1 : 0; dz >= 0; --dz)
+#pragma unroll
+            for (int dy = YB_ ? 1 : 0; dy >= 0; --dy) {
+              constexpr int kNone = 0;
+              const int need = (YB_ ? (dy ? kLowY : kHighY) : kNone) | (ZB_ ? (dz ? kLowZ : kHighZ) : kNone);
+              const int back = dz * (BY * BX * TS - P * NP) + dy * (BX * TS - P * N1);
+              T lo[CH], hi[CH];
+#pragma unroll
+              for (int k = 0; k < CH; ++k) {
+                const bool in = (o[k] & need) == need;
+                const int off = in ? (o[k] >> 8) - back : 0;
+                lo[k] = tiles[in && two ? off + xb : 0];
+                hi[k] = tiles[off + xa];
+              }
+#pragma unroll
+              for (int k = 0; k < CH; ++k) {
+                settle(lo[k]);
+                settle(hi[k]);
+                const bool in = (o[k] & need) == need;
+                lo[k] = in && two ? lo[k] : T(0);
+                hi[k] = in ? hi[k] : T(0);
+              }
+#pragma unroll
+              for (int k = 0; k < CH; ++k) sum[k] += lo[k] + hi[k];
+            }
+#pragma unroll
+          for (int k = 0; k < CH; ++k) settle(sum[k]);
+#pragma unroll
+          for (int k = 0; k < CH; ++k)
+            if ((bm[k] >> x) & 1u) ((GlobalT *)dst[k])[__popc(gm[k] & below)] = sum[k];
+        }
+      }
+    };
+    if (rl < RPW) {
+      using std::integral_constant;
+      rows(integral_constant<int, 0>{}, integral_constant<int, K1>{}, std::false_type{}, std::false_type{});
+      rows(integral_constant<int, K1>{}, integral_constant<int, K2>{}, std::true_type{}, std::false_type{});
+      rows(integral_constant<int, K2>{}, integral_constant<int, K3>{}, std::false_type{}, std::true_type{});
+      rows(integral_constant<int, K3>{}, integral_constant<int, NROWS>{}, std::true_type{}, std::true_type{});
+    }
+  }
+}
+
+template <typename T, int D, int N1>
+__device__ __forceinline__ void brick_body(const int blk, BrickArgs br, const T *__restrict__ fbuf,
+                                           const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
+                                           int nhalo, KTab<T, N1> tab, T scale, int parts) {
+  if constexpr (cell_lanes<D, N1>())
+    cells_body<T, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
+  else
+    sweeps_body<T, D, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
 }
 
 template <typename T, int D, int N1>
@@ -1483,7 +1869,7 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
     if (c->n_bricks > 0 && (parts & (SBM_PART_CELLS | SBM_PART_SBM_FACES))) {
       constexpr int NT = BrickCfg<T, D, N1>::NT;
       const BrickArgs br{c->d_brick_cell_off, c->d_brick_runs, c->d_brick_cell_loc, c->d_brick_face_off,
-                         c->d_brick_face_loc, c->d_face_code,  c->d_row_base,       c->d_row_gmask,
+                         c->d_brick_face_loc, c->d_face_code,  c->d_brick_cell_face, c->d_row_base,       c->d_row_gmask,
                          c->d_row_bmask,      c->d_row_hbase};
       T *halo = (T *)scr.halo;
       T *fbuf = (T *)scr.fbuf;
@@ -1885,7 +2271,7 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
     if (!ok) return hipErrorInvalidValue;
     BatchItem &it = items[i];
     it.br = BrickArgs{c->d_brick_cell_off, c->d_brick_runs, c->d_brick_cell_loc, c->d_brick_face_off,
-                      c->d_brick_face_loc, c->d_face_code,  c->d_row_base,       c->d_row_gmask,
+                      c->d_brick_face_loc, c->d_face_code,  c->d_brick_cell_face, c->d_row_base,       c->d_row_gmask,
                       c->d_row_bmask,      c->d_row_hbase};
     it.face_code = c->d_face_code;
     it.face_runs = c->d_face_runs;

@@ -107,6 +107,9 @@ struct sbm_ctx {
   std::vector<int32_t> brick_runs;  // run bases of the cells in brick order (n_cells x (p+1)^(d-1))
   std::vector<int32_t> face_runs;   // run bases of each surrogate face's cell, faces in brick order
   std::vector<int32_t> brick_face_off, brick_faces, brick_face_loc;
+  // per cell in brick order: 64 x (its first surrogate face, from the brick's first) + the mask of
+  // the codes 2 axis + side of its faces (they follow each other in code order)
+  std::vector<int32_t> brick_cell_face;
   std::vector<int32_t> row_base, row_hbase;
   std::vector<uint32_t> row_gmask, row_bmask;
   // halo assembly: a DoF on brick boundaries collects one value per touching brick, in plane
@@ -121,7 +124,7 @@ struct sbm_ctx {
   void *d_fbuf = nullptr;  // n_sbm x 2 x (p+1)^(d-1) doubles, surrogate-face results; per-handle scratch
   int32_t *d_brick_cell_off = nullptr, *d_brick_runs = nullptr, *d_brick_cell_loc = nullptr;
   int32_t *d_face_runs = nullptr;
-  int32_t *d_brick_face_off = nullptr, *d_brick_face_loc = nullptr;
+  int32_t *d_brick_face_off = nullptr, *d_brick_face_loc = nullptr, *d_brick_cell_face = nullptr;
   int32_t *d_row_base = nullptr;
   uint32_t *d_row_gmask = nullptr, *d_row_bmask = nullptr;
   // device copies (all inside one allocation, d_arena)

@@ -369,7 +369,7 @@ static void free_device(sbm_ctx *c) {
   c->d_runs = c->d_nbr = c->d_face_cell = c->d_face_code = nullptr;
   c->d_face_xi = nullptr;
   c->d_brick_cell_off = c->d_brick_runs = c->d_face_runs = c->d_brick_cell_loc = nullptr;
-  c->d_brick_face_off = c->d_brick_face_loc = c->d_row_base = c->d_row_hbase = c->d_halo_dof = nullptr;
+  c->d_brick_face_off = c->d_brick_face_loc = c->d_brick_cell_face = c->d_row_base = c->d_row_hbase = c->d_halo_dof = nullptr;
   c->d_row_gmask = c->d_row_bmask = nullptr;
   c->d_halo_mask = nullptr;
   c->d_halo = c->d_fbuf = nullptr;
@@ -479,6 +479,17 @@ static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx,
       c->brick_faces[fill[b]] = (int32_t)f;
       c->brick_face_loc[fill[b]] = cell_loc(r, bkey[r]);
       ++fill[b];
+    }
+  }
+  c->brick_cell_face.assign(nc, 0);
+  {
+    std::vector<int32_t> at(nc);
+    for (int64_t i = 0; i < nc; ++i) at[c->brick_cells[i]] = (int32_t)i;
+    for (int64_t i = 0; i < nf; ++i) {
+      const int32_t *fc = &c->faces[3 * (int64_t)c->brick_faces[i]];
+      int32_t &m = c->brick_cell_face[at[fc[0]]];
+      if (m == 0) m = (int32_t)(i - c->brick_face_off[bid[bkey[fc[0]]]]) << 6;
+      m |= 1 << (2 * fc[1] + fc[2]);
     }
   }
   // run bases of each surrogate face's cell, faces in brick order (the device copies of the
@@ -964,6 +975,7 @@ sbm_status sbm_setup(const sbm_mesh *mesh, const sbm_levelset *ls, int p, int di
     plan.add(c->d_brick_cell_loc, c->brick_cell_loc);
     plan.add(c->d_brick_face_off, c->brick_face_off);
     plan.add(c->d_brick_face_loc, c->brick_face_loc);
+    plan.add(c->d_brick_cell_face, c->brick_cell_face);
     plan.add(c->d_row_base, c->row_base);
     plan.add(c->d_row_gmask, c->row_gmask);
     plan.add(c->d_row_bmask, c->row_bmask);
@@ -1212,7 +1224,7 @@ size_t sbm_footprint_estimate(const sbm_mesh *mesh, int p, int disc, int64_t n_c
     const int64_t rows = (B[1] * p + 1) * (d == 3 ? B[2] * p + 1 : 1);  // lattice rows per brick
     const int64_t nbricks = nc;                                        // every brick has a cell
     b += up(4 * nc * np) * 2;                                          // runs, brick_runs
-    b += up(4 * (nbricks + 1)) * 2 + up(4 * nc) + up(4 * nf);          // offsets, cell/face locations
+    b += up(4 * (nbricks + 1)) * 2 + up(4 * nc) * 2 + up(4 * nf);      // offsets, cell/face locations
     b += up(4 * nf * np);                                              // face_runs
     b += 4 * up(4 * nbricks * rows);                                   // row descriptors
     b += up(4 * halo) + up(halo);                                      // halo DoF ids and masks

@@ -223,21 +223,29 @@ __global__ void brick_count_kernel(Geo g, Bricks bk, int64_t nc, int64_t nf, con
 // A brick's cells in rank order: the position of a cell is the number of active cells of its
 // brick that come before it (z, then y, then x, as the ranks).
 __global__ void brick_cells_kernel(Geo g, Bricks bk, int64_t nc, const int32_t *cells, const int32_t *rank_grid,
-                                   const int32_t *bid, const int32_t *cell_off, const int32_t *runs,
-                                   int32_t *brick_cell_loc, int32_t *brick_runs) {
+                                   const int32_t *sflag, const int32_t *bid, const int32_t *cell_off,
+                                   const int32_t *runs, int32_t *brick_cell_loc, int32_t *brick_cell_face,
+                                   int32_t *brick_runs) {
   GRID_LOOP(r, nc) {
     const int32_t *cc = cells + r * g.d;
     const int64_t key = brick_key(g, bk, cc);
     const int64_t x0 = cc[0] - cc[0] % bk.BX, y0 = cc[1] - cc[1] % bk.BY;
     const int64_t z0 = g.d == 3 ? cc[2] - cc[2] % bk.BZ : 0;
     const int64_t me = ((g.d == 3 ? cc[2] : 0) - z0) * bk.BY * bk.BX + (cc[1] - y0) * bk.BX + (cc[0] - x0);
-    int pos = 0;
+    const int ncode = 2 * g.d;
+    int pos = 0, fpos = 0;
     for (int64_t q = 0; q < me; ++q) {
       const int64_t ox = q % bk.BX, oy = (q / bk.BX) % bk.BY, oz = q / (bk.BX * bk.BY);
-      pos += cell_active(g, rank_grid, x0 + ox, y0 + oy, z0 + oz) ? 1 : 0;
+      if (!cell_active(g, rank_grid, x0 + ox, y0 + oy, z0 + oz)) continue;
+      const int64_t rr = rank_grid[((z0 + oz) * g.ny + y0 + oy) * g.nx + x0 + ox];
+      ++pos;
+      for (int c2 = 0; c2 < ncode; ++c2) fpos += sflag[rr * ncode + c2];
     }
     const int64_t i = cell_off[bid[key]] + pos;
     brick_cell_loc[i] = cell_loc(g, bk, cc);
+    int32_t mask = 0;
+    for (int c2 = 0; c2 < ncode; ++c2) mask |= sflag[r * ncode + c2] ? 1 << c2 : 0;
+    brick_cell_face[i] = mask ? fpos << 6 | mask : 0;
     for (int t = 0; t < g.np; ++t) brick_runs[i * g.np + t] = runs[r * g.np + t];
   }
 }
@@ -638,6 +646,7 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     cv.add(c->d_brick_cell_loc, nc);
     cv.add(c->d_brick_face_off, nbk + 1);
     cv.add(c->d_brick_face_loc, nf);
+    cv.add(c->d_brick_cell_face, nc);
     cv.add(c->d_row_base, nrow_all);
     cv.add(c->d_row_gmask, nrow_all);
     cv.add(c->d_row_bmask, nrow_all);
@@ -679,8 +688,9 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
              "upload");
     if (nc > 0) {
       DS_CHECK(hipMemcpyAsync(c->d_runs, runs, sizeof(int32_t) * nc * g.np, hipMemcpyDeviceToDevice, s), "copy");
-      hipLaunchKernelGGL(brick_cells_kernel, dim3(grid_for(nc)), dim3(kT), 0, s, g, bk, nc, cells, rank_grid, d_bid,
-                         c->d_brick_cell_off, runs, c->d_brick_cell_loc, c->d_brick_runs);
+      hipLaunchKernelGGL(brick_cells_kernel, dim3(grid_for(nc)), dim3(kT), 0, s, g, bk, nc, cells, rank_grid, sflag,
+                         d_bid, c->d_brick_cell_off, runs, c->d_brick_cell_loc, c->d_brick_cell_face,
+                         c->d_brick_runs);
     }
     if (nf > 0)
       hipLaunchKernelGGL(brick_faces_kernel, dim3(grid_for(nf)), dim3(kT), 0, s, g, bk, nf, cells, rank_grid, faces,
