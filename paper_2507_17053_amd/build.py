@@ -21,7 +21,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsbm.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["setup.cpp", "kernels_apply.hip", "kernels_taylor.hip", "vec.hip", "solver.hip",
+SOURCES = ["setup.cpp", "kernels_apply.hip", "kernels_taylor.hip", "vec.hip", "rhs.hip", "solver.hip",
            "apply_noalloc.hip", "setup_gpu.hip", "batch.cpp"]
 # per-file flags: the device setup evaluates the level sets with the same floating-point
 # operations as the host build (no multiply-add contraction), so both agree bit for bit
