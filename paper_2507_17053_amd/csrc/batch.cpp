@@ -118,8 +118,8 @@ sbm_status build(int n, const sbm_handle *hs, const void *const *u, void *const 
     set_error("sbm_batch_create: no device");
     return SBM_EHIP;
   }
-  // groups by (discretisation, dimension, degree), in order of first appearance
-  std::map<std::tuple<int, int, int>, int> gid;
+  // groups by (discretisation, dimension, degree, brick-kernel form), in order of first appearance
+  std::map<std::tuple<int, int, int, int>, int> gid;
   std::vector<std::vector<int>> members;
   for (int i = 0; i < n; ++i) {
     sbm_ctx *c = hs[i];
@@ -129,7 +129,7 @@ sbm_status build(int n, const sbm_handle *hs, const void *const *u, void *const 
     b->u.push_back(u[i]);
     b->v.push_back(v[i]);
     if (c->taylor_m >= 0) b->taylor.push_back(k);
-    auto key = std::make_tuple(c->disc, c->dim, c->p);
+    auto key = std::make_tuple(c->disc, c->dim, c->p, (int)c->lanes);
     auto it = gid.find(key);
     if (it == gid.end()) {
       it = gid.emplace(key, (int)members.size()).first;

@@ -78,20 +78,21 @@ inline int two_per_cu() {
 
 // Brick of background cells per CG workgroup, chosen per degree so that the LDS lattice
 // ((BX p + 1)(BY p + 1)(BZ p + 1) values) stays near 20 KB in FP64.
-template <int D, int P>
+template <int D, int P, bool LANES>
 struct BrickDims {
-  // 3D, p <= 3 (cell_lanes): cells that fill whole wavefronts of p + 1 lanes per cell, 128 to 168
-  // of them or 64 at p=3 (shapes of half and twice the size measured within 3 % of these, at
-  // p=2 8 % slower at half the size on a 150^3 mesh: more brick boundary)
+  // 3D by p + 1 lanes per cell (LANES, p <= 3): cells that fill whole wavefronts, 8x4x4, 7x6x4 and
+  // 8x4x2 (shapes of half and twice the size measured within 3 % of these, at p=2 8 % slower at
+  // half the size on a 150^3 mesh: more brick boundary); p=1 by sweeps 8x8x8
   // 3D, p >= 4: p=4,5 4x2x2, p=6 2x2x1, p=7 2x2x2, p=8 2x2x1 (at p=4, 4x2x2 measured faster than
   // 4x4x2, whose LDS allowed 3 workgroups per CU, and than 2x2x2; at p=6, 2x2x1 faster than 2x2x2
   // on a 48^3 mesh, which has too few 2x2x2 bricks to fill the device)
   // 2D: 8x8 up to p=2, 4x4 up to p=7, 3x3 for p=8 (a lattice row must fit 32 points)
-  static constexpr int S3[9][3] = {{1, 1, 1}, {8, 4, 4}, {7, 6, 4}, {8, 4, 2}, {4, 2, 2},
+  static constexpr int S3[9][3] = {{1, 1, 1}, {8, 8, 8}, {7, 6, 4}, {8, 4, 2}, {4, 2, 2},
                                    {4, 2, 2}, {2, 2, 1}, {2, 2, 2}, {2, 2, 1}};
+  static constexpr bool SMALL = D == 3 && P == 1 && LANES;  // 8x4x4
   static constexpr int BX = (D == 2) ? (P <= 2 ? 8 : (P <= 7 ? 4 : 3)) : S3[P][0];
-  static constexpr int BY = (D == 2) ? BX : S3[P][1];
-  static constexpr int BZ = (D == 2) ? 1 : S3[P][2];
+  static constexpr int BY = (D == 2) ? BX : (SMALL ? 4 : S3[P][1]);
+  static constexpr int BZ = (D == 2) ? 1 : (SMALL ? 4 : S3[P][2]);
 };
 
 // XCD-aware block order: the dispatcher hands block b to XCD (b mod 8), so give every XCD
@@ -485,7 +486,8 @@ struct BatchItem {
 template <typename T, int D, int N1>
 struct SweepBrickCfg {
   static constexpr int P = N1 - 1, NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB;
-  static constexpr int BX = BrickDims<D, P>::BX, BY = BrickDims<D, P>::BY, BZ = BrickDims<D, P>::BZ;
+  static constexpr int BX = BrickDims<D, P, false>::BX, BY = BrickDims<D, P, false>::BY,
+                       BZ = BrickDims<D, P, false>::BZ;
   static constexpr int LX = BX * P + 1, LY = BY * P + 1, LZ = (D == 3) ? BZ * P + 1 : 1;
   static constexpr int NL = LX * LY * LZ, NROWS = LY * LZ;
   static constexpr int LINES = (D == 3) ? ((LX * LY > LX * LZ ? LX * LY : LX * LZ) > LY * LZ
@@ -525,16 +527,25 @@ struct SweepBrickCfg {
 // sweeps (sweeps_body).  The line lies where the cells' results still leave four or more wavefronts
 // per SIMD: at p=4 (FP64 160 registers, 1 KB of LDS per cell) the two forms measured alike (64^3:
 // brick kernel 39.5 against 39.1 us FP64, 25.5 against 24.3 us FP32), at p=3 the lanes are ahead
-// (96^3: 52 against 73 us FP64; 24^3: 11 against 24 us FP32).
+// (96^3: 52 against 73 us FP64; 24^3: 11 against 24 us FP32).  At p=1 it also depends on the size:
+// the lanes' smaller bricks leave more DoFs on brick boundaries (51 % against 33 %), which decides
+// once the device is full several times over (FP64 / FP32 apply of 2.4 M cells 79 / - against 113
+// us, of 5.7 M 158 / 125 against 155 / 116, of 9.6 M 254 / 197 against 226 / 150): kLanesMaxCells1.
+constexpr int64_t kLanesMaxCells1 = (int64_t)1 << 22;
 template <int D, int N1>
-constexpr bool cell_lanes() {
+constexpr bool has_lanes() {
   return D == 3 && N1 <= 4;
+}
+template <int D, int N1>
+constexpr bool has_sweeps() {
+  return !has_lanes<D, N1>() || N1 == 2;
 }
 
 template <typename T, int N1>
 struct CellBrickCfg {
   static constexpr int D = 3, P = N1 - 1, NP = N1 * N1, NB = NP * N1;
-  static constexpr int BX = BrickDims<D, P>::BX, BY = BrickDims<D, P>::BY, BZ = BrickDims<D, P>::BZ;
+  static constexpr int BX = BrickDims<D, P, true>::BX, BY = BrickDims<D, P, true>::BY,
+                       BZ = BrickDims<D, P, true>::BZ;
   static constexpr int LX = BX * P + 1, LY = BY * P + 1, LZ = BZ * P + 1, NROWS = LY * LZ;
   static constexpr int MAXC = BX * BY * BZ;
   static constexpr int CPW = 64 / N1;                    // cells per wavefront
@@ -546,8 +557,8 @@ struct CellBrickCfg {
   static constexpr int TILE = (NB > 4 * SC ? NB : 4 * SC) | (N1 == 4 ? 0 : 1);
 };
 
-template <typename T, int D, int N1>
-struct BrickCfg : std::conditional_t<cell_lanes<D, N1>(), CellBrickCfg<T, N1>, SweepBrickCfg<T, D, N1>> {};
+template <typename T, int D, int N1, bool LANES>
+struct BrickCfg : std::conditional_t<LANES, CellBrickCfg<T, N1>, SweepBrickCfg<T, D, N1>> {};
 
 // Lattice-line segments of a full brick.  A line of B cells has B p + 1 nodes; the segment of
 // cell j is nodes j p .. j p + p, and neighbouring segments share one node.  One lane per
@@ -1256,21 +1267,21 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
   }
 }
 
-template <typename T, int D, int N1>
+template <typename T, int D, int N1, bool LANES>
 __device__ __forceinline__ void brick_body(const int blk, BrickArgs br, const T *__restrict__ fbuf,
                                            const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
                                            int nhalo, KTab<T, N1> tab, T scale, int parts) {
-  if constexpr (cell_lanes<D, N1>())
+  if constexpr (LANES)
     cells_body<T, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
   else
     sweeps_body<T, D, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
 }
 
-template <typename T, int D, int N1>
-__global__ __launch_bounds__((BrickCfg<T, D, N1>::NT)) void brick_kernel(
+template <typename T, int D, int N1, bool LANES>
+__global__ __launch_bounds__((BrickCfg<T, D, N1, LANES>::NT)) void brick_kernel(
     BrickArgs br, const T *__restrict__ fbuf, const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
     int nhalo, KTab<T, N1> tab, T scale, int parts) {
-  brick_body<T, D, N1>(xcd_block(), br, fbuf, u, v, halo, nhalo, tab, scale, parts);
+  brick_body<T, D, N1, LANES>(xcd_block(), br, fbuf, u, v, halo, nhalo, tab, scale, parts);
 }
 
 // v[dof] = sum over the planes k present in the DoF's mask, in increasing k (deterministic).
@@ -1867,7 +1878,6 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
   const int nc = (int)c->n_cells, nf = (int)c->n_sbm;
   if (c->disc == SBM_CG) {
     if (c->n_bricks > 0 && (parts & (SBM_PART_CELLS | SBM_PART_SBM_FACES))) {
-      constexpr int NT = BrickCfg<T, D, N1>::NT;
       const BrickArgs br{c->d_brick_cell_off, c->d_brick_runs, c->d_brick_cell_loc, c->d_brick_face_off,
                          c->d_brick_face_loc, c->d_face_code,  c->d_brick_cell_face, c->d_row_base,       c->d_row_gmask,
                          c->d_row_bmask,      c->d_row_hbase};
@@ -1881,8 +1891,16 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
                            c->d_face_code, c->d_face_runs, c->d_face_xi, u, fbuf, tab, sc);
       }
       const int nh = (int)c->n_halo_dofs;
-      hipLaunchKernelGGL((brick_kernel<T, D, N1>), dim3((unsigned)c->n_bricks), dim3(NT), 0, s, br,
-                         (const T *)fbuf, u, v, halo, nh, tab, scale, parts);
+      auto bricks = [&](auto lanes) {
+        constexpr bool LANES = decltype(lanes)::value;
+        hipLaunchKernelGGL((brick_kernel<T, D, N1, LANES>), dim3((unsigned)c->n_bricks),
+                           dim3(BrickCfg<T, D, N1, LANES>::NT), 0, s, br, (const T *)fbuf, u, v, halo, nh, tab, scale,
+                           parts);
+      };
+      if constexpr (has_lanes<D, N1>())
+        if (c->lanes) bricks(std::true_type{});
+      if constexpr (has_sweeps<D, N1>())
+        if (!c->lanes) bricks(std::false_type{});
       if (nh > 0 && !(parts & SBM_PART_NO_ASSEMBLY)) {
         constexpr int HB = kHaloPerThread * 256;  // DoFs per block
         hipLaunchKernelGGL((halo_reduce_kernel<T, D>), dim3((nh + HB - 1) / HB), dim3(256), 0, s, nh, c->d_halo_dof,
@@ -1950,13 +1968,13 @@ struct BatchShape {
   static constexpr int TC = EC * NP;
 };
 
-template <typename T, int D, int N1>
-__global__ __launch_bounds__((BrickCfg<T, D, N1>::NT)) void brick_batch_kernel(const BatchItem *__restrict__ items,
+template <typename T, int D, int N1, bool LANES>
+__global__ __launch_bounds__((BrickCfg<T, D, N1, LANES>::NT)) void brick_batch_kernel(const BatchItem *__restrict__ items,
                                                                               const int32_t *__restrict__ blk_item,
                                                                               KTab<T, N1> tab) {
   const int g = xcd_block();
   const BatchItem *it = items + blk_item[g];
-  brick_body<T, D, N1>(g - it->blk0[1], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v, (T *)it->halo,
+  brick_body<T, D, N1, LANES>(g - it->blk0[1], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v, (T *)it->halo,
                        it->nh, tab, T(D == 3 ? it->sc.h : 1.0), SBM_PART_ALL);
 }
 
@@ -2034,9 +2052,16 @@ hipError_t batch_launch_impl(const BatchGroup &g, const unsigned char *base, hip
     if (g.nblk[0] > 0)
       hipLaunchKernelGGL((sbm_face_cg_batch_kernel<T, D, N1, S::EF>), dim3(g.nblk[0]), dim3(S::EF * S::NP), 0, s,
                          items, bi[0], tab);
-    if (g.nblk[1] > 0)
-      hipLaunchKernelGGL((brick_batch_kernel<T, D, N1>), dim3(g.nblk[1]), dim3(BrickCfg<T, D, N1>::NT), 0, s, items,
-                         bi[1], tab);
+    auto bricks = [&](auto lanes) {
+      constexpr bool LANES = decltype(lanes)::value;
+      if (g.nblk[1] > 0)
+        hipLaunchKernelGGL((brick_batch_kernel<T, D, N1, LANES>), dim3(g.nblk[1]), dim3(BrickCfg<T, D, N1, LANES>::NT),
+                           0, s, items, bi[1], tab);
+    };
+    if constexpr (has_lanes<D, N1>())
+      if (g.first->lanes) bricks(std::true_type{});
+    if constexpr (has_sweeps<D, N1>())
+      if (!g.first->lanes) bricks(std::false_type{});
     if (g.nblk[2] > 0)
       hipLaunchKernelGGL((halo_reduce_batch_kernel<T, D>), dim3(g.nblk[2]), dim3(256), 0, s, items, bi[2]);
   } else {
@@ -2221,16 +2246,22 @@ hipError_t apply_dim(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t 
 
 }  // namespace
 
-void brick_dims(int dim, int p, int *bx, int *by, int *bz) {
-#define SBM_BD(D_, P_)                  \
-  if (dim == D_ && p == P_) {           \
-    *bx = BrickDims<D_, P_>::BX;        \
-    *by = BrickDims<D_, P_>::BY;        \
-    *bz = BrickDims<D_, P_>::BZ;        \
-    return;                             \
+bool brick_lanes(int dim, int p, int64_t n_cells) {
+  return dim == 3 && p <= 3 && (p > 1 || n_cells <= kLanesMaxCells1);
+}
+
+void brick_dims(int dim, int p, bool lanes, int *bx, int *by, int *bz) {
+#define SBM_BD(D_, P_, L_)                 \
+  if (dim == D_ && p == P_ && lanes == L_) { \
+    *bx = BrickDims<D_, P_, L_>::BX;       \
+    *by = BrickDims<D_, P_, L_>::BY;       \
+    *bz = BrickDims<D_, P_, L_>::BZ;       \
+    return;                                \
   }
-  SBM_BD(2, 1) SBM_BD(2, 2) SBM_BD(2, 3) SBM_BD(2, 4) SBM_BD(2, 5) SBM_BD(2, 6) SBM_BD(2, 7) SBM_BD(2, 8)
-  SBM_BD(3, 1) SBM_BD(3, 2) SBM_BD(3, 3) SBM_BD(3, 4) SBM_BD(3, 5) SBM_BD(3, 6) SBM_BD(3, 7) SBM_BD(3, 8)
+  SBM_BD(2, 1, false) SBM_BD(2, 2, false) SBM_BD(2, 3, false) SBM_BD(2, 4, false)
+  SBM_BD(2, 5, false) SBM_BD(2, 6, false) SBM_BD(2, 7, false) SBM_BD(2, 8, false)
+  SBM_BD(3, 1, true) SBM_BD(3, 2, true) SBM_BD(3, 3, true) SBM_BD(3, 1, false) SBM_BD(3, 4, false)
+  SBM_BD(3, 5, false) SBM_BD(3, 6, false) SBM_BD(3, 7, false) SBM_BD(3, 8, false)
 #undef SBM_BD
   *bx = *by = *bz = 1;
 }
@@ -2262,7 +2293,7 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
   int64_t tot[3] = {0, 0, 0};
   for (size_t i = 0; i < cs.size(); ++i) {
     const sbm_ctx *c = cs[i];
-    if (c->disc != c0->disc || c->dim != c0->dim || c->p != c0->p) return hipErrorInvalidValue;
+    if (c->disc != c0->disc || c->dim != c0->dim || c->p != c0->p || c->lanes != c0->lanes) return hipErrorInvalidValue;
     int32_t nb[3] = {0, 0, 0};
     const bool ok = g.prec == SBM_F64 ? (c->dim == 3 ? batch_blocks_dim<double, 3>(c, own_faces[i] != 0, nb)
                                                      : batch_blocks_dim<double, 2>(c, own_faces[i] != 0, nb))

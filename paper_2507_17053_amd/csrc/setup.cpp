@@ -408,7 +408,8 @@ int64_t order_bricks(const std::vector<int32_t> &count, const std::vector<int32_
 static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx, int64_t ly, int64_t lz) {
   const int d = c->dim, p = c->p;
   int BX, BY, BZ;
-  brick_dims(d, p, &BX, &BY, &BZ);
+  c->lanes = brick_lanes(d, p, c->n_cells);
+  brick_dims(d, p, c->lanes, &BX, &BY, &BZ);
   if (d == 2) BZ = 1;
   c->brick[0] = BX;
   c->brick[1] = BY;
@@ -1214,7 +1215,8 @@ size_t sbm_footprint_estimate(const sbm_mesh *mesh, int p, int disc, int64_t n_c
   if (disc == SBM_CG) {
     const int64_t ndofs = nc * nb;  // every active cell touches (p+1)^d lattice points
     int bx = 1, by = 1, bz = 1;
-    brick_dims(d, p, &bx, &by, &bz);
+    const bool lanes = brick_lanes(d, p, nc);
+    brick_dims(d, p, lanes, &bx, &by, &bz);
     const int64_t B[3] = {bx, by, d == 3 ? bz : 1};
     // brick-boundary points of one cell: on each axis it meets both brick planes if the brick
     // is one cell wide there, else at most one
@@ -1223,10 +1225,18 @@ size_t sbm_footprint_estimate(const sbm_mesh *mesh, int p, int disc, int64_t n_c
     const int64_t halo = std::min<int64_t>(ndofs, nc * (nb - inner));
     const int64_t rows = (B[1] * p + 1) * (d == 3 ? B[2] * p + 1 : 1);  // lattice rows per brick
     const int64_t nbricks = nc;                                        // every brick has a cell
+    int64_t nrows = nbricks * rows;
+    if (lanes) {
+      // (bricks of many rows, but no more of them than the mesh has places: bounded by 81 or 169
+      // rows per cell unless the domain is that sparse)
+      int64_t places = 1;
+      for (int k = 0; k < d; ++k) places *= (mesh->n[k] + B[k] - 1) / B[k];
+      nrows = std::max(nbricks * (p <= 2 ? 81 : 169), std::min(nbricks, places) * rows);
+    }
     b += up(4 * nc * np) * 2;                                          // runs, brick_runs
     b += up(4 * (nbricks + 1)) * 2 + up(4 * nc) * 2 + up(4 * nf);      // offsets, cell/face locations
     b += up(4 * nf * np);                                              // face_runs
-    b += 4 * up(4 * nbricks * rows);                                   // row descriptors
+    b += 4 * up(4 * nrows);                                            // row descriptors
     b += up(4 * halo) + up(halo);                                      // halo DoF ids and masks
     b += up(((int64_t)1 << d) * 8 * halo);                             // halo planes (FP64)
   } else {

@@ -51,3 +51,43 @@ def test_low_degree_bricks(p, n):
                 assert ex <= 1.0, (parts, i)
     finally:
         op.close()
+
+
+def test_large_q1_mesh_takes_the_sweeps():
+    """165^3 Q1 cells, all active: above the size where degree 1 goes back to the lattice sweeps.
+    The DoFs form the whole lattice, so the cell term is the Kronecker sum of the assembled 1D
+    stiffness and mass matrices."""
+    import numpy as np
+    n = 165
+    op = sbm.Operator(3, n, 0.0, 1.0, inputs.halfspace((1.0, 0.0, 0.0), 2.0), 1)
+    try:
+        assert op.n_cells == n ** 3 and op.n_dofs == (n + 1) ** 3
+        h = 1.0 / n
+        u = inputs.uniform_vector(op.n_dofs, seed=3)
+
+        def line(x, axis, d0, off):  # assembled 1D matrix, unit cells: off-diagonal off, diagonal 2 d0 (d0 at the ends)
+            x = np.moveaxis(x, axis, 0)
+            y = 2 * d0 * x
+            y[0] -= d0 * x[0]
+            y[-1] -= d0 * x[-1]
+            y[1:] += off * x[:-1]
+            y[:-1] += off * x[1:]
+            return np.moveaxis(y, 0, axis)
+
+        U = u.reshape(n + 1, n + 1, n + 1)
+        ref = np.zeros_like(U)
+        for a in range(3):
+            t = line(U, a, 1.0, -1.0)
+            for m in range(3):
+                if m != a:
+                    t = line(t, m, 1.0 / 3.0, 1.0 / 6.0)
+            ref += h * t
+        for dtype, tol in TOL.items():
+            print(f"case q1 n={n} dtype={dtype}", flush=True)
+            ud = torch.from_numpy(u).to("cuda").to(dtype)
+            vd = torch.full_like(ud, float("nan"))
+            op.apply_parts(ud, vd, sbm.PART_CELLS)
+            torch.cuda.synchronize()
+            assert rel(vd.double().cpu().numpy(), ref.ravel()) <= tol
+    finally:
+        op.close()
