@@ -129,7 +129,7 @@ sbm_status build(int n, const sbm_handle *hs, const void *const *u, void *const 
     b->u.push_back(u[i]);
     b->v.push_back(v[i]);
     if (c->taylor_m >= 0) b->taylor.push_back(k);
-    auto key = std::make_tuple(c->disc, c->dim, c->p, (int)c->lanes);
+    auto key = std::make_tuple(c->disc, c->dim, c->p, (int)c->by_cells);
     auto it = gid.find(key);
     if (it == gid.end()) {
       it = gid.emplace(key, (int)members.size()).first;

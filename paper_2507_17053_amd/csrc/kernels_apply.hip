@@ -2,9 +2,9 @@
 //
 //   brick_kernel    CG: one workgroup per brick of BX x BY x BZ background cells.  The
 //                   brick's active cells (Alg. 1) are evaluated into an LDS copy of the
-//                   brick's DoF lattice (a brick whose cells are all active by 1D line
-//                   sweeps over the whole lattice, others cell by cell; 3D p <= 3: every
-//                   cell by p + 1 lanes), with the rows of its surrogate-boundary faces
+//                   brick's DoF lattice (on large operators a brick whose cells are all
+//                   active by 1D line sweeps over the whole lattice; small ones and 3D p = 2
+//                   and 3 cell by cell), with the rows of its surrogate-boundary faces
 //                   (Alg. 3); points strictly inside the brick are
 //                   then stored to v directly, points on the brick's boundary (shared with
 //                   neighbouring bricks) go to halo slots that halo_reduce_kernel sums.
@@ -78,9 +78,9 @@ inline int two_per_cu() {
 
 // Brick of background cells per CG workgroup, chosen per degree so that the LDS lattice
 // ((BX p + 1)(BY p + 1)(BZ p + 1) values) stays near 20 KB in FP64.
-template <int D, int P, bool LANES>
+template <int D, int P, bool CELLS>
 struct BrickDims {
-  // 3D by p + 1 lanes per cell (LANES, p <= 3): cells that fill whole wavefronts, 8x4x4, 7x6x4 and
+  // 3D by p + 1 lanes per cell (CELLS, p <= 3): cells that fill whole wavefronts, 8x4x4, 7x6x4 and
   // 8x4x2 (shapes of half and twice the size measured within 3 % of these, at p=2 8 % slower at
   // half the size on a 150^3 mesh: more brick boundary); p=1 by sweeps 8x8x8
   // 3D, p >= 4: p=4,5 4x2x2, p=6 2x2x1, p=7 2x2x2, p=8 2x2x1 (at p=4, 4x2x2 measured faster than
@@ -89,7 +89,7 @@ struct BrickDims {
   // 2D: 8x8 up to p=2, 4x4 up to p=7, 3x3 for p=8 (a lattice row must fit 32 points)
   static constexpr int S3[9][3] = {{1, 1, 1}, {8, 8, 8}, {7, 6, 4}, {8, 4, 2}, {4, 2, 2},
                                    {4, 2, 2}, {2, 2, 1}, {2, 2, 2}, {2, 2, 1}};
-  static constexpr bool SMALL = D == 3 && P == 1 && LANES;  // 8x4x4
+  static constexpr bool SMALL = D == 3 && P == 1 && CELLS;  // 8x4x4
   static constexpr int BX = (D == 2) ? (P <= 2 ? 8 : (P <= 7 ? 4 : 3)) : S3[P][0];
   static constexpr int BY = (D == 2) ? BX : (SMALL ? 4 : S3[P][1]);
   static constexpr int BZ = (D == 2) ? 1 : (SMALL ? 4 : S3[P][2]);
@@ -479,7 +479,7 @@ struct BatchItem {
 // ------------------------------------------------------------------------------------
 // CG brick kernel
 // ------------------------------------------------------------------------------------
-// Geometry of the CG brick kernel for (D, P): lattice extents, block size (enough threads
+// Geometry of the CG brick kernel by sweeps for (D, P): lattice extents, block size (enough threads
 // for the longest set of lattice lines, at most 256 so that several workgroups share a CU),
 // cells per batch on the per-cell path, and the LDS size (the larger of the two paths,
 // which share one buffer).
@@ -523,27 +523,50 @@ struct SweepBrickCfg {
   static constexpr int SMEM = NL + (TAIL_SWEEP > TAIL_CELLS ? TAIL_SWEEP : TAIL_CELLS);
 };
 
-// The brick kernel of 3D p <= 3 takes p + 1 lanes per cell (cells_body), the others the lattice
-// sweeps (sweeps_body).  The line lies where the cells' results still leave four or more wavefronts
-// per SIMD: at p=4 (FP64 160 registers, 1 KB of LDS per cell) the two forms measured alike (64^3:
-// brick kernel 39.5 against 39.1 us FP64, 25.5 against 24.3 us FP32), at p=3 the lanes are ahead
-// (96^3: 52 against 73 us FP64; 24^3: 11 against 24 us FP32).  At p=1 it also depends on the size:
-// the lanes' smaller bricks leave more DoFs on brick boundaries (51 % against 33 %), which decides
-// once the device is full several times over (FP64 / FP32 apply of 2.4 M cells 79 / - against 113
-// us, of 5.7 M 158 / 125 against 155 / 116, of 9.6 M 254 / 197 against 226 / 150): kLanesMaxCells1.
-constexpr int64_t kLanesMaxCells1 = (int64_t)1 << 22;
-template <int D, int N1>
-constexpr bool has_lanes() {
-  return D == 3 && N1 <= 4;
-}
+// Form of an operator's brick kernel: cell by cell up to kCellsMax cells, lattice sweeps
+// (sweeps_body) above.  Cell by cell means p + 1 lanes per cell in 3D at p <= 3 (cells_body), else
+// (p+1)^(d-1) threads per cell (tile_body).
+// 3D, p = 2 and 3: always; the lanes' results leave four or more wavefronts per SIMD (p=3, 96^3: 52
+// against 73 us FP64; 24^3: 11 against 24 us FP32.  At p=4 the lanes, FP64 160 registers and 1 KB of
+// LDS per cell, and the sweeps measured alike on 64^3).
+// 3D, p = 1: the lanes' smaller bricks leave more DoFs on brick boundaries (51 % against 33 %), which
+// decides once the device is full several times over (FP64 / FP32 apply of 2.4 M cells 79 / - against
+// 113 us, of 5.7 M 158 / 125 against 155 / 116, of 9.6 M 254 / 197 against 226 / 150).
+// 3D, p >= 4, and 2D: all cells at once is one short chain (one gather, one pass per axis, one
+// write-out) where the sweeps of a brick with cut cells run batch after batch; that decides as long
+// as every brick has a place on the device, and the larger LDS and workgroup against it after that.
+// Brick kernel alone, sweeps -> cells in us, balls of radius 0.75 in [-1,1]^3, FP64 and FP32:
+//   p=4  24^3 17.1 -> 10.5, 15.9 ->  9.5   40^3 21.0 -> 18.9, 16.8 -> 15.4   48^3 23.3 -> 25.2, 19.2 -> 20.9
+//   p=5  24^3 18.9 -> 12.1, 16.7 -> 10.7   32^3 22.1 -> 18.6, 17.7 -> 12.6   40^3 26.6 -> 31.0, 20.5 -> 24.4
+//   p=6  16^3 14.6 -> 11.6, 11.2 ->  9.8   24^3 16.8 -> 14.5, 12.1 -> 11.2   48^3 58.9 -> 58.4, 28.0 -> 34.3
+//   p=7  12^3 21.2 -> 13.1, 16.1 -> 11.6   20^3 18.4 -> 14.8, 15.0 -> 12.3   30^3 33.1 -> 30.8, 21.5 -> 19.2
+//   p=8  12^3 18.7 -> 13.6, 13.8 -> 12.1   20^3 21.0 -> 17.1, 15.5 -> 14.4   36^3 74.1 -> 64.0, 31.6 -> 40.8
+// (the balls hold about 0.22 n^3 cells); 2D, FP64 and FP32:
+//   p=2  16^2 10.8 ->  9.9, 10.4 ->  9.2   p=6 300^2 16.3 -> 15.3, 13.0 -> 12.0   p=8 200^2 19.2 -> 16.1, 12.9 -> 11.7
+//   p=4 512^2 17.7 -> 18.3, 13.8 -> 15.9   p=5 400^2 17.2 -> 18.1, 13.0 -> 15.0   p=8 600^2 91 -> 106, 48 -> 62
+constexpr int64_t kAll = INT64_MAX;
+constexpr int64_t kCellsMax[2][9] = {{0, 16384, 16384, 16384, 16384, 16384, 16384, 16384, 16384},
+                                     {0, (int64_t)1 << 22, kAll, kAll, 16384, 8192, 4096, 8192, 4096}};
 template <int D, int N1>
 constexpr bool has_sweeps() {
-  return !has_lanes<D, N1>() || N1 == 2;
+  return kCellsMax[D - 2][N1 - 1] != kAll;
 }
+
+// Bricks by cell places, (p+1)^(d-1) threads each
+template <typename T, int D, int N1>
+struct TileBrickCfg {
+  static constexpr int DIM = D, P = N1 - 1, NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB;
+  static constexpr int BX = BrickDims<D, P, false>::BX, BY = BrickDims<D, P, false>::BY,
+                       BZ = BrickDims<D, P, false>::BZ;
+  static constexpr int LX = BX * P + 1, LY = BY * P + 1, LZ = (D == 3) ? BZ * P + 1 : 1, NROWS = LY * LZ;
+  static constexpr int MAXC = BX * BY * BZ;
+  static constexpr int NW = (MAXC * NP + 63) / 64, NT = 64 * NW;
+  static constexpr int TILE = NB;
+};
 
 template <typename T, int N1>
 struct CellBrickCfg {
-  static constexpr int D = 3, P = N1 - 1, NP = N1 * N1, NB = NP * N1;
+  static constexpr int DIM = 3, D = 3, P = N1 - 1, NP = N1 * N1, NB = NP * N1;
   static constexpr int BX = BrickDims<D, P, true>::BX, BY = BrickDims<D, P, true>::BY,
                        BZ = BrickDims<D, P, true>::BZ;
   static constexpr int LX = BX * P + 1, LY = BY * P + 1, LZ = BZ * P + 1, NROWS = LY * LZ;
@@ -557,8 +580,10 @@ struct CellBrickCfg {
   static constexpr int TILE = (NB > 4 * SC ? NB : 4 * SC) | (N1 == 4 ? 0 : 1);
 };
 
-template <typename T, int D, int N1, bool LANES>
-struct BrickCfg : std::conditional_t<LANES, CellBrickCfg<T, N1>, SweepBrickCfg<T, D, N1>> {};
+template <typename T, int D, int N1, bool CELLS>
+struct BrickCfg
+    : std::conditional_t<!CELLS, SweepBrickCfg<T, D, N1>,
+                         std::conditional_t<D == 3 && N1 <= 4, CellBrickCfg<T, N1>, TileBrickCfg<T, D, N1>>> {};
 
 // Lattice-line segments of a full brick.  A line of B cells has B p + 1 nodes; the segment of
 // cell j is nodes j p .. j p + p, and neighbouring segments share one node.  One lane per
@@ -953,24 +978,177 @@ __device__ __forceinline__ void settle(T &x) {
   asm volatile("" : "+v"(x));
 }
 
+// Rows of a brick's lattice in LDS, sorted by kind (y and z inside a cell, z inside and y on a plane
+// between cells, y inside and z on such a plane, both on planes; in 2D there is the one plane z = 0).
+template <typename T, class C>
+struct BrickRows {
+  static constexpr int P = C::P, YI = C::BY * (P - 1), ZI = C::DIM == 3 ? C::BZ * (P - 1) : 0, YB = C::BY + 1,
+                       ZB = C::DIM == 3 ? C::BZ + 1 : 1;
+  static constexpr int K1 = YI * ZI, K2 = K1 + YB * ZI, K3 = K2 + YI * ZB;  // first row of each kind but the first
+  static_assert(K3 + YB * ZB == C::NROWS, "every row once");
+  static_assert(C::NROWS <= C::NT, "one row per thread");
+  static_assert(C::LX <= 32, "row masks hold 32 points");
+  enum { kLowY = 1, kHighY = 2, kLowZ = 4, kHighZ = 8, kY0 = 16, kZ0 = 32, kEdge = 64 };
+  T *dst[C::NROWS];           // where the points 0 < x < LX-1 go, by their place among the row's DoFs
+  int32_t hbase[C::NROWS];    // halo index
+  int32_t off[C::NROWS];      // 256 x (place of the row in the results) + flags
+  uint32_t gmask[C::NROWS], bmask[C::NROWS];
+  int32_t base[C::NROWS];     // by the row's own place y + LY z: id of its first DoF,
+  uint32_t first[C::NROWS];   // mask of its DoFs
+
+  // One row per thread (full: all masks are ones).  A barrier has to follow.
+  __device__ __forceinline__ void fill(const BrickArgs &br, int brick, bool full, T *v, T *halo, int nhalo) {
+    constexpr int BX = C::BX, BY = C::BY, BZ = C::BZ, LX = C::LX, LY = C::LY, LZ = C::LZ, PI = P > 1 ? P - 1 : 1;
+    const int r = threadIdx.x;
+    if (r >= C::NROWS) return;
+    const bool yb = (r >= K1 && r < K2) || r >= K3, zb = r >= K2;
+    const int rq = r - (r >= K3 ? K3 : (r >= K2 ? K2 : (r >= K1 ? K1 : 0)));
+    const int ny = yb ? YB : (YI > 0 ? YI : 1), iy = rq % ny, iz = rq / ny;
+    const int cy = yb ? iy : iy / PI, cz = zb ? iz : iz / PI;
+    const int ly = yb ? 0 : 1 + iy - cy * PI, lz = zb ? 0 : 1 + iz - cz * PI;
+    const int y = cy * P + ly, z = cz * P + lz, own = y + LY * z;
+    const int64_t at = (int64_t)brick * C::NROWS + own;
+    const int32_t b = br.row_base[at], hb = br.row_hbase[at];
+    const uint32_t gm = full ? ~0u : br.row_gmask[at], bm = full ? ~0u : br.row_bmask[at];
+    const bool edge = y == 0 || y == LY - 1 || (C::DIM == 3 && (z == 0 || z == LZ - 1));
+    const int plane = (y == 0 ? 2 : 0) | (C::DIM == 3 && z == 0 ? 4 : 0);
+    base[own] = b;
+    first[own] = gm;
+    dst[r] = edge ? halo + (int64_t)plane * nhalo + hb : v + b;
+    hbase[r] = hb;
+    off[r] = (((cz * BY + cy) * BX * C::TILE + (lz * (P + 1) + ly) * (P + 1)) << 8) |
+             (yb && cy > 0 ? kLowY : 0) | (cy < BY ? kHighY : 0) | (zb && cz > 0 ? kLowZ : 0) |
+             (cz < BZ ? kHighZ : 0) | (y == 0 ? kY0 : 0) | (C::DIM == 3 && z == 0 ? kZ0 : 0) | (edge ? kEdge : 0);
+    gmask[r] = gm;
+    bmask[r] = bm;
+  }
+  // First DoF of the x-run (j, k) of the cell at (cx, cy, cz).
+  __device__ __forceinline__ int32_t run(int cx, int cy, int cz, int j, int k) const {
+    const int own = cy * P + j + C::LY * (cz * P + k);
+    return base[own] + __popc(first[own] & ((1u << (cx * P)) - 1u));
+  }
+  // Halo plane and index of a row's end (side 0: x = 0, 1: x = LX-1), as an offset.  The row's
+  // brick-boundary DoFs follow each other: all of it on the brick's y or z sides, else the two ends.
+  __device__ __forceinline__ int64_t end_at(int r, int side, int nhalo) const {
+    const int o = off[r], x = side ? C::LX - 1 : 0;
+    const uint32_t gm = gmask[r], hgm = (o & kEdge) ? gm : (gm & (1u | (1u << (C::LX - 1))));
+    const int plane = (side ? 0 : 1) | ((o & kY0) ? 2 : 0) | ((o & kZ0) ? 4 : 0);
+    return (int64_t)plane * nhalo + hbase[r] + __popc(hgm & ((1u << x) - 1u));
+  }
+};
+
+// (a pointer read from LDS is generic otherwise, and its stores wait on LDS too)
+template <typename T>
+using GlobalT = __attribute__((address_space(1))) T;
+
+// Assembly and write-out of a brick's cells, one tile of results [z][y][x] per cell place (zero
+// where there is no cell): every lattice point sums its cells' values (z, then y, then x from the
+// low side: a fixed order) and is stored once.
+template <typename T, class C>
+__device__ __forceinline__ void brick_assemble(const T *tiles, const BrickRows<T, C> &R, T *__restrict__ halo,
+                                               int nhalo) {
+  using Rows = BrickRows<T, C>;
+  constexpr int P = C::P, N1 = P + 1, TS = C::TILE, BX = C::BX, BY = C::BY, LX = C::LX, NROWS = C::NROWS;
+  constexpr int STEP_Y = BX * TS - P * N1, STEP_Z = BY * BX * TS - P * N1 * N1;  // to the cell before
+  constexpr int DZ = C::DIM == 3 ? 1 : 0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the rows' ends, all of them brick-boundary points
+  constexpr int NE = (2 * NROWS + C::NT - 1) / C::NT;
+#pragma unroll
+  for (int m = 0; m < NE; ++m) {
+    const int i = tid + m * C::NT, r = i < 2 * NROWS ? i >> 1 : 0, side = i & 1, o = R.off[r];
+    const int off = (o >> 8) + (side ? (BX - 1) * TS + P : 0);
+    const uint32_t bm = i < 2 * NROWS ? R.bmask[r] : 0u;
+    T sum = T(0);
+#pragma unroll
+    for (int dz = DZ; dz >= 0; --dz)
+#pragma unroll
+      for (int dy = 1; dy >= 0; --dy) {
+        const bool in = (o & (dy ? Rows::kLowY : Rows::kHighY)) && (o & (dz ? Rows::kLowZ : Rows::kHighZ));
+        const T val = tiles[in ? off - dz * STEP_Z - dy * STEP_Y : 0];
+        sum += in ? val : T(0);
+      }
+    if ((bm >> (side ? LX - 1 : 0)) & 1u) halo[R.end_at(r, side, nhalo)] = sum;
+  }
+  // the points 0 < x < LX-1: lanes take whole rows, so that a lane's x is fixed, and the rows of one
+  // kind sum equally many cells.  Up to four rows per lane at a time, every LDS read before the first
+  // store: one by one the rows spent their time on the latency of three dependent LDS reads.
+  constexpr int W = LX - 2, RPW = 64 / W, STEP = C::NW * RPW;
+  static_assert(RPW >= 1, "a wavefront holds at least one row");
+  const int rl = lane / W, x = 1 + lane - rl * W, cx = x / P;
+  const uint32_t below = (1u << x) - 1u;
+  const int xa = cx * TS + (x - cx * P), xb = (cx - 1) * TS + P;
+  const bool two = x == cx * P;  // a point between two cells
+  auto rows = [&](auto r0_, auto r1_, auto yb_, auto zb_) {
+    constexpr int R0 = decltype(r0_)::value, R1 = decltype(r1_)::value;
+    constexpr bool YB_ = decltype(yb_)::value, ZB_ = decltype(zb_)::value && DZ == 1;
+    constexpr int NPASS = (R1 - R0 + STEP - 1) / STEP, CH = NPASS < 4 ? NPASS : 4;
+    if constexpr (NPASS > 0) {
+#pragma unroll
+      for (int k0 = 0; k0 < NPASS; k0 += CH) {
+        int o[CH];
+        T *dst[CH];
+        uint32_t gm[CH], bm[CH];
+        T sum[CH];
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+          const int r = R0 + wave * RPW + rl + (k0 + k) * STEP, rc = r < R1 ? r : R1 - 1;
+          o[k] = R.off[rc];
+          dst[k] = R.dst[rc];
+          gm[k] = R.gmask[rc];
+          bm[k] = r < R1 ? R.bmask[rc] : 0u;
+          sum[k] = T(0);
+        }
+#pragma unroll
+        for (int dz = ZB_ ? 1 : 0; dz >= 0; --dz)
+#pragma unroll
+          for (int dy = YB_ ? 1 : 0; dy >= 0; --dy) {
+            const int need = (YB_ ? (dy ? Rows::kLowY : Rows::kHighY) : 0) | (ZB_ ? (dz ? Rows::kLowZ : Rows::kHighZ) : 0);
+            T lo[CH], hi[CH];
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+              const bool in = (o[k] & need) == need;
+              const int off = in ? (o[k] >> 8) - dz * STEP_Z - dy * STEP_Y : 0;
+              lo[k] = tiles[in && two ? off + xb : 0];
+              hi[k] = tiles[off + xa];
+            }
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+              settle(lo[k]);
+              settle(hi[k]);
+              const bool in = (o[k] & need) == need;
+              lo[k] = in && two ? lo[k] : T(0);
+              hi[k] = in ? hi[k] : T(0);
+            }
+#pragma unroll
+            for (int k = 0; k < CH; ++k) sum[k] += lo[k] + hi[k];
+          }
+#pragma unroll
+        for (int k = 0; k < CH; ++k) settle(sum[k]);
+#pragma unroll
+        for (int k = 0; k < CH; ++k)
+          if ((bm[k] >> x) & 1u) ((GlobalT<T> *)dst[k])[__popc(gm[k] & below)] = sum[k];
+      }
+    }
+  };
+  if (rl < RPW) {
+    using std::integral_constant;
+    rows(integral_constant<int, 0>{}, integral_constant<int, Rows::K1>{}, std::false_type{}, std::false_type{});
+    rows(integral_constant<int, Rows::K1>{}, integral_constant<int, Rows::K2>{}, std::true_type{}, std::false_type{});
+    rows(integral_constant<int, Rows::K2>{}, integral_constant<int, Rows::K3>{}, std::false_type{}, std::true_type{});
+    rows(integral_constant<int, Rows::K3>{}, integral_constant<int, NROWS>{}, std::true_type{}, std::true_type{});
+  }
+}
+
 template <typename T, int N1>
 __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const T *__restrict__ fbuf,
                                            const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
                                            int nhalo, KTab<T, N1> tab, T scale, int parts) {
   using C = CellBrickCfg<T, N1>;
   constexpr int P = N1 - 1, NP = C::NP, HC = (N1 + 1) / 2, HF = N1 / 2, TS = C::TILE;
-  constexpr int BX = C::BX, BY = C::BY, BZ = C::BZ, LX = C::LX, LY = C::LY, LZ = C::LZ, NROWS = C::NROWS;
-  static_assert(LX <= 32, "row masks hold 32 points");
+  constexpr int BX = C::BX, BY = C::BY, LX = C::LX, LY = C::LY;
   __shared__ T tiles[C::NW * C::CPW * TS];
-  // rows of the lattice, sorted by kind: where the points 0 < x < LX-1 go, halo index, masks, and
-  // 256 x (place of the row in the cells' results) + flags
-  using GlobalT = __attribute__((address_space(1))) T;  // (a pointer read from LDS is generic otherwise)
-  __shared__ T *s_dst[NROWS];
-  __shared__ int32_t s_hbase[NROWS], s_off[NROWS];
-  __shared__ uint32_t s_gmask[NROWS], s_bmask[NROWS];
-  __shared__ int32_t s_base[NROWS];   // by the row's place: id of its first DoF,
-  __shared__ uint32_t s_first[NROWS]; // mask of its DoFs
-  constexpr int kLowY = 1, kHighY = 2, kLowZ = 4, kHighZ = 8, kY0 = 16, kZ0 = 32, kEdge = 64;
+  __shared__ BrickRows<T, C> rows;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c0 = br.cell_off[brick], nc = br.cell_off[brick + 1] - c0, f0 = br.face_off[brick];
   const bool full = nc == C::MAXC;
@@ -978,36 +1156,13 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
   const bool on = wc < C::CPW && c < nc;
   const int loc = on ? br.cell_loc[c0 + c] : 0;
   const int cface = on ? br.cell_face[c0 + c] : 0;
-  // row kinds, in the order of the tables: y and z inside a cell, z inside and y on a plane between
-  // cells, y inside and z on such a plane, both on planes
-  constexpr int YI = BY * (P - 1), ZI = BZ * (P - 1), YB = BY + 1, ZB = BZ + 1;
-  constexpr int K1 = YI * ZI, K2 = K1 + YB * ZI, K3 = K2 + YI * ZB;
-  static_assert(K3 + YB * ZB == NROWS, "every row once");
-  static_assert(NROWS <= C::NT, "one row per thread");
-  const int r = tid < NROWS ? tid : 0;
-  const bool yb = (r >= K1 && r < K2) || r >= K3, zb = r >= K2;
-  const int rq = r - (r >= K3 ? K3 : (r >= K2 ? K2 : (r >= K1 ? K1 : 0)));
-  const int ny = yb ? YB : (YI > 0 ? YI : 1), riy = rq % ny, riz = rq / ny;
-  constexpr int PI = P > 1 ? P - 1 : 1;
-  const int rcy = yb ? riy : riy / PI, rcz = zb ? riz : riz / PI;
-  const int rly = yb ? 0 : 1 + riy - rcy * PI, rlz = zb ? 0 : 1 + riz - rcz * PI;
-  const int ry = rcy * P + rly, rz = rcz * P + rlz;
-  const int64_t rat = (int64_t)brick * NROWS + ry + LY * rz;
-  const int32_t rbase = br.row_base[rat], rhb = br.row_hbase[rat];
-  const uint32_t rgm = full ? ~0u : br.row_gmask[rat], rbm = full ? ~0u : br.row_bmask[rat];
-  if (tid < NROWS) {
-    s_base[ry + LY * rz] = rbase;
-    s_first[ry + LY * rz] = rgm;
-  }
+  rows.fill(br, brick, full, v, halo, nhalo);
   __syncthreads();
   // the cell's place in the brick, and the lane's x-runs (j, k): the first DoF of each from its row
   const int lcx = (loc % LX) / P, lcy = (loc / LX % LY) / P, lcz = loc / (LX * LY) / P;
   int32_t run[N1];
 #pragma unroll
-  for (int k = 0; k < N1; ++k) {
-    const int row = lcy * P + (on ? j : 0) + LY * (lcz * P + k);
-    run[k] = s_base[row] + __popc(s_first[row] & ((1u << (lcx * P)) - 1u));
-  }
+  for (int k = 0; k < N1; ++k) run[k] = rows.run(lcx, lcy, lcz, on ? j : 0, k);
   T lo[N1], hi[N1];  // x-runs of planes k and p - k
   auto fetch = [&](int k) {
 #pragma unroll
@@ -1017,17 +1172,6 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
     }
   };
   if (on && (parts & SBM_PART_CELLS)) fetch(0);
-  if (tid < NROWS) {
-    const bool edge = ry == 0 || ry == LY - 1 || rz == 0 || rz == LZ - 1;
-    const int plane = (ry == 0 ? 2 : 0) | (rz == 0 ? 4 : 0);
-    s_dst[r] = edge ? halo + (int64_t)plane * nhalo + rhb : v + rbase;
-    s_hbase[r] = rhb;
-    s_off[r] = (((rcz * BY + rcy) * BX * TS + (rlz * N1 + rly) * N1) << 8) | (yb && rcy > 0 ? kLowY : 0) |
-               (rcy < BY ? kHighY : 0) | (zb && rcz > 0 ? kLowZ : 0) | (rcz < BZ ? kHighZ : 0) | (ry == 0 ? kY0 : 0) |
-               (rz == 0 ? kZ0 : 0) | (edge ? kEdge : 0);
-    s_gmask[r] = rgm;
-    s_bmask[r] = rbm;
-  }
   T out[N1][N1];  // [z][y] at x = j
 #pragma unroll
   for (int z = 0; z < N1; ++z)
@@ -1165,123 +1309,102 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
       for (int y = 0; y < N1; ++y) tile[(z * N1 + y) * N1 + j] = out[z][y];
   }
   __syncthreads();
-  // Assembly and write-out: every lattice point sums its cells' values (z, then y, then x from the
-  // low side: a fixed order) and is stored once.
-  // the rows' ends, all of them brick-boundary points
-  constexpr int NE = (2 * NROWS + C::NT - 1) / C::NT;
-#pragma unroll
-  for (int m = 0; m < NE; ++m) {
-    const int i = tid + m * C::NT, er = i < 2 * NROWS ? i >> 1 : 0, side = i & 1, o = s_off[er];
-    const int off = (o >> 8) + (side ? (BX - 1) * TS + P : 0);
-    const uint32_t gm = s_gmask[er], bm = i < 2 * NROWS ? s_bmask[er] : 0u;
-    const int32_t hb = s_hbase[er];
-    T sum = T(0);
-#pragma unroll
-    for (int dz = 1; dz >= 0; --dz)
-#pragma unroll
-      for (int dy = 1; dy >= 0; --dy) {
-        const bool in = (o & (dy ? kLowY : kHighY)) && (o & (dz ? kLowZ : kHighZ));
-        const T val = tiles[in ? off - dz * (BY * BX * TS - P * NP) - dy * (BX * TS - P * N1) : 0];
-        sum += in ? val : T(0);
-      }
-    const int x = side ? LX - 1 : 0;
-    // (the row's brick-boundary DoFs follow each other: all of it on the brick's y or z sides,
-    // else the two ends)
-    const uint32_t hgm = (o & kEdge) ? gm : (gm & (1u | (1u << (LX - 1))));
-    const int plane = (side ? 0 : 1) | ((o & kY0) ? 2 : 0) | ((o & kZ0) ? 4 : 0);
-    if ((bm >> x) & 1u) halo[(int64_t)plane * nhalo + hb + __popc(hgm & ((1u << x) - 1u))] = sum;
-  }
-  // the points 0 < x < LX-1: lanes take whole rows, so that a lane's x is fixed, and the rows of one
-  // kind sum equally many cells
-  {
-    constexpr int W = LX - 2, RPW = 64 / W, STEP = C::NW * RPW;
-    static_assert(RPW >= 1, "a wavefront holds at least one row");
-    const int rl = lane / W, x = 1 + lane - rl * W, cx = x / P;
-    const uint32_t below = (1u << x) - 1u;
-    const int xa = cx * TS + (x - cx * P), xb = (cx - 1) * TS + P;
-    const bool two = x == cx * P;  // a point between two cells
-    // (up to four rows per lane at a time, every LDS read before the first store: the row loop one
-    // by one spent its time on the latency of three dependent LDS reads)
-    auto rows = [&](auto r0_, auto r1_, auto yb_, auto zb_) {
-      constexpr int R0 = decltype(r0_)::value, R1 = decltype(r1_)::value;
-      constexpr bool YB_ = decltype(yb_)::value, ZB_ = decltype(zb_)::value;
-      constexpr int NPASS = (R1 - R0 + STEP - 1) / STEP, CH = NPASS < 4 ? NPASS : 4;
-      if constexpr (NPASS > 0) {
-#pragma unroll
-        for (int k0 = 0; k0 < NPASS; k0 += CH) {
-          int o[CH];
-          T *dst[CH];
-          uint32_t gm[CH], bm[CH];
-          T sum[CH];
-#pragma unroll
-          for (int k = 0; k < CH; ++k) {
-            const int r = R0 + wave * RPW + rl + (k0 + k) * STEP;
-            const int rc = r < R1 ? r : R1 - 1;
-            o[k] = s_off[rc];
-            dst[k] = s_dst[rc];
-            gm[k] = s_gmask[rc];
-            bm[k] = r < R1 ? s_bmask[rc] : 0u;
-            sum[k] = T(0);
-          }
-#pragma unroll
-          for (int dz = ZB_ ? 1 : 0; dz >= 0; --dz)
-#pragma unroll
-            for (int dy = YB_ ? 1 : 0; dy >= 0; --dy) {
-              constexpr int kNone = 0;
-              const int need = (YB_ ? (dy ? kLowY : kHighY) : kNone) | (ZB_ ? (dz ? kLowZ : kHighZ) : kNone);
-              const int back = dz * (BY * BX * TS - P * NP) + dy * (BX * TS - P * N1);
-              T lo[CH], hi[CH];
-#pragma unroll
-              for (int k = 0; k < CH; ++k) {
-                const bool in = (o[k] & need) == need;
-                const int off = in ? (o[k] >> 8) - back : 0;
-                lo[k] = tiles[in && two ? off + xb : 0];
-                hi[k] = tiles[off + xa];
-              }
-#pragma unroll
-              for (int k = 0; k < CH; ++k) {
-                settle(lo[k]);
-                settle(hi[k]);
-                const bool in = (o[k] & need) == need;
-                lo[k] = in && two ? lo[k] : T(0);
-                hi[k] = in ? hi[k] : T(0);
-              }
-#pragma unroll
-              for (int k = 0; k < CH; ++k) sum[k] += lo[k] + hi[k];
-            }
-#pragma unroll
-          for (int k = 0; k < CH; ++k) settle(sum[k]);
-#pragma unroll
-          for (int k = 0; k < CH; ++k)
-            if ((bm[k] >> x) & 1u) ((GlobalT *)dst[k])[__popc(gm[k] & below)] = sum[k];
-        }
-      }
-    };
-    if (rl < RPW) {
-      using std::integral_constant;
-      rows(integral_constant<int, 0>{}, integral_constant<int, K1>{}, std::false_type{}, std::false_type{});
-      rows(integral_constant<int, K1>{}, integral_constant<int, K2>{}, std::true_type{}, std::false_type{});
-      rows(integral_constant<int, K2>{}, integral_constant<int, K3>{}, std::false_type{}, std::true_type{});
-      rows(integral_constant<int, K3>{}, integral_constant<int, NROWS>{}, std::true_type{}, std::true_type{});
-    }
-  }
+  brick_assemble<T, C>(tiles, rows, halo, nhalo);
 }
 
-template <typename T, int D, int N1, bool LANES>
+// ------------------------------------------------------------------------------------
+// Small operators of 3D p >= 4 and of 2D: all of a brick's cell places at once, (p+1)^(d-1) threads
+// each, two tiles of LDS per place; every lattice point then sums its cells' values as it is stored.
+// What bounds it: the latency of its phases (row tables, gather, one pass per axis, write-out), so it
+// takes the operators whose bricks are on the device all at once (kCellsMax; 24^3 Q4 apply FP64 26.9
+// -> 20.5 us, FP32 24.6 -> 18.4 us, 2D disk of 349 unknowns 16.4 -> 14.5 us).
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int N1>
+__device__ __forceinline__ void tile_body(const int brick, BrickArgs br, const T *__restrict__ fbuf,
+                                          const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
+                                          int nhalo, KTab<T, N1> tab, T scale, int parts) {
+  using C = TileBrickCfg<T, D, N1>;
+  constexpr int P = N1 - 1, NP = C::NP, NB = C::NB, BX = C::BX, BY = C::BY, BZ = C::BZ;
+  constexpr int LX = C::LX, LY = C::LY;
+  __shared__ T smem[C::MAXC * (C::TILE + NB)];
+  __shared__ BrickRows<T, C> rows;
+  __shared__ int32_t s_info[C::MAXC];  // per place: 0 without a cell, else 1 + 2 x its faces (cell_face)
+  const int tid = threadIdx.x;
+  const int c0 = br.cell_off[brick], nc = br.cell_off[brick + 1] - c0, f0 = br.face_off[brick];
+  const int loc = tid < nc ? br.cell_loc[c0 + tid] : 0, info_ = tid < nc ? 2 * br.cell_face[c0 + tid] + 1 : 0;
+  if (tid < C::MAXC) s_info[tid] = 0;
+  rows.fill(br, brick, nc == C::MAXC, v, halo, nhalo);
+  __syncthreads();
+  if (tid < nc) s_info[(loc / (LX * LY) / P * BY + (loc / LX % LY) / P) * BX + (loc % LX) / P] = info_;
+  __syncthreads();
+  const int le = tid / NP, t = tid - le * NP;
+  const bool place = le < C::MAXC;
+  const int info = place ? s_info[le] : 0;
+  const int cx = le % BX, cy = le / BX % BY, cz = le / (BX * BY);
+  const int t0 = (D == 3) ? t % N1 : t, t1 = (D == 3) ? t / N1 : 0;
+  const bool work = info != 0 && (parts & SBM_PART_CELLS) != 0;
+  T x[N1], out[N1];
+#pragma unroll
+  for (int k = 0; k < N1; ++k) {  // the pencil along the last axis
+    x[k] = work ? u[(int64_t)rows.run(cx, cy, cz, (D == 3) ? t1 : k, (D == 3) ? k : 0) + t0] : T(0);
+    out[k] = T(0);
+  }
+  // the rows of the cell's surrogate faces for x-run t, in code order, from their (Rv, Rg) per face
+  // node, loaded while the pencil is under way
+  T frow[N1];
+#pragma unroll
+  for (int i = 0; i < N1; ++i) frow[i] = T(0);
+  if ((parts & SBM_PART_SBM_FACES) && (info >> 1)) {
+    const int cf = info >> 1;
+    const T *Rq = fbuf + (int64_t)(f0 + (cf >> 6)) * 2 * NP;
+#pragma unroll
+    for (int code = 0; code < 2 * D; ++code) {
+      if (!((cf >> code) & 1)) continue;
+      const int a = code >> 1, s = code & 1;
+      const T *Rv = Rq, *Rg = Rq + NP;
+      Rq += 2 * NP;
+      if (a == 0) {
+        const T rv = Rv[t], rg = Rg[t];
+#pragma unroll
+        for (int i = 0; i < N1; ++i) frow[i] += (i == s * P ? rv : T(0)) + (s ? tab.D1[i] : tab.D0[i]) * rg;
+      } else {
+        const int ia = a == 1 ? t0 : t1, n0 = (D == 3) ? N1 * (a == 1 ? t1 : t0) : 0;
+        T da = T(0);
+#pragma unroll
+        for (int i = 0; i < N1; ++i) da = i == ia ? (s ? tab.D1[i] : tab.D0[i]) : da;
+        const bool on = ia == s * P;
+#pragma unroll
+        for (int i = 0; i < N1; ++i) frow[i] += (on ? Rv[n0 + i] : T(0)) + da * Rg[n0 + i];
+      }
+    }
+  }
+  T *const A = smem + (place ? le : 0) * C::TILE, *const B = smem + C::MAXC * C::TILE + (place ? le : 0) * NB;
+  kron_cell<T, D, N1>(tab, t, x, A, B, scale, out, work, work);
+  if (place) {  // (the thread's own x-run of the tile, which it alone has read)
+#pragma unroll
+    for (int i = 0; i < N1; ++i) A[N1 * t + i] = out[i] + frow[i];
+  }
+  __syncthreads();
+  brick_assemble<T, C>(smem, rows, halo, nhalo);
+}
+
+template <typename T, int D, int N1, bool CELLS>
 __device__ __forceinline__ void brick_body(const int blk, BrickArgs br, const T *__restrict__ fbuf,
                                            const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
                                            int nhalo, KTab<T, N1> tab, T scale, int parts) {
-  if constexpr (LANES)
+  if constexpr (!CELLS)
+    sweeps_body<T, D, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
+  else if constexpr (D == 3 && N1 <= 4)
     cells_body<T, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
   else
-    sweeps_body<T, D, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
+    tile_body<T, D, N1>(blk, br, fbuf, u, v, halo, nhalo, tab, scale, parts);
 }
 
-template <typename T, int D, int N1, bool LANES>
-__global__ __launch_bounds__((BrickCfg<T, D, N1, LANES>::NT)) void brick_kernel(
+template <typename T, int D, int N1, bool CELLS>
+__global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_kernel(
     BrickArgs br, const T *__restrict__ fbuf, const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
     int nhalo, KTab<T, N1> tab, T scale, int parts) {
-  brick_body<T, D, N1, LANES>(xcd_block(), br, fbuf, u, v, halo, nhalo, tab, scale, parts);
+  brick_body<T, D, N1, CELLS>(xcd_block(), br, fbuf, u, v, halo, nhalo, tab, scale, parts);
 }
 
 // v[dof] = sum over the planes k present in the DoF's mask, in increasing k (deterministic).
@@ -1891,16 +2014,15 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
                            c->d_face_code, c->d_face_runs, c->d_face_xi, u, fbuf, tab, sc);
       }
       const int nh = (int)c->n_halo_dofs;
-      auto bricks = [&](auto lanes) {
-        constexpr bool LANES = decltype(lanes)::value;
-        hipLaunchKernelGGL((brick_kernel<T, D, N1, LANES>), dim3((unsigned)c->n_bricks),
-                           dim3(BrickCfg<T, D, N1, LANES>::NT), 0, s, br, (const T *)fbuf, u, v, halo, nh, tab, scale,
+      auto bricks = [&](auto by_cells) {
+        constexpr bool CELLS = decltype(by_cells)::value;
+        hipLaunchKernelGGL((brick_kernel<T, D, N1, CELLS>), dim3((unsigned)c->n_bricks),
+                           dim3(BrickCfg<T, D, N1, CELLS>::NT), 0, s, br, (const T *)fbuf, u, v, halo, nh, tab, scale,
                            parts);
       };
-      if constexpr (has_lanes<D, N1>())
-        if (c->lanes) bricks(std::true_type{});
+      if (c->by_cells) bricks(std::true_type{});
       if constexpr (has_sweeps<D, N1>())
-        if (!c->lanes) bricks(std::false_type{});
+        if (!c->by_cells) bricks(std::false_type{});
       if (nh > 0 && !(parts & SBM_PART_NO_ASSEMBLY)) {
         constexpr int HB = kHaloPerThread * 256;  // DoFs per block
         hipLaunchKernelGGL((halo_reduce_kernel<T, D>), dim3((nh + HB - 1) / HB), dim3(256), 0, s, nh, c->d_halo_dof,
@@ -1968,13 +2090,13 @@ struct BatchShape {
   static constexpr int TC = EC * NP;
 };
 
-template <typename T, int D, int N1, bool LANES>
-__global__ __launch_bounds__((BrickCfg<T, D, N1, LANES>::NT)) void brick_batch_kernel(const BatchItem *__restrict__ items,
+template <typename T, int D, int N1, bool CELLS>
+__global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_batch_kernel(const BatchItem *__restrict__ items,
                                                                               const int32_t *__restrict__ blk_item,
                                                                               KTab<T, N1> tab) {
   const int g = xcd_block();
   const BatchItem *it = items + blk_item[g];
-  brick_body<T, D, N1, LANES>(g - it->blk0[1], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v, (T *)it->halo,
+  brick_body<T, D, N1, CELLS>(g - it->blk0[1], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v, (T *)it->halo,
                        it->nh, tab, T(D == 3 ? it->sc.h : 1.0), SBM_PART_ALL);
 }
 
@@ -2052,16 +2174,15 @@ hipError_t batch_launch_impl(const BatchGroup &g, const unsigned char *base, hip
     if (g.nblk[0] > 0)
       hipLaunchKernelGGL((sbm_face_cg_batch_kernel<T, D, N1, S::EF>), dim3(g.nblk[0]), dim3(S::EF * S::NP), 0, s,
                          items, bi[0], tab);
-    auto bricks = [&](auto lanes) {
-      constexpr bool LANES = decltype(lanes)::value;
+    auto bricks = [&](auto by_cells) {
+      constexpr bool CELLS = decltype(by_cells)::value;
       if (g.nblk[1] > 0)
-        hipLaunchKernelGGL((brick_batch_kernel<T, D, N1, LANES>), dim3(g.nblk[1]), dim3(BrickCfg<T, D, N1, LANES>::NT),
+        hipLaunchKernelGGL((brick_batch_kernel<T, D, N1, CELLS>), dim3(g.nblk[1]), dim3(BrickCfg<T, D, N1, CELLS>::NT),
                            0, s, items, bi[1], tab);
     };
-    if constexpr (has_lanes<D, N1>())
-      if (g.first->lanes) bricks(std::true_type{});
+    if (g.first->by_cells) bricks(std::true_type{});
     if constexpr (has_sweeps<D, N1>())
-      if (!g.first->lanes) bricks(std::false_type{});
+      if (!g.first->by_cells) bricks(std::false_type{});
     if (g.nblk[2] > 0)
       hipLaunchKernelGGL((halo_reduce_batch_kernel<T, D>), dim3(g.nblk[2]), dim3(256), 0, s, items, bi[2]);
   } else {
@@ -2246,22 +2367,20 @@ hipError_t apply_dim(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t 
 
 }  // namespace
 
-bool brick_lanes(int dim, int p, int64_t n_cells) {
-  return dim == 3 && p <= 3 && (p > 1 || n_cells <= kLanesMaxCells1);
-}
+bool brick_by_cells(int dim, int p, int64_t n_cells) { return n_cells <= kCellsMax[dim - 2][p]; }
 
-void brick_dims(int dim, int p, bool lanes, int *bx, int *by, int *bz) {
-#define SBM_BD(D_, P_, L_)                 \
-  if (dim == D_ && p == P_ && lanes == L_) { \
-    *bx = BrickDims<D_, P_, L_>::BX;       \
-    *by = BrickDims<D_, P_, L_>::BY;       \
-    *bz = BrickDims<D_, P_, L_>::BZ;       \
-    return;                                \
+void brick_dims(int dim, int p, bool by_cells, int *bx, int *by, int *bz) {
+#define SBM_BD(D_, P_, C_)                     \
+  if (dim == D_ && p == P_ && by_cells == C_) { \
+    *bx = BrickDims<D_, P_, C_>::BX;           \
+    *by = BrickDims<D_, P_, C_>::BY;           \
+    *bz = BrickDims<D_, P_, C_>::BZ;           \
+    return;                                    \
   }
-  SBM_BD(2, 1, false) SBM_BD(2, 2, false) SBM_BD(2, 3, false) SBM_BD(2, 4, false)
-  SBM_BD(2, 5, false) SBM_BD(2, 6, false) SBM_BD(2, 7, false) SBM_BD(2, 8, false)
-  SBM_BD(3, 1, true) SBM_BD(3, 2, true) SBM_BD(3, 3, true) SBM_BD(3, 1, false) SBM_BD(3, 4, false)
-  SBM_BD(3, 5, false) SBM_BD(3, 6, false) SBM_BD(3, 7, false) SBM_BD(3, 8, false)
+#define SBM_BD2(D_, P_) SBM_BD(D_, P_, true) SBM_BD(D_, P_, false)
+  SBM_BD2(2, 1) SBM_BD2(2, 2) SBM_BD2(2, 3) SBM_BD2(2, 4) SBM_BD2(2, 5) SBM_BD2(2, 6) SBM_BD2(2, 7) SBM_BD2(2, 8)
+  SBM_BD2(3, 1) SBM_BD2(3, 2) SBM_BD2(3, 3) SBM_BD2(3, 4) SBM_BD2(3, 5) SBM_BD2(3, 6) SBM_BD2(3, 7) SBM_BD2(3, 8)
+#undef SBM_BD2
 #undef SBM_BD
   *bx = *by = *bz = 1;
 }
@@ -2293,7 +2412,7 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
   int64_t tot[3] = {0, 0, 0};
   for (size_t i = 0; i < cs.size(); ++i) {
     const sbm_ctx *c = cs[i];
-    if (c->disc != c0->disc || c->dim != c0->dim || c->p != c0->p || c->lanes != c0->lanes) return hipErrorInvalidValue;
+    if (c->disc != c0->disc || c->dim != c0->dim || c->p != c0->p || c->by_cells != c0->by_cells) return hipErrorInvalidValue;
     int32_t nb[3] = {0, 0, 0};
     const bool ok = g.prec == SBM_F64 ? (c->dim == 3 ? batch_blocks_dim<double, 3>(c, own_faces[i] != 0, nb)
                                                      : batch_blocks_dim<double, 2>(c, own_faces[i] != 0, nb))

@@ -101,7 +101,7 @@ struct sbm_ctx {
   std::vector<int32_t> nbr;        // n_cells x 2d: neighbour rank, or -2 - f for surrogate face f
   // CG bricks: BX x BY x BZ blocks of background cells, one workgroup each
   int brick[3] = {1, 1, 1};
-  bool lanes = false;  // form of the brick kernel (brick_lanes)
+  bool by_cells = false;  // form of the brick kernel (brick_by_cells)
   int64_t n_bricks = 0;
   int64_t n_bricks_faces = 0;  // number of bricks that carry surrogate faces
   std::vector<int32_t> brick_cell_off, brick_cells, brick_cell_loc;
@@ -186,10 +186,10 @@ hipError_t launch_batch_group(const BatchGroup &g, const void *base, hipStream_t
 // The truncated extension's surrogate-face results (Rv, Rg per face node) of u into fbuf
 // (kernels_taylor.hip); nothing to do for an operator without surrogate faces.
 hipError_t launch_taylor_faces(const sbm_ctx *c, const void *u, void *fbuf, int prec, hipStream_t s);
-// Form of the CG brick kernel for an operator (p + 1 lanes per cell, or lattice sweeps), and the
+// Form of the CG brick kernel for an operator (cell by cell, or lattice sweeps), and the
 // brick shape (cells per direction) of a form.
-bool brick_lanes(int dim, int p, int64_t n_cells);
-void brick_dims(int dim, int p, bool lanes, int *bx, int *by, int *bz);
+bool brick_by_cells(int dim, int p, int64_t n_cells);
+void brick_dims(int dim, int p, bool by_cells, int *bx, int *by, int *bz);
 // Brick numbering from the per-slot cell and face counts of the brick grid: key_of[b] is the
 // grid slot of brick b, bid[slot] its brick number (-1 if empty).  Every one of the 8 XCD
 // ranges gets an equal share of the face-carrying bricks, first, then of the others (see

@@ -408,8 +408,8 @@ int64_t order_bricks(const std::vector<int32_t> &count, const std::vector<int32_
 static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx, int64_t ly, int64_t lz) {
   const int d = c->dim, p = c->p;
   int BX, BY, BZ;
-  c->lanes = brick_lanes(d, p, c->n_cells);
-  brick_dims(d, p, c->lanes, &BX, &BY, &BZ);
+  c->by_cells = brick_by_cells(d, p, c->n_cells);
+  brick_dims(d, p, c->by_cells, &BX, &BY, &BZ);
   if (d == 2) BZ = 1;
   c->brick[0] = BX;
   c->brick[1] = BY;
@@ -1215,8 +1215,8 @@ size_t sbm_footprint_estimate(const sbm_mesh *mesh, int p, int disc, int64_t n_c
   if (disc == SBM_CG) {
     const int64_t ndofs = nc * nb;  // every active cell touches (p+1)^d lattice points
     int bx = 1, by = 1, bz = 1;
-    const bool lanes = brick_lanes(d, p, nc);
-    brick_dims(d, p, lanes, &bx, &by, &bz);
+    const bool by_cells = brick_by_cells(d, p, nc);
+    brick_dims(d, p, by_cells, &bx, &by, &bz);
     const int64_t B[3] = {bx, by, d == 3 ? bz : 1};
     // brick-boundary points of one cell: on each axis it meets both brick planes if the brick
     // is one cell wide there, else at most one
@@ -1226,7 +1226,7 @@ size_t sbm_footprint_estimate(const sbm_mesh *mesh, int p, int disc, int64_t n_c
     const int64_t rows = (B[1] * p + 1) * (d == 3 ? B[2] * p + 1 : 1);  // lattice rows per brick
     const int64_t nbricks = nc;                                        // every brick has a cell
     int64_t nrows = nbricks * rows;
-    if (lanes) {
+    if (by_cells && d == 3 && p <= 3) {
       // (bricks of many rows, but no more of them than the mesh has places: bounded by 81 or 169
       // rows per cell unless the domain is that sparse)
       int64_t places = 1;

@@ -587,8 +587,8 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
   int32_t *hflag = nullptr, *hpre = nullptr;
   if (cg) {
     int BX, BY, BZ;
-    c->lanes = brick_lanes(d, g.p, nc);
-    brick_dims(d, g.p, c->lanes, &BX, &BY, &BZ);
+    c->by_cells = brick_by_cells(d, g.p, nc);
+    brick_dims(d, g.p, c->by_cells, &BX, &BY, &BZ);
     if (d == 2) BZ = 1;
     c->brick[0] = BX;
     c->brick[1] = BY;
