@@ -459,7 +459,10 @@ struct BrickArgs {
   const int32_t *row_base;   // n_bricks x rows: DoF id of the first globally present point
   const uint32_t *row_gmask; // bit x: lattice point x of the row is a DoF
   const uint32_t *row_bmask; // bit x: ... and is touched by an active cell of this brick
-  const int32_t *row_hbase;  // first halo slot of the row's brick-boundary points
+  // (halo indices) a row on the brick's y or z boundary: where its points 0 < x < LX - 1 start, less
+  // one if its point x = 0 is a DoF, so that a point follows by its place among the row's DoFs
+  const int32_t *row_hbase;
+  const int32_t *row_hend;   // n_bricks x 2 x rows: the rows' points x = 0, then their points x = LX - 1
 };
 
 // One operator of a batch of applies (see the batched kernels after apply_impl): its arrays,
@@ -648,6 +651,13 @@ __device__ __forceinline__ void sweeps_body(const int blk, BrickArgs br, const T
       s_gmask[r] = br.row_gmask[rb + r];
       s_bmask[r] = br.row_bmask[rb + r];
     }
+  }
+  constexpr int NE = (2 * NROWS + nthr - 1) / nthr;  // row ends per thread
+  int32_t hend[NE];
+#pragma unroll
+  for (int m = 0; m < NE; ++m) {
+    const int i = tid + m * nthr;
+    hend[m] = br.row_hend[2 * rb + (i < 2 * NROWS ? i : 0)];
   }
   if (C::STAGE_RUNS && !full && (parts & SBM_PART_CELLS)) {
     for (int i = tid; i < (c1 - c0) * NP; i += nthr) s_runs[i] = br.runs[(int64_t)c0 * NP + i];
@@ -889,26 +899,32 @@ __device__ __forceinline__ void sweeps_body(const int blk, BrickArgs br, const T
     }
   }
   __syncthreads();
-  // write-out: lanes walk the lattice with x fastest, so stores are row-contiguous.
-  // Points strictly inside the brick box belong to this brick alone: final value.  Points
+  // write-out: points strictly inside the brick box belong to this brick alone: final value.  Points
   // on the box boundary go to plane k = [x == 0] + 2 [y == 0] + 4 [z == 0] of the halo (the
   // brick's side of the point; bricks sharing the point differ in k), at the point's halo
-  // index (consecutive along the row's boundary DoFs); halo_reduce_kernel sums the planes.
-  // Lane layout: each wavefront takes RPW whole rows per pass (lane = row slot * LX + x), so a
-  // lane's x and everything that depends on it only (masks below x, x on the box boundary)
-  // are fixed, and a pass only advances the row; (y, z) of the row advance by a constant.
-  // The passes are unrolled, every LDS read first, so that one wait covers them all.
+  // index; halo_reduce_kernel sums the planes.
+  // The rows' ends: y fastest, as their halo indices.
+#pragma unroll
+  for (int m = 0; m < NE; ++m) {
+    const int i = tid + m * nthr, side = i >= NROWS ? 1 : 0, r = i < 2 * NROWS ? i - side * NROWS : 0;
+    const int y = r % LY, z = r / LY, x = side ? LX - 1 : 0;
+    const uint32_t bm = full ? ~0u : s_bmask[r];
+    const int plane = (side ? 0 : 1) | (y == 0 ? 2 : 0) | ((D == 3 && z == 0) ? 4 : 0);
+    const T val = acc[r * LX + x];
+    if (i < 2 * NROWS && ((bm >> x) & 1u)) halo[(int64_t)plane * nhalo + hend[m]] = val;
+  }
+  // The points 0 < x < LX - 1, x fastest: stores are row-contiguous.  Each wavefront takes RPW whole
+  // rows per pass, so a lane's x is fixed, and a pass only advances the row; (y, z) of the row
+  // advance by a constant.  The passes are unrolled, every LDS read first, so that one wait covers
+  // them all.
   {
-    constexpr int RPW = 64 / LX, NW = C::NT / 64, STEP = NW * RPW;
+    constexpr int W = LX - 2, RPW = 64 / W, NW = C::NT / 64, STEP = NW * RPW;
     constexpr int NPASS = (NROWS + STEP - 1) / STEP;
     constexpr int QY = STEP % LY, QZ = STEP / LY;
-    constexpr uint32_t ALL = (LX == 32) ? 0xffffffffu : ((1u << LX) - 1u);
     static_assert(RPW >= 1 && C::NT % 64 == 0, "a wavefront holds at least one lattice row");
-    const int lane = tid & 63, rl = lane / LX, x = lane - rl * LX;
+    const int lane = tid & 63, rl = lane / W, x = 1 + lane - rl * W;
     const bool xl = rl < RPW;
     const uint32_t below = (1u << x) - 1u;
-    const bool xin = (unsigned)(x - 1) < (unsigned)(LX - 2);  // 0 < x < LX - 1
-    const int xplane = x == 0 ? 1 : 0;
     const int row0 = (tid >> 6) * RPW + rl;
     int y = row0 % LY, z = row0 / LY;
     constexpr int CH = NPASS < 9 ? NPASS : 9;  // passes per group (bounds the registers held)
@@ -925,19 +941,15 @@ __device__ __forceinline__ void sweeps_body(const int blk, BrickArgs br, const T
         val[k] = acc[rc * LX + x];
         base[k] = s_base[rc];
         hb[k] = s_hbase[rc];
-        gmk[k] = full ? ALL : s_gmask[rc];
-        bmk[k] = (full || !on) ? (on ? ALL : 0u) : s_bmask[rc];
+        gmk[k] = full ? ~0u : s_gmask[rc];
+        bmk[k] = (full || !on) ? (on ? ~0u : 0u) : s_bmask[rc];
       }
 #pragma unroll
       for (int k = 0; k < CH; ++k) {
-        const uint32_t gm = gmk[k];
         const bool brow = ((unsigned)(y - 1) >= (unsigned)(LY - 2)) |
                           ((D == 3) & ((unsigned)(z - 1) >= (unsigned)(LZ - 2)));
-        const bool inner = !brow & xin;
-        const uint32_t hgm = brow ? gm : (gm & (1u | (1u << (LX - 1))));
-        const int plane = xplane | (y == 0 ? 2 : 0) | ((D == 3 && z == 0) ? 4 : 0);
-        T *dst = inner ? v + base[k] + __popc(gm & below)
-                       : halo + (int64_t)plane * nhalo + hb[k] + __popc(hgm & below);
+        const int plane = (y == 0 ? 2 : 0) | ((D == 3 && z == 0) ? 4 : 0);
+        T *dst = (brow ? halo + ((int64_t)plane * nhalo + hb[k]) : v + base[k]) + __popc(gmk[k] & below);
         if ((bmk[k] >> x) & 1u) *dst = val[k];
         y += QY;
         z += QZ;
@@ -988,9 +1000,9 @@ struct BrickRows {
   static_assert(K3 + YB * ZB == C::NROWS, "every row once");
   static_assert(C::NROWS <= C::NT, "one row per thread");
   static_assert(C::LX <= 32, "row masks hold 32 points");
-  enum { kLowY = 1, kHighY = 2, kLowZ = 4, kHighZ = 8, kY0 = 16, kZ0 = 32, kEdge = 64 };
+  enum { kLowY = 1, kHighY = 2, kLowZ = 4, kHighZ = 8, kY0 = 16, kZ0 = 32 };
   T *dst[C::NROWS];           // where the points 0 < x < LX-1 go, by their place among the row's DoFs
-  int32_t hbase[C::NROWS];    // halo index
+  int32_t hend[2 * C::NROWS]; // halo indices of the rows' ends, x = 0 first
   int32_t off[C::NROWS];      // 256 x (place of the row in the results) + flags
   uint32_t gmask[C::NROWS], bmask[C::NROWS];
   int32_t base[C::NROWS];     // by the row's own place y + LY z: id of its first DoF,
@@ -1015,10 +1027,11 @@ struct BrickRows {
     base[own] = b;
     first[own] = gm;
     dst[r] = edge ? halo + (int64_t)plane * nhalo + hb : v + b;
-    hbase[r] = hb;
+    hend[r] = br.row_hend[2 * (at - own) + own];
+    hend[C::NROWS + r] = br.row_hend[2 * (at - own) + C::NROWS + own];
     off[r] = (((cz * BY + cy) * BX * C::TILE + (lz * (P + 1) + ly) * (P + 1)) << 8) |
              (yb && cy > 0 ? kLowY : 0) | (cy < BY ? kHighY : 0) | (zb && cz > 0 ? kLowZ : 0) |
-             (cz < BZ ? kHighZ : 0) | (y == 0 ? kY0 : 0) | (C::DIM == 3 && z == 0 ? kZ0 : 0) | (edge ? kEdge : 0);
+             (cz < BZ ? kHighZ : 0) | (y == 0 ? kY0 : 0) | (C::DIM == 3 && z == 0 ? kZ0 : 0);
     gmask[r] = gm;
     bmask[r] = bm;
   }
@@ -1027,13 +1040,10 @@ struct BrickRows {
     const int own = cy * P + j + C::LY * (cz * P + k);
     return base[own] + __popc(first[own] & ((1u << (cx * P)) - 1u));
   }
-  // Halo plane and index of a row's end (side 0: x = 0, 1: x = LX-1), as an offset.  The row's
-  // brick-boundary DoFs follow each other: all of it on the brick's y or z sides, else the two ends.
+  // Halo plane and index of a row's end (side 0: x = 0, 1: x = LX-1), as an offset.
   __device__ __forceinline__ int64_t end_at(int r, int side, int nhalo) const {
-    const int o = off[r], x = side ? C::LX - 1 : 0;
-    const uint32_t gm = gmask[r], hgm = (o & kEdge) ? gm : (gm & (1u | (1u << (C::LX - 1))));
-    const int plane = (side ? 0 : 1) | ((o & kY0) ? 2 : 0) | ((o & kZ0) ? 4 : 0);
-    return (int64_t)plane * nhalo + hbase[r] + __popc(hgm & ((1u << x) - 1u));
+    const int o = off[r], plane = (side ? 0 : 1) | ((o & kY0) ? 2 : 0) | ((o & kZ0) ? 4 : 0);
+    return (int64_t)plane * nhalo + hend[side * C::NROWS + r];
   }
 };
 
@@ -1056,7 +1066,7 @@ __device__ __forceinline__ void brick_assemble(const T *tiles, const BrickRows<T
   constexpr int NE = (2 * NROWS + C::NT - 1) / C::NT;
 #pragma unroll
   for (int m = 0; m < NE; ++m) {
-    const int i = tid + m * C::NT, r = i < 2 * NROWS ? i >> 1 : 0, side = i & 1, o = R.off[r];
+    const int i = tid + m * C::NT, side = i >= NROWS ? 1 : 0, r = i < 2 * NROWS ? i - side * NROWS : 0, o = R.off[r];
     const int off = (o >> 8) + (side ? (BX - 1) * TS + P : 0);
     const uint32_t bm = i < 2 * NROWS ? R.bmask[r] : 0u;
     T sum = T(0);
@@ -1407,9 +1417,22 @@ __global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_kernel(
   brick_body<T, D, N1, CELLS>(xcd_block(), br, fbuf, u, v, halo, nhalo, tab, scale, parts);
 }
 
+// (nontemporal in FP64: 128^3 Q4 apply 357 -> 346 us, 64^3 61 -> 58 us, 1024^2 Q3 54 -> 48 us; FP32 64^3
+// Q4 39.5 -> 40.9 us)
+template <typename T>
+__device__ __forceinline__ T load_once(const T *p) {
+  if constexpr (sizeof(T) == 8) return __builtin_nontemporal_load(p);
+  return *p;
+}
+
 // v[dof] = sum over the planes k present in the DoF's mask, in increasing k (deterministic).
 // Two DoFs per thread (a block's 2 * 256 consecutive ones), so that each thread has twice the
-// loads in flight (FP64 apply at 64^3 Q4: 50.2 against 51.2 us).
+// loads in flight (FP64 apply at 64^3 Q4: 50.2 against 51.2 us; with four 1.5 us slower).
+// What bounds it: the points on x planes, each a store of one value to a cache line of v.  They are a
+// sixteenth of all points at 3D p=4 and cost 45 of 110 us on 128^3 FP64 (measured with the same stores
+// side by side).  With the halo numbered for dense planes and stores (see build_bricks) instead of in
+// DoF order, 128^3 Q4 FP64: brick kernel 264 -> 235 us, apply 417 -> 357 us; FP32 152 -> 140 and
+// 231 -> 221 us.  One contiguous range of it per XCD measured slower (128^3 FP64 381 us).
 constexpr int kHaloPerThread = 2;
 template <typename T, int D>
 __device__ __forceinline__ void halo_reduce_body(const int blk, int n, const int32_t *__restrict__ dof,
@@ -1431,7 +1454,7 @@ __device__ __forceinline__ void halo_reduce_body(const int blk, int n, const int
   for (int k = 0; k < (1 << D); ++k)
 #pragma unroll
     for (int r = 0; r < kHaloPerThread; ++r)
-      s[r] += ((m[r] >> k) & 1u) ? halo[(int64_t)k * n + i0 + r * 256] : T(0);
+      s[r] += ((m[r] >> k) & 1u) ? load_once(&halo[(int64_t)k * n + i0 + r * 256]) : T(0);
 #pragma unroll
   for (int r = 0; r < kHaloPerThread; ++r)
     if (i0 + r * 256 < n) v[dd[r]] = s[r];
@@ -2003,7 +2026,7 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
     if (c->n_bricks > 0 && (parts & (SBM_PART_CELLS | SBM_PART_SBM_FACES))) {
       const BrickArgs br{c->d_brick_cell_off, c->d_brick_runs, c->d_brick_cell_loc, c->d_brick_face_off,
                          c->d_brick_face_loc, c->d_face_code,  c->d_brick_cell_face, c->d_row_base,       c->d_row_gmask,
-                         c->d_row_bmask,      c->d_row_hbase};
+                         c->d_row_bmask,      c->d_row_hbase,     c->d_row_hend};
       T *halo = (T *)scr.halo;
       T *fbuf = (T *)scr.fbuf;
       if (nf > 0 && (parts & SBM_PART_SBM_FACES) && !(parts & SBM_PART_REUSE_FACES)) {
@@ -2422,7 +2445,7 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
     BatchItem &it = items[i];
     it.br = BrickArgs{c->d_brick_cell_off, c->d_brick_runs, c->d_brick_cell_loc, c->d_brick_face_off,
                       c->d_brick_face_loc, c->d_face_code,  c->d_brick_cell_face, c->d_row_base,       c->d_row_gmask,
-                      c->d_row_bmask,      c->d_row_hbase};
+                      c->d_row_bmask,      c->d_row_hbase,     c->d_row_hend};
     it.face_code = c->d_face_code;
     it.face_runs = c->d_face_runs;
     it.face_cell = c->d_face_cell;

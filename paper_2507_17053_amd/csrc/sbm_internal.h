@@ -111,7 +111,7 @@ struct sbm_ctx {
   // per cell in brick order: 64 x (its first surrogate face, from the brick's first) + the mask of
   // the codes 2 axis + side of its faces (they follow each other in code order)
   std::vector<int32_t> brick_cell_face;
-  std::vector<int32_t> row_base, row_hbase;
+  std::vector<int32_t> row_base, row_hbase, row_hend;
   std::vector<uint32_t> row_gmask, row_bmask;
   // halo assembly: a DoF on brick boundaries collects one value per touching brick, in plane
   // k (2^d planes of n_halo_dofs values) given by the brick's side of the point
@@ -119,7 +119,7 @@ struct sbm_ctx {
   std::vector<int32_t> halo_dof;   // halo index -> DoF
   std::vector<uint8_t> halo_mask;  // halo index -> planes written
   bool halo_ok = true;             // consistency of the halo numbering (checked at setup)
-  int32_t *d_row_hbase = nullptr, *d_halo_dof = nullptr;
+  int32_t *d_row_hbase = nullptr, *d_row_hend = nullptr, *d_halo_dof = nullptr;
   uint8_t *d_halo_mask = nullptr;
   void *d_halo = nullptr;  // 2^d x n_halo_dofs doubles (also used as floats); per-handle scratch
   void *d_fbuf = nullptr;  // n_sbm x 2 x (p+1)^(d-1) doubles, surrogate-face results; per-handle scratch

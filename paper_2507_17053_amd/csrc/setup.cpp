@@ -369,7 +369,8 @@ static void free_device(sbm_ctx *c) {
   c->d_runs = c->d_nbr = c->d_face_cell = c->d_face_code = nullptr;
   c->d_face_xi = nullptr;
   c->d_brick_cell_off = c->d_brick_runs = c->d_face_runs = c->d_brick_cell_loc = nullptr;
-  c->d_brick_face_off = c->d_brick_face_loc = c->d_brick_cell_face = c->d_row_base = c->d_row_hbase = c->d_halo_dof = nullptr;
+  c->d_brick_face_off = c->d_brick_face_loc = c->d_brick_cell_face = c->d_row_base = c->d_row_hbase = c->d_row_hend = c->d_halo_dof =
+      nullptr;
   c->d_row_gmask = c->d_row_bmask = nullptr;
   c->d_halo_mask = nullptr;
   c->d_halo = c->d_fbuf = nullptr;
@@ -543,54 +544,85 @@ static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx,
       }
   }
   // Halo: the DoFs on brick-box boundaries (bricks are aligned, so such a point lies on the
-  // boundary of every brick that contains it).  They are numbered in DoF order (halo index);
-  // along a brick row the boundary DoFs have consecutive halo indices.  A brick writes its
+  // boundary of every brick that contains it), numbered (halo index) so that a brick's stores and the
+  // reduction's reads of one plane are dense, and the reduction stores whole rows of v where it can:
+  // first the points on x planes only, by their row within the bricks, then x plane, then row of
+  // bricks; then, lattice row by lattice row, the row's points on x planes and its others, where those
+  // of a brick row are consecutive.
+  // (All of them in DoF order, the reduction read planes 1 and 3 in full for every 16th point of a
+  // row at 3D p=4, and a brick stored its x planes one value to a cache line.)  A brick writes its
   // value for such a point into plane k = [x == 0] + 2 [y == 0] + 4 [z == 0] (its brick-
   // lattice coordinates: the side of the point the brick lies on), at the point's halo index;
   // bricks sharing a point have distinct k.  The reduction sums, per halo DoF, the planes
-  // present in its mask in increasing k (a fixed order).  row_hbase: halo index of the row's
-  // first boundary DoF.
+  // present in its mask in increasing k (a fixed order).
   const uint32_t edge = 1u | (1u << (LX - 1));
-  auto boundary_mask = [&](int y, int z, uint32_t gm) {
-    const bool brow = (y == 0 || y == LY - 1 || (d == 3 && (z == 0 || z == LZ - 1)));
-    return brow ? gm : (gm & edge);
+  auto boundary_row = [&](int y, int z) { return y == 0 || y == LY - 1 || (d == 3 && (z == 0 || z == LZ - 1)); };
+  auto boundary_mask = [&](int y, int z, uint32_t gm) { return boundary_row(y, z) ? gm : (gm & edge); };
+  const int64_t BYP = BY * p, nyb = ly / BYP + 1;
+  std::vector<int32_t> hidx(c->n_dofs, -1), sidx((nbx + 1) * nyb * BYP * lz, -1);
+  std::vector<unsigned char> kind(c->n_dofs, 0);  // 1: on an x plane, 2: not
+  auto end_slot = [&](int32_t b, int side, int y, int z) {
+    const int64_t key = key_of[b], Y = (key / nbx) % nby * BYP + y, Z = d == 3 ? key / (nbx * nby) * BZ * p + z : 0;
+    return Y % BYP + BYP * (key % nbx + side + (nbx + 1) * (Y / BYP + nyb * Z));
   };
-  std::vector<int32_t> hidx(c->n_dofs, -1);
   for (int32_t b = 0; b < nb; ++b)
     for (int z = 0; z < LZ; ++z)
       for (int y = 0; y < LY; ++y) {
         const size_t ri = (size_t)b * nrows + y + LY * z;
         const uint32_t hm = boundary_mask(y, z, c->row_bmask[ri]);
-        for (int x = 0; x < LX; ++x)
-          if ((hm >> x) & 1u)
-            hidx[c->row_base[ri] + __builtin_popcount(c->row_gmask[ri] & ((1u << x) - 1u))] = 0;
+        for (int x = 0; x < LX; ++x) {
+          if (!((hm >> x) & 1u)) continue;
+          const int32_t g = c->row_base[ri] + __builtin_popcount(c->row_gmask[ri] & ((1u << x) - 1u));
+          if (boundary_row(y, z))
+            kind[g] = x == 0 || x == LX - 1 ? 1 : 2;
+          else
+            sidx[end_slot(b, x == 0 ? 0 : 1, y, z)] = g;
+        }
       }
   c->halo_dof.clear();
-  for (int64_t g = 0; g < c->n_dofs; ++g)
-    if (hidx[g] == 0) {
+  for (int32_t g : sidx)
+    if (g >= 0) {
       hidx[g] = (int32_t)c->halo_dof.size();
-      c->halo_dof.push_back((int32_t)g);
+      c->halo_dof.push_back(g);
     }
+  std::vector<int32_t> row;
+  for (int64_t m = 0; m < ly * lz; ++m) {
+    row.clear();
+    for (int64_t x = 0; x < lx; ++x)
+      if (id[m * lx + x] >= 0) row.push_back(id[m * lx + x]);
+    for (int k = 1; k <= 2; ++k)
+      for (int32_t g : row)
+        if (kind[g] == k) {
+          hidx[g] = (int32_t)c->halo_dof.size();
+          c->halo_dof.push_back(g);
+        }
+  }
   c->n_halo_dofs = (int64_t)c->halo_dof.size();
   c->halo_mask.assign(c->n_halo_dofs, 0);
   c->row_hbase.assign((size_t)nb * nrows, 0);
+  c->row_hend.assign((size_t)nb * nrows * 2, 0);
   int64_t slots = 0;
   c->halo_ok = true;
   for (int32_t b = 0; b < nb; ++b)
     for (int z = 0; z < LZ; ++z)
       for (int y = 0; y < LY; ++y) {
-        const size_t ri = (size_t)b * nrows + y + LY * z;
+        const int row = y + LY * z;
+        const size_t ri = (size_t)b * nrows + row;
         const uint32_t gm = c->row_gmask[ri];
         const uint32_t hgm = boundary_mask(y, z, gm), hm = boundary_mask(y, z, c->row_bmask[ri]);
-        if (hgm) {
-          const int x0 = __builtin_ctz(hgm);
-          c->row_hbase[ri] = hidx[c->row_base[ri] + __builtin_popcount(gm & ((1u << x0) - 1u))];
-        }
+        const uint32_t inner = hgm & ~edge;
+        if (inner)
+          c->row_hbase[ri] = hidx[c->row_base[ri] + __builtin_popcount(gm & ((inner & -inner) - 1u))] - (int32_t)(gm & 1u);
         for (int x = 0; x < LX; ++x) {
           if (!((hgm >> x) & 1u)) continue;
-          const int32_t h = hidx[c->row_base[ri] + __builtin_popcount(gm & ((1u << x) - 1u))];
-          // every boundary DoF of the row is a halo DoF, numbered consecutively along the row
-          if (h < 0 || h != c->row_hbase[ri] + __builtin_popcount(hgm & ((1u << x) - 1u))) c->halo_ok = false;
+          const int before = __builtin_popcount(gm & ((1u << x) - 1u));
+          const int32_t h = hidx[c->row_base[ri] + before];
+          // every boundary DoF of the row is a halo DoF, those inside the row numbered consecutively
+          if (x == 0 || x == LX - 1)
+            c->row_hend[(size_t)b * 2 * nrows + (x == 0 ? 0 : nrows) + row] = h;
+          else if (h != c->row_hbase[ri] + before)
+            c->halo_ok = false;
+          if (h < 0) c->halo_ok = false;
           if ((hm >> x) & 1u) {
             const int k = (x == 0 ? 1 : 0) | (y == 0 ? 2 : 0) | ((d == 3 && z == 0) ? 4 : 0);
             if (h >= 0) c->halo_mask[h] |= (uint8_t)(1u << k);
@@ -981,6 +1013,7 @@ sbm_status sbm_setup(const sbm_mesh *mesh, const sbm_levelset *ls, int p, int di
     plan.add(c->d_row_gmask, c->row_gmask);
     plan.add(c->d_row_bmask, c->row_bmask);
     plan.add(c->d_row_hbase, c->row_hbase);
+    plan.add(c->d_row_hend, c->row_hend);
     plan.add(c->d_halo_dof, c->halo_dof);
     plan.add(c->d_halo_mask, c->halo_mask);
     plan.scratch(c->d_halo, ((size_t)1 << c->dim) * (size_t)c->n_halo_dofs * sizeof(double));
@@ -1236,7 +1269,7 @@ size_t sbm_footprint_estimate(const sbm_mesh *mesh, int p, int disc, int64_t n_c
     b += up(4 * nc * np) * 2;                                          // runs, brick_runs
     b += up(4 * (nbricks + 1)) * 2 + up(4 * nc) * 2 + up(4 * nf);      // offsets, cell/face locations
     b += up(4 * nf * np);                                              // face_runs
-    b += 4 * up(4 * nrows);                                            // row descriptors
+    b += 4 * up(4 * nrows) + up(8 * nrows);                                            // row descriptors
     b += up(4 * halo) + up(halo);                                      // halo DoF ids and masks
     b += up(((int64_t)1 << d) * 8 * halo);                             // halo planes (FP64)
   } else {

@@ -303,15 +303,33 @@ __device__ __forceinline__ bool brick_touched(const Geo &g, const Bricks &bk, co
   return false;
 }
 
+__device__ __forceinline__ bool boundary_row(const Geo &g, const Bricks &bk, int y, int z) {
+  return y == 0 || y == bk.LY - 1 || (g.d == 3 && (z == 0 || z == bk.LZ - 1));
+}
+
 __device__ __forceinline__ uint32_t boundary_mask(const Geo &g, const Bricks &bk, int y, int z, uint32_t m) {
   const uint32_t edge = 1u | (1u << (bk.LX - 1));
-  const bool brow = (y == 0 || y == bk.LY - 1 || (g.d == 3 && (z == 0 || z == bk.LZ - 1)));
-  return brow ? m : (m & edge);
+  return boundary_row(g, bk, y, z) ? m : (m & edge);
+}
+
+// Halo numbering (see build_bricks): flags, then their exclusive prefix sums, of the points on x planes
+// only (side, by end_slot), and by DoF of the other boundary points on x planes (end) and off them (in).
+struct HaloScan {
+  int32_t *side, *end, *in;
+  int32_t n_side;
+};
+
+// Place of lattice row (Y, Z)'s point on the x plane to the low (side 0) or high side of a brick: by the
+// row within its bricks, then x plane, then row of bricks.
+__device__ __forceinline__ int64_t end_slot(const Bricks &bk, const Lat &lt, int64_t key, int side, int64_t Y,
+                                            int64_t Z) {
+  const int64_t B = bk.LY - 1, nb = lt.ly / B + 1;
+  return Y % B + B * (key % bk.nbx + side + (bk.nbx + 1) * (Y / B + nb * Z));
 }
 
 __global__ void rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, const int64_t *key_of,
                             const int32_t *rank_grid, const int32_t *lflag, const int32_t *lpre, int32_t *row_base,
-                            uint32_t *row_gmask, uint32_t *row_bmask, int32_t *hflag) {
+                            uint32_t *row_gmask, uint32_t *row_bmask, HaloScan hs) {
   GRID_LOOP(e, nbricks * bk.nrows) {
     const int64_t b = e / bk.nrows;
     const int row = (int)(e % bk.nrows);
@@ -341,44 +359,71 @@ __global__ void rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, const int
     row_bmask[e] = bm;
     const uint32_t hm = boundary_mask(g, bk, y, z, bm);
     for (int x = 0; x < bk.LX; ++x)
-      if ((hm >> x) & 1u) hflag[base + __popc(gm & ((1u << x) - 1u))] = 1;
+      if ((hm >> x) & 1u) {
+        const bool end = x == 0 || x == bk.LX - 1;
+        if (!boundary_row(g, bk, y, z))
+          hs.side[end_slot(bk, lt, key, x == 0 ? 0 : 1, Y, Z)] = 1;
+        else
+          (end ? hs.end : hs.in)[base + __popc(gm & ((1u << x) - 1u))] = 1;
+      }
   }
 }
 
-__global__ void halo_dof_kernel(int64_t n, const int32_t *hflag, const int32_t *hpre, int32_t *halo_dof) {
-  GRID_LOOP(g, n) {
-    if (hflag[g]) halo_dof[hpre[g]] = (int32_t)g;
-  }
-}
-
-__global__ void halo_rows_kernel(Geo g, Bricks bk, int64_t nbricks, const int32_t *row_base, const uint32_t *row_gmask,
-                                 const uint32_t *row_bmask, const int32_t *hflag, const int32_t *hpre,
-                                 int32_t *row_hbase, uint32_t *hmask32, unsigned long long *slots, int *bad) {
+__global__ void halo_rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, int64_t n_dofs, const int64_t *key_of,
+                                 const int32_t *lpre, const int32_t *row_base, const uint32_t *row_gmask,
+                                 const uint32_t *row_bmask, HaloScan hs, int32_t *row_hbase, int32_t *row_hend,
+                                 int32_t *halo_dof, uint32_t *hmask32, unsigned long long *slots, int *bad) {
   GRID_LOOP(e, nbricks * bk.nrows) {
+    const int64_t b = e / bk.nrows, key = key_of[b];
     const int row = (int)(e % bk.nrows);
     const int y = row % bk.LY, z = row / bk.LY;
+    const int64_t Y = (key / bk.nbx) % bk.nby * bk.BY * g.p + y,
+                  Z = g.d == 3 ? key / (bk.nbx * bk.nby) * bk.BZ * g.p + z : 0;
     const uint32_t gm = row_gmask[e];
     const uint32_t hgm = boundary_mask(g, bk, y, z, gm), hm = boundary_mask(g, bk, y, z, row_bmask[e]);
+    const uint32_t inner = hgm & ~(1u | (1u << (bk.LX - 1)));
     const int32_t base = row_base[e];
-    auto hidx = [&](int x) {
+    const bool brow = boundary_row(g, bk, y, z);
+    int32_t first_end = 0, first_in = 0;  // of the lattice row
+    if (hgm && brow) {
+      const int64_t m = (Z * lt.ly + Y) * lt.lx;
+      const int64_t r0 = lpre[m], r1 = m + lt.lx < lt.lx * lt.ly * lt.lz ? lpre[m + lt.lx] : n_dofs;
+      first_end = hs.n_side + hs.in[r0];
+      first_in = hs.n_side + hs.end[r1];
+    }
+    auto index = [&](int x) {
       const int32_t dof = base + __popc(gm & ((1u << x) - 1u));
-      return hflag[dof] ? hpre[dof] : -1;
+      const bool end = x == 0 || x == bk.LX - 1;
+      const int64_t at = brow ? dof : end_slot(bk, lt, key, x == 0 ? 0 : 1, Y, Z);
+      const int32_t *pre = brow ? (end ? hs.end : hs.in) : hs.side;
+      return pre[at + 1] == pre[at] ? -1 : pre[at] + (brow ? (end ? first_end : first_in) : 0);
     };
-    int32_t hb = 0;
-    if (hgm) hb = hidx(__ffs(hgm) - 1);
+    const int32_t hb = inner ? index(__ffs(inner) - 1) - (int32_t)(gm & 1u) : 0;
     row_hbase[e] = hb;
+    int32_t he[2] = {0, 0};
     int cnt = 0;
     for (int x = 0; x < bk.LX; ++x) {
       if (!((hgm >> x) & 1u)) continue;
-      const int32_t h = hidx(x);
-      // every boundary DoF of the row is a halo DoF, numbered consecutively along the row
-      if (h < 0 || h != hb + (int32_t)__popc(hgm & ((1u << x) - 1u))) atomicOr(bad, 2);
+      const int before = __popc(gm & ((1u << x) - 1u));
+      const int32_t h = index(x);
+      // every boundary DoF of the row is a halo DoF, those inside the row numbered consecutively
+      if (x == 0 || x == bk.LX - 1)
+        he[x == 0 ? 0 : 1] = h;
+      else if (h != hb + before)
+        atomicOr(bad, 2);
+      if (h < 0) {
+        atomicOr(bad, 2);
+        continue;
+      }
       if ((hm >> x) & 1u) {
         const int k = (x == 0 ? 1 : 0) | (y == 0 ? 2 : 0) | ((g.d == 3 && z == 0) ? 4 : 0);
-        if (h >= 0) atomicOr(&hmask32[h], 1u << k);
+        atomicOr(&hmask32[h], 1u << k);
+        halo_dof[h] = base + before;
         ++cnt;
       }
     }
+    row_hend[2 * (e - row) + row] = he[0];
+    row_hend[2 * (e - row) + bk.nrows + row] = he[1];
     if (cnt) atomicAdd(slots, (unsigned long long)cnt);
   }
 }
@@ -419,10 +464,10 @@ hipError_t exclusive_scan(Temps &tmp, const int32_t *in, int32_t *out, int64_t n
   if (e != hipSuccess) return e;
   void *ws = tmp.get<char>((int64_t)bytes);
   if (!ws) return tmp.err;
-  e = hipcub::DeviceScan::ExclusiveSum(ws, bytes, in, out, (int)n, tmp.s);
-  if (e != hipSuccess) return e;
   int32_t last_in = 0, last_out = 0;
-  e = hipMemcpyAsync(&last_in, in + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);
+  e = hipMemcpyAsync(&last_in, in + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);  // before out replaces it
+  if (e != hipSuccess) return e;
+  e = hipcub::DeviceScan::ExclusiveSum(ws, bytes, in, out, (int)n, tmp.s);
   if (e == hipSuccess) e = hipMemcpyAsync(&last_out, out + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);
   if (e == hipSuccess) e = hipStreamSynchronize(tmp.s);
   *total = (int64_t)last_in + last_out;
@@ -540,7 +585,7 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
   Bricks bk{};
   std::vector<int64_t> key_of;
   std::vector<int32_t> bid, cell_off, face_off;
-  int64_t n_dofs = 0, n_halo = 0;
+  int64_t n_dofs = 0, n_halo = 0, n_ends = 0;
   if (cg) {
     lt.lx = (int64_t)g.p * g.nx + 1;
     lt.ly = (int64_t)g.p * g.ny + 1;
@@ -584,7 +629,7 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
   // ---- CG bricks ----
   int32_t *d_bid = nullptr;
   int64_t *d_key_of = nullptr;
-  int32_t *hflag = nullptr, *hpre = nullptr;
+  HaloScan hs{};
   if (cg) {
     int BX, BY, BZ;
     c->by_cells = brick_by_cells(d, g.p, nc);
@@ -629,10 +674,14 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     DS_CHECK(hipMemcpyAsync(d_bid, bid.data(), sizeof(int32_t) * nslot, hipMemcpyHostToDevice, s), "upload");
     if (nbk)
       DS_CHECK(hipMemcpyAsync(d_key_of, key_of.data(), sizeof(int64_t) * nbk, hipMemcpyHostToDevice, s), "upload");
-    hflag = tmp.get<int32_t>(n_dofs);
-    hpre = tmp.get<int32_t>(n_dofs);
+    n_ends = (bk.nbx + 1) * (lt.ly / (bk.LY - 1) + 1) * (bk.LY - 1) * lt.lz;
+    hs.side = tmp.get<int32_t>(n_ends + 1);
+    hs.end = tmp.get<int32_t>(n_dofs + 1);
+    hs.in = tmp.get<int32_t>(n_dofs + 1);
     DS_CHECK(tmp.err, "allocation");
-    DS_CHECK(hipMemsetAsync(hflag, 0, sizeof(int32_t) * std::max<int64_t>(1, n_dofs), s), "memset");  // >= 1 slot
+    DS_CHECK(hipMemsetAsync(hs.side, 0, sizeof(int32_t) * (n_ends + 1), s), "memset");
+    DS_CHECK(hipMemsetAsync(hs.end, 0, sizeof(int32_t) * (n_dofs + 1), s), "memset");
+    DS_CHECK(hipMemsetAsync(hs.in, 0, sizeof(int32_t) * (n_dofs + 1), s), "memset");
   }
 
   // ---- the arena: the arrays the kernels and the host build upload, same order ----
@@ -652,6 +701,7 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     cv.add(c->d_row_gmask, nrow_all);
     cv.add(c->d_row_bmask, nrow_all);
     cv.add(c->d_row_hbase, nrow_all);
+    cv.add(c->d_row_hend, 2 * nrow_all);
   } else {
     cv.add(c->d_nbr, ne);
   }
@@ -669,8 +719,13 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     DS_CHECK(tmp.err, "allocation");
     if (nrow_all > 0)
       hipLaunchKernelGGL(rows_kernel, dim3(grid_for(nrow_all)), dim3(kT), 0, s, g, bk, lt, nbk, d_key_of, rank_grid,
-                         lflag, lpre, t_row_base, t_row_gmask, t_row_bmask, hflag);
-    DS_CHECK(exclusive_scan(tmp, hflag, hpre, n_dofs, &n_halo), "halo scan");
+                         lflag, lpre, t_row_base, t_row_gmask, t_row_bmask, hs);
+    int64_t n_side = 0, n_end = 0, n_in = 0;
+    DS_CHECK(exclusive_scan(tmp, hs.side, hs.side, n_ends + 1, &n_side), "halo scan");
+    DS_CHECK(exclusive_scan(tmp, hs.end, hs.end, n_dofs + 1, &n_end), "halo scan");
+    DS_CHECK(exclusive_scan(tmp, hs.in, hs.in, n_dofs + 1, &n_in), "halo scan");
+    hs.n_side = (int32_t)n_side;
+    n_halo = n_side + n_end + n_in;
     c->n_halo_dofs = n_halo;
     cv.add(c->d_halo_dof, n_halo);
     cv.add(c->d_halo_mask, n_halo);
@@ -709,17 +764,16 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     DS_CHECK(tmp.err, "allocation");
     DS_CHECK(hipMemsetAsync(hmask32, 0, sizeof(uint32_t) * std::max<int64_t>(1, n_halo), s), "memset");
     DS_CHECK(hipMemsetAsync(slots, 0, sizeof(unsigned long long), s), "memset");
-    if (n_dofs > 0)
-      hipLaunchKernelGGL(halo_dof_kernel, dim3(grid_for(n_dofs)), dim3(kT), 0, s, n_dofs, hflag, hpre, c->d_halo_dof);
     if (nrow_all > 0)
-      hipLaunchKernelGGL(halo_rows_kernel, dim3(grid_for(nrow_all)), dim3(kT), 0, s, g, bk, nbk, c->d_row_base,
-                         c->d_row_gmask, c->d_row_bmask, hflag, hpre, c->d_row_hbase, hmask32, slots, bad);
+      hipLaunchKernelGGL(halo_rows_kernel, dim3(grid_for(nrow_all)), dim3(kT), 0, s, g, bk, lt, nbk, n_dofs, d_key_of,
+                         lpre, c->d_row_base, c->d_row_gmask, c->d_row_bmask, hs, c->d_row_hbase, c->d_row_hend,
+                         c->d_halo_dof, hmask32, slots, bad);
     if (n_halo > 0)
       hipLaunchKernelGGL(to_u8_kernel, dim3(grid_for(n_halo)), dim3(kT), 0, s, n_halo, hmask32, c->d_halo_mask);
-    unsigned long long hs = 0;
-    DS_CHECK(hipMemcpyAsync(&hs, slots, sizeof(hs), hipMemcpyDeviceToHost, s), "download");
+    unsigned long long n_slots = 0;
+    DS_CHECK(hipMemcpyAsync(&n_slots, slots, sizeof(n_slots), hipMemcpyDeviceToHost, s), "download");
     DS_CHECK(hipStreamSynchronize(s), "synchronise");
-    c->n_halo_slots = (int64_t)hs;
+    c->n_halo_slots = (int64_t)n_slots;
   } else {
     if (ne > 0) DS_CHECK(hipMemcpyAsync(c->d_nbr, nbr_t, sizeof(int32_t) * ne, hipMemcpyDeviceToDevice, s), "copy");
     if (nf > 0) {
