@@ -369,6 +369,12 @@ __global__ void rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, const int
   }
 }
 
+__global__ void halo_totals_kernel(HaloScan hs, int64_t n_ends, int64_t n_dofs, int32_t *out) {
+  out[0] = hs.side[n_ends];
+  out[1] = hs.end[n_dofs];
+  out[2] = hs.in[n_dofs];
+}
+
 __global__ void halo_rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, int64_t n_dofs, const int64_t *key_of,
                                  const int32_t *lpre, const int32_t *row_base, const uint32_t *row_gmask,
                                  const uint32_t *row_bmask, HaloScan hs, int32_t *row_hbase, int32_t *row_hend,
@@ -455,9 +461,10 @@ struct Temps {
   }
 };
 
-// exclusive prefix sum of n int32 (in place allowed); returns the total through *total (host)
+// exclusive prefix sum of n int32 (in place allowed); returns the total through *total (host), unless
+// that is null: then nothing is waited for
 hipError_t exclusive_scan(Temps &tmp, const int32_t *in, int32_t *out, int64_t n, int64_t *total) {
-  *total = 0;
+  if (total) *total = 0;
   if (n == 0) return hipSuccess;
   size_t bytes = 0;
   hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, (int)n, tmp.s);
@@ -465,9 +472,11 @@ hipError_t exclusive_scan(Temps &tmp, const int32_t *in, int32_t *out, int64_t n
   void *ws = tmp.get<char>((int64_t)bytes);
   if (!ws) return tmp.err;
   int32_t last_in = 0, last_out = 0;
-  e = hipMemcpyAsync(&last_in, in + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);  // before out replaces it
+  if (total)  // before out replaces it
+    e = hipMemcpyAsync(&last_in, in + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);
   if (e != hipSuccess) return e;
   e = hipcub::DeviceScan::ExclusiveSum(ws, bytes, in, out, (int)n, tmp.s);
+  if (!total) return e;
   if (e == hipSuccess) e = hipMemcpyAsync(&last_out, out + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);
   if (e == hipSuccess) e = hipStreamSynchronize(tmp.s);
   *total = (int64_t)last_in + last_out;
@@ -675,13 +684,12 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     if (nbk)
       DS_CHECK(hipMemcpyAsync(d_key_of, key_of.data(), sizeof(int64_t) * nbk, hipMemcpyHostToDevice, s), "upload");
     n_ends = (bk.nbx + 1) * (lt.ly / (bk.LY - 1) + 1) * (bk.LY - 1) * lt.lz;
-    hs.side = tmp.get<int32_t>(n_ends + 1);
-    hs.end = tmp.get<int32_t>(n_dofs + 1);
-    hs.in = tmp.get<int32_t>(n_dofs + 1);
+    const int64_t n_scan = n_ends + 2 * n_dofs + 3;
+    hs.side = tmp.get<int32_t>(n_scan);
     DS_CHECK(tmp.err, "allocation");
-    DS_CHECK(hipMemsetAsync(hs.side, 0, sizeof(int32_t) * (n_ends + 1), s), "memset");
-    DS_CHECK(hipMemsetAsync(hs.end, 0, sizeof(int32_t) * (n_dofs + 1), s), "memset");
-    DS_CHECK(hipMemsetAsync(hs.in, 0, sizeof(int32_t) * (n_dofs + 1), s), "memset");
+    hs.end = hs.side + n_ends + 1;
+    hs.in = hs.end + n_dofs + 1;
+    DS_CHECK(hipMemsetAsync(hs.side, 0, sizeof(int32_t) * n_scan, s), "memset");
   }
 
   // ---- the arena: the arrays the kernels and the host build upload, same order ----
@@ -720,12 +728,16 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     if (nrow_all > 0)
       hipLaunchKernelGGL(rows_kernel, dim3(grid_for(nrow_all)), dim3(kT), 0, s, g, bk, lt, nbk, d_key_of, rank_grid,
                          lflag, lpre, t_row_base, t_row_gmask, t_row_bmask, hs);
-    int64_t n_side = 0, n_end = 0, n_in = 0;
-    DS_CHECK(exclusive_scan(tmp, hs.side, hs.side, n_ends + 1, &n_side), "halo scan");
-    DS_CHECK(exclusive_scan(tmp, hs.end, hs.end, n_dofs + 1, &n_end), "halo scan");
-    DS_CHECK(exclusive_scan(tmp, hs.in, hs.in, n_dofs + 1, &n_in), "halo scan");
-    hs.n_side = (int32_t)n_side;
-    n_halo = n_side + n_end + n_in;
+    DS_CHECK(exclusive_scan(tmp, hs.side, hs.side, n_ends + 1, nullptr), "halo scan");
+    DS_CHECK(exclusive_scan(tmp, hs.end, hs.end, n_dofs + 1, nullptr), "halo scan");
+    DS_CHECK(exclusive_scan(tmp, hs.in, hs.in, n_dofs + 1, nullptr), "halo scan");
+    int32_t *last = tmp.get<int32_t>(3), totals[3] = {0, 0, 0};
+    DS_CHECK(tmp.err, "allocation");
+    hipLaunchKernelGGL(halo_totals_kernel, dim3(1), dim3(1), 0, s, hs, n_ends, n_dofs, last);
+    DS_CHECK(hipMemcpyAsync(totals, last, sizeof(totals), hipMemcpyDeviceToHost, s), "download");
+    DS_CHECK(hipStreamSynchronize(s), "synchronise");
+    hs.n_side = totals[0];
+    n_halo = (int64_t)totals[0] + totals[1] + totals[2];
     c->n_halo_dofs = n_halo;
     cv.add(c->d_halo_dof, n_halo);
     cv.add(c->d_halo_mask, n_halo);
