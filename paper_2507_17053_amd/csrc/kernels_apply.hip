@@ -1471,10 +1471,14 @@ __global__ __launch_bounds__(256) void halo_reduce_kernel(int n, const int32_t *
 // CG surrogate-boundary faces (Alg. 3), EPB faces per workgroup, faces in brick order.
 // Output per face: Rv and Rg at its NP face nodes (fbuf[f][0][t], fbuf[f][1][t]);
 // brick_kernel expands them into the (p+1)^d local rows (face_row).
-// Two thread layouts: "node" (le = tid / NP, t = tid % NP: one face node or Gauss point
-// each) for the sum-factorised face sweeps, and "pair" (HP = ceil(NP / 2) threads per face,
-// Gauss points 2k and 2k + 1 each) for the point evaluation E u, which reads the cell's
-// (p+1)^d values once for both points.
+// Thread t of a face is face node t, then face Gauss point t.  With dn = (2s-1)/h d/dxi_a on the face
+// and N the GLL -> Gauss matrix, the dn u term, N^T W N per tangential axis, is the 1D mass matrix M per
+// axis on the nodes' normal derivatives: it needs no Gauss points and is swept together with
+// N^T (W E u), two sweeps in all.
+// What bounds it: the latency of that chain; a face's 5 kB and 10 kFLOP at 3D p=4 are small against it.
+// With half of the threads for E u, two points each, and dn u taken to the Gauss points and back (four
+// sweeps), apply in us: 64^3 Q4 FP64 59.8 -> 57.7, 128^3 Q4 346 -> 338, 96^3 Q3 84.3 -> 80.6, 40^3 Q5
+// 43.3 -> 41.5, 20^3 Q8 46.1 -> 39.1; FP32 64^3 Q4 40.3 -> 40.2.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int N1, int EPB>
 __device__ __forceinline__ void sbm_face_cg_body(const int blk, int n_faces, const int32_t *__restrict__ face_code,
@@ -1482,153 +1486,103 @@ __device__ __forceinline__ void sbm_face_cg_body(const int blk, int n_faces, con
                                                           const double *__restrict__ face_xi,
                                                           const T *__restrict__ u, T *__restrict__ fbuf,
                                                           KTab<T, N1> tab, KScal sc) {
-  constexpr int NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB, HP = (NP + 1) / 2;
+  constexpr int NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB;
   __shared__ T su_all[EPB * NB];
-  __shared__ T fw_all[6 * EPB * NP];  // per face: g, sweep, E u, integrands v / dn v, scratch
-  const int tid = threadIdx.x;
-  const int f0 = blk * EPB;
-  // node layout
-  const int le = tid / NP, t = tid - le * NP;
-  const int f = f0 + le;
-  const bool act = le < EPB && f < n_faces;
-  T *su = su_all + (le < EPB ? le : 0) * NB;
-  T *fw = fw_all + (le < EPB ? le : 0) * 6 * NP;
-  T *fg = fw, *fs = fw + NP, *fe = fw + 2 * NP, *f5 = fw + 3 * NP, *f6 = fw + 4 * NP, *fx = fw + 5 * NP;
-  // pair layout
-  const int pf = tid / HP, pk = tid - pf * HP;
-  const int q0 = 2 * pk, q1 = 2 * pk + 1;
-  const bool pact = pf < EPB && f0 + pf < n_faces;
-  const bool has1 = pact && q1 < NP;
-  // loads first: face code, the cell's u (one x-run per node thread), the pair's points
+  __shared__ T fw_all[4 * EPB * NP];  // per face: W E u, normal derivative, and both after the first sweep
+  __shared__ T sN[N1 * N1], sM[N1 * N1];
+  const int tid = threadIdx.x, le = tid / NP, t = tid - le * NP;
+  const int f = blk * EPB + le;
+  const bool act = f < n_faces;  // (the launch has EPB NP threads)
+  T *su = su_all + le * NB, *fe = fw_all + le * 4 * NP, *fg = fe + NP, *re = fe + 2 * NP, *rg = fe + 3 * NP;
+  // loads first: face code, the point, the cell's u (one x-run per thread)
   const int code = act ? face_code[f] : 0;
-  if (act) {
-    const int64_t base = face_runs[(int64_t)f * NP + t];
+  double xp[D];
 #pragma unroll
-    for (int i = 0; i < N1; ++i) su[N1 * t + i] = u[base + i];
+  for (int k = 0; k < D; ++k) xp[k] = act ? face_xi[((int64_t)f * NP + t) * D + k] : 0.0;
+  {
+    const int64_t base = act ? face_runs[(int64_t)f * NP + t] : 0;
+#pragma unroll
+    for (int i = 0; i < N1; ++i) su[N1 * t + i] = act ? u[base + i] : T(0);
   }
-  double xa[D], xb[D];
+  for (int i = tid; i < N1 * N1; i += EPB * NP) {
+    sN[i] = tab.N[i];
+    sM[i] = tab.M[i];
+  }
+  T l[D][N1];
 #pragma unroll
   for (int k = 0; k < D; ++k) {
-    xa[k] = pact ? face_xi[((int64_t)(f0 + pf) * NP + q0) * D + k] : 0.0;
-    xb[k] = has1 ? face_xi[((int64_t)(f0 + pf) * NP + q1) * D + k] : 0.0;
+    double lk[N1];
+    lagrange_at<N1>(tab.z, tab.cinv, xp[k], lk);
+#pragma unroll
+    for (int j = 0; j < N1; ++j) l[k][j] = T(lk[j]);
   }
   __syncthreads();
   const FaceAxes<D, N1> fa(code);
   const int jb = (D == 3) ? t % N1 : t, jc = (D == 3) ? t / N1 : 0;
-  // normal derivative (reference, times the outward sign / h below) at face node t
+  const T h = T(sc.h), sig = T(sc.sigma_gamma), sh = (fa.s ? T(1) : T(-1)) / h;
   {
     T g = 0;
     const int node_off = jb * fa.Sb + jc * fa.Sc;
 #pragma unroll
     for (int ia = 0; ia < N1; ++ia) g += (fa.s ? tab.D1[ia] : tab.D0[ia]) * su[ia * fa.Sa + node_off];
-    if (le < EPB) fg[t] = g;
+    fg[t] = g;
   }
-  // E u at the pair's two shifted points
-  if (pact) {
-    const T *sp = su_all + pf * NB;
-    double la[D][N1], lb[D][N1];
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      lagrange_at<N1>(tab.z, tab.cinv, xa[k], la[k]);
-      lagrange_at<N1>(tab.z, tab.cinv, xb[k], lb[k]);
-    }
-    T a0[N1], a1[N1], b0[N1], b1[N1];
-#pragma unroll
-    for (int j = 0; j < N1; ++j) {
-      a0[j] = T(la[0][j]);
-      a1[j] = T(la[1][j]);
-      b0[j] = T(lb[0][j]);
-      b1[j] = T(lb[1][j]);
-    }
-    T ea = 0, eb = 0;
+  {
+    T e = 0;
     if constexpr (D == 3) {
-      T a2[N1], b2[N1];
 #pragma unroll
-      for (int j = 0; j < N1; ++j) {
-        a2[j] = T(la[2][j]);
-        b2[j] = T(lb[2][j]);
-      }
-      // one (p+1)^2 slab per iteration, so that at most one slab of loads is in flight
-#pragma unroll 1
       for (int i2 = 0; i2 < N1; ++i2) {
-        const T *sl = sp + NP * i2;
-        T ra = 0, rb = 0;
+        T r = 0;
 #pragma unroll
         for (int i1 = 0; i1 < N1; ++i1) {
-          T sa = 0, sb = 0;
+          T q = 0;
 #pragma unroll
-          for (int i0 = 0; i0 < N1; ++i0) {
-            const T w = sl[i0 + N1 * i1];
-            sa += a0[i0] * w;
-            sb += b0[i0] * w;
-          }
-          ra += a1[i1] * sa;
-          rb += b1[i1] * sb;
+          for (int i0 = 0; i0 < N1; ++i0) q += l[0][i0] * su[i0 + N1 * i1 + NP * i2];
+          r += l[1][i1] * q;
         }
-        T wa = 0, wb = 0;
+        T l2 = 0;
 #pragma unroll
-        for (int j = 0; j < N1; ++j) {
-          wa = (j == i2) ? a2[j] : wa;
-          wb = (j == i2) ? b2[j] : wb;
-        }
-        ea += wa * ra;
-        eb += wb * rb;
+        for (int j = 0; j < N1; ++j) l2 = (j == i2) ? l[2][j] : l2;
+        e += l2 * r;
       }
     } else {
 #pragma unroll
       for (int i1 = 0; i1 < N1; ++i1) {
-        T sa = 0, sb = 0;
+        T q = 0;
 #pragma unroll
-        for (int i0 = 0; i0 < N1; ++i0) {
-          const T w = sp[i0 + N1 * i1];
-          sa += a0[i0] * w;
-          sb += b0[i0] * w;
-        }
-        ea += a1[i1] * sa;
-        eb += b1[i1] * sb;
+        for (int i0 = 0; i0 < N1; ++i0) q += l[0][i0] * su[i0 + N1 * i1];
+        e += l[1][i1] * q;
       }
     }
-    T *pe = fw_all + pf * 6 * NP + 2 * NP;
-    pe[q0] = ea;
-    if (has1) pe[q1] = eb;
+    fe[t] = ((D == 3) ? h * h * tab.w[t % N1] * tab.w[t / N1] : h * tab.w[t]) * e;
   }
   __syncthreads();
-  // GLL -> Gauss interpolation of the normal derivative on the face
-  T dn;
+  T ae = 0, ag = 0;
   if constexpr (D == 3) {
-    const int qb = t % N1;
-    T r = 0;
+    T r1 = 0, r2 = 0;
 #pragma unroll
-    for (int j = 0; j < N1; ++j) r += tab.N[qb * N1 + j] * fg[j + N1 * jc];
-    if (le < EPB) fs[t] = r;  // (qb, jc)
+    for (int k = 0; k < N1; ++k) {
+      r1 += sN[k * N1 + jc] * fe[jb + N1 * k];
+      r2 += sM[k * N1 + jc] * fg[jb + N1 * k];
+    }
+    re[t] = r1;
+    rg[t] = r2;
     __syncthreads();
-    const int qc = t / N1;
-    dn = 0;
 #pragma unroll
-    for (int j = 0; j < N1; ++j) dn += tab.N[qc * N1 + j] * fs[qb + N1 * j];
+    for (int k = 0; k < N1; ++k) {
+      ae += sN[k * N1 + jb] * re[k + N1 * jc];
+      ag += sM[k * N1 + jb] * rg[k + N1 * jc];
+    }
   } else {
-    dn = 0;
 #pragma unroll
-    for (int j = 0; j < N1; ++j) dn += tab.N[t * N1 + j] * fg[j];
-  }
-  // integrands at Gauss point t
-  {
-    const T h = T(sc.h), sig = T(sc.sigma_gamma);
-    const T sh = (fa.s ? T(1) : T(-1)) / h;
-    const T om = act ? ((D == 3) ? h * h * tab.w[t % N1] * tab.w[t / N1] : h * tab.w[t]) : T(0);
-    const T eu = fe[t];
-    dn *= sh;
-    if (le < EPB) {
-      f5[t] = om * (sig * eu - dn);  // tested against v
-      f6[t] = -om * eu * sh;         // tested against the reference derivative along a
+    for (int k = 0; k < N1; ++k) {
+      ae += sN[k * N1 + t] * fe[k];
+      ag += sM[k * N1 + t] * fg[k];
     }
   }
-  __syncthreads();
-  T Rv, Rg;
-  face_integrate<T, D, N1>(tab, t, fg, fx, f5, f6, Rv, Rg);
   if (act) {
-    fbuf[(int64_t)f * 2 * NP + t] = Rv;
-    fbuf[(int64_t)f * 2 * NP + NP + t] = Rg;
+    fbuf[(int64_t)f * 2 * NP + t] = sig * ae - ((D == 3) ? h * h : h) * sh * ag;  // tested against v
+    fbuf[(int64_t)f * 2 * NP + NP + t] = -sh * ae;  // tested against the reference derivative along a
   }
 }
 
@@ -2030,8 +1984,8 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
       T *halo = (T *)scr.halo;
       T *fbuf = (T *)scr.fbuf;
       if (nf > 0 && (parts & SBM_PART_SBM_FACES) && !(parts & SBM_PART_REUSE_FACES)) {
-        // (the one-thread-per-(point, slab) layout of the DG faces measured 21.7 against
-        // 11.6 us here at 3D p = 4: the pair layout reads each cell value once for two points)
+        // (the one-thread-per-(point, slab) layout of the DG faces measured 21.7 against 11.6 us here
+        // at 3D p = 4)
         constexpr int EF = epb<T, D, N1, 2, 0>();
         hipLaunchKernelGGL((sbm_face_cg_kernel<T, D, N1, EF>), dim3((nf + EF - 1) / EF), dim3(EF * NP), 0, s, nf,
                            c->d_face_code, c->d_face_runs, c->d_face_xi, u, fbuf, tab, sc);
