@@ -112,7 +112,7 @@ constexpr int taylor_slabs() {
 // fbuf (fbuf[f][0][t], fbuf[f][1][t]); the cell kernels add the face's rows (Rv on the face's
 // own nodes plus Rg times the normal derivative of the row's 1D function) in a fixed order, as
 // for the full extension.  FP64 inside; the 1D tables are staged in LDS.  JN: Taylor orders
-// carried per axis (p+1, or 2 for a launch with m <= 1).
+// carried per axis (p+1; launches with m <= 2 take sbm_face_taylor_low_kernel).
 template <typename T, int D, int N1, int JN>
 __global__ __launch_bounds__(kTaylorThreads) void sbm_face_taylor_kernel(
     int n_faces, int disc_dg, int m, const int32_t *__restrict__ face_cell, const int32_t *__restrict__ face_code,

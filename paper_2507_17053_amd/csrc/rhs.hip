@@ -14,8 +14,8 @@
 //
 // What bounds it: the copy of f from the caller's memory (8 (p+1)^d bytes per cell, 28 GB/s from
 // ordinary host memory); the kernels take a few microseconds each.  The same sums on 16 host
-// threads took TIMES.  f goes to the device in chunks of at most 64 MB, so that the scratch stays
-// small beside the operator at any size.
+// threads took 2.76 ms for 40^3 Q4, 0.36 ms here.  f goes to the device in chunks of at most 64 MB,
+// so that the scratch stays small beside the operator at any size.
 #include <algorithm>
 
 #include "sbm_internal.h"

@@ -288,6 +288,11 @@ __device__ __forceinline__ double wave_sum(const double *__restrict__ p, int nbl
   return s;
 }
 
+// Row groups of 64 per block and step of the Gram-Schmidt kernels, one value per class of columns per
+// wave (1 and 2, 3 and 4, 5 to 8, 9 to 16): a run's sums are the same with any CPW of the class.
+constexpr int gs_class(int cpw) { return cpw > 8 ? 3 : (cpw > 4 ? 2 : (cpw > 2 ? 1 : 0)); }
+constexpr int gs_rows(int cpw) { return 16 >> gs_class(cpw); }
+
 // One Gram-Schmidt kernel of a GMRES step, in a single launch:
 //   MODE 0: out = V^T w                                  (ncol columns of V)
 //   MODE 1: w -= V coef, then out = V^T w
@@ -301,12 +306,18 @@ __device__ __forceinline__ double wave_sum(const double *__restrict__ p, int nbl
 // block b at partial[i kMaxBlocks + b]); the last block to finish (ticket on *counter, which it
 // resets to 0 for the next launch) adds them in a fixed order, so the result is independent of
 // the block schedule.
+// What bounds it: the reading of V, 3.4 M rows of 24 columns FP64 at 3.7 TB/s and of 50 at 4.5 (a plain
+// read reaches 6.0).  Every load of a step is pinned ahead of its first use: without that the compiler
+// held 40 registers and had about ten of the 32 loads under way.  A single run's launch has as many
+// columns per wave as it needs, where 2, 4, 8 or 16 left up to half of the slots to masked loads.  50
+// steps on 3.4 M rows: FP64 35.0 -> 32.1 ms, FP32 refinement 22.8 -> 20.5 ms; on 0.4 M rows 8.2 -> 8.0
+// and 7.3 -> 6.95 ms.
 template <typename T, int CPW, int MODE, bool TICKET = true>
 __device__ __forceinline__ void gs_body(const int blk, const int nblk, const T *__restrict__ V, int m1, int ncol,
                                         const double *__restrict__ coef, T *__restrict__ w, int64_t n,
                                         double *__restrict__ partial, unsigned *__restrict__ counter,
                                         double *__restrict__ out, const ArnoldiArgs &aa) {
-  constexpr int NW = kThreads / 64, R = 32 / CPW;
+  constexpr int NW = kThreads / 64, R = gs_rows(CPW);
   __shared__ double red[MODE == 0 ? 1 : NW][64 * R];
   __shared__ bool last;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -332,6 +343,12 @@ __device__ __forceinline__ void gs_body(const int blk, const int nblk, const T *
         tv[rr][c] = V[(ok && i < ncol) ? base + (int64_t)i * kTile : 0];
       }
       tw[rr] = w[ok ? k : 0];
+    }
+#pragma unroll
+    for (int rr = 0; rr < R; ++rr) {
+#pragma unroll
+      for (int c = 0; c < CPW; ++c) asm volatile("" : "+v"(tv[rr][c]));
+      asm volatile("" : "+v"(tw[rr]));
     }
     double v[R][CPW], wv[R];
 #pragma unroll
@@ -862,25 +879,32 @@ static void gs_grid_caps(int (*g)[3]) {
 template <typename T, int CPW, int MODE>
 static void gs_launch1(const Workspace *ws, const T *V, int m1, int ncol, const double *coef, T *w, int64_t n,
                        double *partial, unsigned *ticket, double *out, const ArnoldiArgs &aa, hipStream_t s) {
-  constexpr int L = CPW == 2 ? 0 : (CPW == 4 ? 1 : (CPW == 8 ? 2 : 3));
-  const int64_t rows = 64 * (32 / CPW);  // rows per block and step
+  constexpr int L = gs_class(CPW);
+  const int64_t rows = 64 * gs_rows(CPW);  // rows per block and step
   const int cap = ws->gs_grid[sizeof(T) == 4 ? 1 : 0][L][MODE];
   const int nb = (int)std::max<int64_t>(1, std::min<int64_t>((n + rows - 1) / rows, cap));
   hipLaunchKernelGGL((gs_kernel<T, CPW, MODE>), dim3(nb), dim3(kThreads), 0, s, V, m1, ncol, coef, w, n, partial,
                      ticket, out, aa);
 }
 
+// the kernel with just the columns per wave that ncol <= 64 columns take
+template <typename T, int MODE, int CPW = 1>
+static void gs_launch_cols(const Workspace *ws, const T *V, int m1, int ncol, const double *coef, T *w, int64_t n,
+                           double *partial, unsigned *ticket, double *out, const ArnoldiArgs &aa, hipStream_t s) {
+  if constexpr (CPW < 16) {
+    if (ncol > 4 * CPW) {
+      gs_launch_cols<T, MODE, CPW + 1>(ws, V, m1, ncol, coef, w, n, partial, ticket, out, aa, s);
+      return;
+    }
+  }
+  gs_launch1<T, CPW, MODE>(ws, V, m1, ncol, coef, w, n, partial, ticket, out, aa, s);
+}
+
 template <typename T, int MODE>
 static void gs_launch(const Workspace *ws, const T *V, int m1, int ncol, const double *coef, T *w, int64_t n,
                       double *partial, unsigned *ticket, double *out, const ArnoldiArgs &aa, hipStream_t s) {
-  if (ncol <= 8)
-    gs_launch1<T, 2, MODE>(ws, V, m1, ncol, coef, w, n, partial, ticket, out, aa, s);
-  else if (ncol <= 16)
-    gs_launch1<T, 4, MODE>(ws, V, m1, ncol, coef, w, n, partial, ticket, out, aa, s);
-  else if (ncol <= 32)
-    gs_launch1<T, 8, MODE>(ws, V, m1, ncol, coef, w, n, partial, ticket, out, aa, s);
-  else if (ncol <= 64)
-    gs_launch1<T, 16, MODE>(ws, V, m1, ncol, coef, w, n, partial, ticket, out, aa, s);
+  if (ncol <= 64)
+    gs_launch_cols<T, MODE>(ws, V, m1, ncol, coef, w, n, partial, ticket, out, aa, s);
   else {
     const int64_t rows = 128;  // rows per block and step of gs_wide_kernel
     const int cap = ws->gs_grid[sizeof(T) == 4 ? 1 : 0][4][MODE];
@@ -1393,7 +1417,7 @@ struct OrthoPlan {
         int nb;
         if (kind < kOrthoKinds - 1) {
           const int L = kind / 3, mode = kind % 3;
-          const int64_t rows = 64 * (32 / (2 << L));  // as gs_launch1
+          const int64_t rows = 64 * gs_rows(2 << L);  // as gs_launch1
           nb = (int)std::max<int64_t>(1, std::min<int64_t>((n + rows - 1) / rows, caps[L][mode]));
         } else {
           nb = nblocks(n);
