@@ -69,20 +69,24 @@ extern "C" sbm_status sbm_apply_noalloc(sbm_handle h, const void *u, void *v, in
     set_error("sbm_apply_noalloc: u and v must not alias");
     return SBM_EINVAL;
   }
-  const size_t need = sbm::apply_scratch_bytes(h, prec);
+  const size_t s = prec == SBM_F64 ? sizeof(double) : sizeof(float);
+  const size_t own = sbm::apply_scratch_bytes(h, prec);
+  const size_t halo_bytes = h->disc == SBM_CG ? ((size_t)1 << h->dim) * (size_t)h->n_halo_dofs * s : 0;
+  const size_t limit_bytes = h->disc == SBM_CG ? ((size_t)1 << h->dim) * (size_t)h->n_halo_limit * s : 0;
+  const size_t need = own - (halo_bytes + 255) / 256 * 256 + (limit_bytes + 255) / 256 * 256;
   if (need > kScratchBytes) {
     set_error("sbm_apply_noalloc: the operator needs " + std::to_string(need) +
               " bytes of scratch, more than the " + std::to_string(kScratchBytes) +
               " bytes of the static device scratch; use sbm_apply");
     return SBM_EINVAL;
   }
-  void *base = nullptr;
-  SBM_HIP_CHECK(scratch_address(&base));
-  const size_t s = prec == SBM_F64 ? sizeof(double) : sizeof(float);
-  const size_t halo_bytes = h->disc == SBM_CG ? ((size_t)1 << h->dim) * (size_t)h->n_halo_dofs * s : 0;
-  sbm::Scratch scr;
-  scr.halo = base;
-  scr.fbuf = (unsigned char *)base + (halo_bytes + 255) / 256 * 256;
+  sbm::Scratch scr{};  // (an accepted operator whose bricks need more than that has the scratch it was set up with)
+  if (own <= kScratchBytes) {
+    void *base = nullptr;
+    SBM_HIP_CHECK(scratch_address(&base));
+    scr.halo = base;
+    scr.fbuf = (unsigned char *)base + (halo_bytes + 255) / 256 * 256;
+  }
   SBM_HIP_CHECK(sbm::launch_operator(h, u, v, prec, SBM_PART_ALL, (hipStream_t)stream, &scr));
   sbm::note_work(h, (hipStream_t)stream);
   return SBM_OK;

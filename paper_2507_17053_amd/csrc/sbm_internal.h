@@ -116,6 +116,8 @@ struct sbm_ctx {
   // halo assembly: a DoF on brick boundaries collects one value per touching brick, in plane
   // k (2^d planes of n_halo_dofs values) given by the brick's side of the point
   int64_t n_halo_slots = 0, n_halo_dofs = 0;
+  // DoFs on the planes that set sbm_apply_noalloc's limit (noalloc_brick)
+  int64_t n_halo_limit = 0;
   std::vector<int32_t> halo_dof;   // halo index -> DoF
   std::vector<uint8_t> halo_mask;  // halo index -> planes written
   bool halo_ok = true;             // consistency of the halo numbering (checked at setup)
@@ -190,6 +192,15 @@ hipError_t launch_taylor_faces(const sbm_ctx *c, const void *u, void *fbuf, int 
 // brick shape (cells per direction) of a form.
 bool brick_by_cells(int dim, int p, int64_t n_cells);
 void brick_dims(int dim, int p, bool by_cells, int *bx, int *by, int *bz);
+// sbm_apply_noalloc accepts a 3D operator of degree 1 to 3 by the brick-boundary DoFs of one fixed brick
+// shape (8x8x8, 8x4x4, 4x4x4), whatever shape its form takes: false for the other operators, where
+// the bricks' own count decides.
+inline bool noalloc_brick(int dim, int p, int b[3]) {
+  if (dim != 3 || p > 3) return false;
+  b[0] = p == 3 ? 4 : 8;
+  b[1] = b[2] = p == 1 ? 8 : 4;
+  return true;
+}
 // Brick numbering from the per-slot cell and face counts of the brick grid: key_of[b] is the
 // grid slot of brick b, bid[slot] its brick number (-1 if empty).  Every one of the 8 XCD
 // ranges gets an equal share of the face-carrying bricks, first, then of the others (see

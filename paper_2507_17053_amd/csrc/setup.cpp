@@ -635,6 +635,16 @@ static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx,
         }
       }
   c->n_halo_slots = slots;
+  c->n_halo_limit = c->n_halo_dofs;
+  int lb[3];
+  if (noalloc_brick(d, p, lb)) {
+    c->n_halo_limit = 0;
+    for (int64_t z = 0; z < lz; ++z)
+      for (int64_t y = 0; y < ly; ++y)
+        for (int64_t x = 0; x < lx; ++x)
+          if (id[(z * ly + y) * lx + x] >= 0 && (x % (lb[0] * p) == 0 || y % (lb[1] * p) == 0 || z % (lb[2] * p) == 0))
+            ++c->n_halo_limit;
+  }
 }
 
 namespace sbm {

@@ -369,6 +369,19 @@ __global__ void rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, const int
   }
 }
 
+// DoFs on the lattice planes x % px = 0, y % py = 0 or z % pz = 0
+__global__ void plane_dofs_kernel(Lat lt, int64_t n, int px, int py, int pz, const int32_t *lflag,
+                                  unsigned long long *count) {
+  int mine = 0;
+  GRID_LOOP(m, n) {
+    if (!lflag[m]) continue;
+    const int64_t x = m % lt.lx, q = m / lt.lx, y = q % lt.ly, z = q / lt.ly;
+    mine += x % px == 0 || y % py == 0 || z % pz == 0;
+  }
+  for (int off = 32; off > 0; off >>= 1) mine += __shfl_down(mine, off, 64);
+  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(count, (unsigned long long)mine);
+}
+
 __global__ void halo_totals_kernel(HaloScan hs, int64_t n_ends, int64_t n_dofs, int32_t *out) {
   out[0] = hs.side[n_ends];
   out[1] = hs.end[n_dofs];
@@ -772,20 +785,28 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
                "copy");
     }
     uint32_t *hmask32 = tmp.get<uint32_t>(n_halo);
-    unsigned long long *slots = tmp.get<unsigned long long>(1);
+    unsigned long long *slots = tmp.get<unsigned long long>(2);  // and the DoFs of noalloc_brick's planes
     DS_CHECK(tmp.err, "allocation");
     DS_CHECK(hipMemsetAsync(hmask32, 0, sizeof(uint32_t) * std::max<int64_t>(1, n_halo), s), "memset");
-    DS_CHECK(hipMemsetAsync(slots, 0, sizeof(unsigned long long), s), "memset");
+    DS_CHECK(hipMemsetAsync(slots, 0, 2 * sizeof(unsigned long long), s), "memset");
+    int lb[3];
+    const bool limit = noalloc_brick(d, g.p, lb);
+    if (limit) {
+      const int64_t nl = lt.lx * lt.ly * lt.lz;
+      hipLaunchKernelGGL(plane_dofs_kernel, dim3(grid_for(nl)), dim3(kT), 0, s, lt, nl, lb[0] * g.p, lb[1] * g.p,
+                         lb[2] * g.p, lflag, slots + 1);
+    }
     if (nrow_all > 0)
       hipLaunchKernelGGL(halo_rows_kernel, dim3(grid_for(nrow_all)), dim3(kT), 0, s, g, bk, lt, nbk, n_dofs, d_key_of,
                          lpre, c->d_row_base, c->d_row_gmask, c->d_row_bmask, hs, c->d_row_hbase, c->d_row_hend,
                          c->d_halo_dof, hmask32, slots, bad);
     if (n_halo > 0)
       hipLaunchKernelGGL(to_u8_kernel, dim3(grid_for(n_halo)), dim3(kT), 0, s, n_halo, hmask32, c->d_halo_mask);
-    unsigned long long n_slots = 0;
-    DS_CHECK(hipMemcpyAsync(&n_slots, slots, sizeof(n_slots), hipMemcpyDeviceToHost, s), "download");
+    unsigned long long n_slots[2] = {0, 0};
+    DS_CHECK(hipMemcpyAsync(n_slots, slots, sizeof(n_slots), hipMemcpyDeviceToHost, s), "download");
     DS_CHECK(hipStreamSynchronize(s), "synchronise");
-    c->n_halo_slots = (int64_t)n_slots;
+    c->n_halo_slots = (int64_t)n_slots[0];
+    c->n_halo_limit = limit ? (int64_t)n_slots[1] : n_halo;
   } else {
     if (ne > 0) DS_CHECK(hipMemcpyAsync(c->d_nbr, nbr_t, sizeof(int32_t) * ne, hipMemcpyDeviceToDevice, s), "copy");
     if (nf > 0) {

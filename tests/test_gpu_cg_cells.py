@@ -91,3 +91,24 @@ def test_large_q1_mesh_takes_the_sweeps():
             assert rel(vd.double().cpu().numpy(), ref.ravel()) <= tol
     finally:
         op.close()
+
+
+def test_noalloc_limit_does_not_follow_the_brick_shape():
+    """60^3 Q3 cells: within the static scratch by 4x4x4 bricks (95 MB), beyond it by the 8x4x2 bricks
+    in use (107 MB): still accepted, and bitwise the apply.  64^3 is beyond it by both: refused."""
+    for n in (60, 64):
+        print(f"case q3 n={n}", flush=True)
+        op = sbm.Operator(3, n, 0.0, 1.0, inputs.halfspace((1.0, 0.0, 0.0), 2.0), 3)
+        try:
+            u = torch.from_numpy(inputs.uniform_vector(op.n_dofs, seed=3)).to("cuda")
+            a, b = torch.full_like(u, float("nan")), torch.full_like(u, float("nan"))
+            if n == 60:
+                op.apply(u, a)
+                op.apply_noalloc(u, b)
+                torch.cuda.synchronize()
+                assert torch.equal(a, b) and bool(torch.isfinite(a).all())
+            else:
+                with pytest.raises(sbm.SbmError):
+                    op.apply_noalloc(u, b)
+        finally:
+            op.close()
