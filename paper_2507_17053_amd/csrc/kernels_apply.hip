@@ -1417,14 +1417,6 @@ __global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_kernel(
   brick_body<T, D, N1, CELLS>(xcd_block(), br, fbuf, u, v, halo, nhalo, tab, scale, parts);
 }
 
-// (nontemporal in FP64: 128^3 Q4 apply 357 -> 346 us, 64^3 61 -> 58 us, 1024^2 Q3 54 -> 48 us; FP32 64^3
-// Q4 39.5 -> 40.9 us)
-template <typename T>
-__device__ __forceinline__ T load_once(const T *p) {
-  if constexpr (sizeof(T) == 8) return __builtin_nontemporal_load(p);
-  return *p;
-}
-
 // v[dof] = sum over the planes k present in the DoF's mask, in increasing k (deterministic).
 // Two DoFs per thread (a block's 2 * 256 consecutive ones), so that each thread has twice the
 // loads in flight (FP64 apply at 64^3 Q4: 50.2 against 51.2 us; with four 1.5 us slower).
@@ -1434,7 +1426,7 @@ __device__ __forceinline__ T load_once(const T *p) {
 // DoF order, 128^3 Q4 FP64: brick kernel 264 -> 235 us, apply 417 -> 357 us; FP32 152 -> 140 and
 // 231 -> 221 us.  One contiguous range of it per XCD measured slower (128^3 FP64 381 us).
 constexpr int kHaloPerThread = 2;
-template <typename T, int D>
+template <typename T, int D, bool ONCE>
 __device__ __forceinline__ void halo_reduce_body(const int blk, int n, const int32_t *__restrict__ dof,
                                                           const uint8_t *__restrict__ mask,
                                                           const T *__restrict__ halo, T *__restrict__ v) {
@@ -1454,17 +1446,18 @@ __device__ __forceinline__ void halo_reduce_body(const int blk, int n, const int
   for (int k = 0; k < (1 << D); ++k)
 #pragma unroll
     for (int r = 0; r < kHaloPerThread; ++r)
-      s[r] += ((m[r] >> k) & 1u) ? load_once(&halo[(int64_t)k * n + i0 + r * 256]) : T(0);
+      s[r] += ((m[r] >> k) & 1u) ? (ONCE ? __builtin_nontemporal_load(&halo[(int64_t)k * n + i0 + r * 256])
+                                        : halo[(int64_t)k * n + i0 + r * 256]) : T(0);
 #pragma unroll
   for (int r = 0; r < kHaloPerThread; ++r)
     if (i0 + r * 256 < n) v[dd[r]] = s[r];
 }
 
-template <typename T, int D>
+template <typename T, int D, bool ONCE>
 __global__ __launch_bounds__(256) void halo_reduce_kernel(int n, const int32_t *__restrict__ dof,
                                                           const uint8_t *__restrict__ mask,
                                                           const T *__restrict__ halo, T *__restrict__ v) {
-  halo_reduce_body<T, D>(blockIdx.x, n, dof, mask, halo, v);
+  halo_reduce_body<T, D, ONCE>(blockIdx.x, n, dof, mask, halo, v);
 }
 
 // ------------------------------------------------------------------------------------
@@ -2002,8 +1995,17 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
         if (!c->by_cells) bricks(std::false_type{});
       if (nh > 0 && !(parts & SBM_PART_NO_ASSEMBLY)) {
         constexpr int HB = kHaloPerThread * 256;  // DoFs per block
-        hipLaunchKernelGGL((halo_reduce_kernel<T, D>), dim3((nh + HB - 1) / HB), dim3(256), 0, s, nh, c->d_halo_dof,
-                           (const uint8_t *)c->d_halo_mask, (const T *)halo, v);
+        auto reduce = [&](auto once) {
+          hipLaunchKernelGGL((halo_reduce_kernel<T, D, decltype(once)::value>), dim3((nh + HB - 1) / HB), dim3(256), 0,
+                             s, nh, c->d_halo_dof, (const uint8_t *)c->d_halo_mask, (const T *)halo, v);
+        };
+        // nontemporal reads of the planes once an apply's data is several times the 256 MB cache, in FP64:
+        // 128^3 Q4 (8.1 M points) 340 -> 323 us, 112^3 (5.4 M) 220 -> 216 us; on 64^3 (1.0 M) they cost a
+        // solver's repeated applies 47.9 -> 51.5 us, 80^3 (2.0 M) 76 -> 83 us; FP32 64^3 39.5 -> 40.9 us
+        if (sizeof(T) == 8 && nh >= 1 << 22)
+          reduce(std::true_type{});
+        else
+          reduce(std::false_type{});
       }
     }
   } else {
@@ -2082,7 +2084,7 @@ __global__ __launch_bounds__(256) void halo_reduce_batch_kernel(const BatchItem 
                                                                 const int32_t *__restrict__ blk_item) {
   const int g = blockIdx.x;
   const BatchItem *it = items + blk_item[g];
-  halo_reduce_body<T, D>(g - it->blk0[2], it->nh, it->halo_dof, it->halo_mask, (const T *)it->halo, (T *)it->v);
+  halo_reduce_body<T, D, false>(g - it->blk0[2], it->nh, it->halo_dof, it->halo_mask, (const T *)it->halo, (T *)it->v);
 }
 
 template <typename T, int D, int N1, int EPB>
