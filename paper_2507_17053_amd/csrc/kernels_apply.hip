@@ -1002,14 +1002,16 @@ struct BrickRows {
   static_assert(C::LX <= 32, "row masks hold 32 points");
   enum { kLowY = 1, kHighY = 2, kLowZ = 4, kHighZ = 8, kY0 = 16, kZ0 = 32 };
   T *dst[C::NROWS];           // where the points 0 < x < LX-1 go, by their place among the row's DoFs
-  int32_t hend[2 * C::NROWS]; // halo indices of the rows' ends, x = 0 first
   int32_t off[C::NROWS];      // 256 x (place of the row in the results) + flags
   uint32_t gmask[C::NROWS], bmask[C::NROWS];
   int32_t base[C::NROWS];     // by the row's own place y + LY z: id of its first DoF,
   uint32_t first[C::NROWS];   // mask of its DoFs
 
-  // One row per thread (full: all masks are ones).  A barrier has to follow.
-  __device__ __forceinline__ void fill(const BrickArgs &br, int brick, bool full, T *v, T *halo, int nhalo) {
+  // One row per thread (full: all masks are ones).  A barrier has to follow.  The halo indices of the
+  // row's ends stay in the thread's registers for the write-out: in LDS they cost 3D p=2 FP64 one of
+  // three workgroups per CU (150^3 brick kernel 70 -> 83 us).
+  __device__ __forceinline__ void fill(const BrickArgs &br, int brick, bool full, T *v, T *halo, int nhalo,
+                                       int32_t (&ends)[2]) {
     constexpr int BX = C::BX, BY = C::BY, BZ = C::BZ, LX = C::LX, LY = C::LY, LZ = C::LZ, PI = P > 1 ? P - 1 : 1;
     const int r = threadIdx.x;
     if (r >= C::NROWS) return;
@@ -1027,8 +1029,8 @@ struct BrickRows {
     base[own] = b;
     first[own] = gm;
     dst[r] = edge ? halo + (int64_t)plane * nhalo + hb : v + b;
-    hend[r] = br.row_hend[2 * (at - own) + own];
-    hend[C::NROWS + r] = br.row_hend[2 * (at - own) + C::NROWS + own];
+    ends[0] = br.row_hend[2 * (at - own) + own];
+    ends[1] = br.row_hend[2 * (at - own) + C::NROWS + own];
     off[r] = (((cz * BY + cy) * BX * C::TILE + (lz * (P + 1) + ly) * (P + 1)) << 8) |
              (yb && cy > 0 ? kLowY : 0) | (cy < BY ? kHighY : 0) | (zb && cz > 0 ? kLowZ : 0) |
              (cz < BZ ? kHighZ : 0) | (y == 0 ? kY0 : 0) | (C::DIM == 3 && z == 0 ? kZ0 : 0);
@@ -1040,11 +1042,6 @@ struct BrickRows {
     const int own = cy * P + j + C::LY * (cz * P + k);
     return base[own] + __popc(first[own] & ((1u << (cx * P)) - 1u));
   }
-  // Halo plane and index of a row's end (side 0: x = 0, 1: x = LX-1), as an offset.
-  __device__ __forceinline__ int64_t end_at(int r, int side, int nhalo) const {
-    const int o = off[r], plane = (side ? 0 : 1) | ((o & kY0) ? 2 : 0) | ((o & kZ0) ? 4 : 0);
-    return (int64_t)plane * nhalo + hend[side * C::NROWS + r];
-  }
 };
 
 // (a pointer read from LDS is generic otherwise, and its stores wait on LDS too)
@@ -1055,20 +1052,19 @@ using GlobalT = __attribute__((address_space(1))) T;
 // where there is no cell): every lattice point sums its cells' values (z, then y, then x from the
 // low side: a fixed order) and is stored once.
 template <typename T, class C>
-__device__ __forceinline__ void brick_assemble(const T *tiles, const BrickRows<T, C> &R, T *__restrict__ halo,
-                                               int nhalo) {
+__device__ __forceinline__ void brick_assemble(const T *tiles, const BrickRows<T, C> &R, const int32_t (&ends)[2],
+                                               T *__restrict__ halo, int nhalo) {
   using Rows = BrickRows<T, C>;
   constexpr int P = C::P, N1 = P + 1, TS = C::TILE, BX = C::BX, BY = C::BY, LX = C::LX, NROWS = C::NROWS;
   constexpr int STEP_Y = BX * TS - P * N1, STEP_Z = BY * BX * TS - P * N1 * N1;  // to the cell before
   constexpr int DZ = C::DIM == 3 ? 1 : 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // the rows' ends, all of them brick-boundary points
-  constexpr int NE = (2 * NROWS + C::NT - 1) / C::NT;
+  // the rows' ends, all of them brick-boundary points: a row per thread
 #pragma unroll
-  for (int m = 0; m < NE; ++m) {
-    const int i = tid + m * C::NT, side = i >= NROWS ? 1 : 0, r = i < 2 * NROWS ? i - side * NROWS : 0, o = R.off[r];
+  for (int side = 0; side < 2; ++side) {
+    const int r = tid < NROWS ? tid : 0, o = R.off[r];
     const int off = (o >> 8) + (side ? (BX - 1) * TS + P : 0);
-    const uint32_t bm = i < 2 * NROWS ? R.bmask[r] : 0u;
+    const uint32_t bm = tid < NROWS ? R.bmask[r] : 0u;
     T sum = T(0);
 #pragma unroll
     for (int dz = DZ; dz >= 0; --dz)
@@ -1078,7 +1074,8 @@ __device__ __forceinline__ void brick_assemble(const T *tiles, const BrickRows<T
         const T val = tiles[in ? off - dz * STEP_Z - dy * STEP_Y : 0];
         sum += in ? val : T(0);
       }
-    if ((bm >> (side ? LX - 1 : 0)) & 1u) halo[R.end_at(r, side, nhalo)] = sum;
+    const int plane = (side ? 0 : 1) | ((o & Rows::kY0) ? 2 : 0) | ((o & Rows::kZ0) ? 4 : 0);
+    if ((bm >> (side ? LX - 1 : 0)) & 1u) halo[(int64_t)plane * nhalo + ends[side]] = sum;
   }
   // the points 0 < x < LX-1: lanes take whole rows, so that a lane's x is fixed, and the rows of one
   // kind sum equally many cells.  Up to four rows per lane at a time, every LDS read before the first
@@ -1166,7 +1163,8 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
   const bool on = wc < C::CPW && c < nc;
   const int loc = on ? br.cell_loc[c0 + c] : 0;
   const int cface = on ? br.cell_face[c0 + c] : 0;
-  rows.fill(br, brick, full, v, halo, nhalo);
+  int32_t ends[2] = {0, 0};
+  rows.fill(br, brick, full, v, halo, nhalo, ends);
   __syncthreads();
   // the cell's place in the brick, and the lane's x-runs (j, k): the first DoF of each from its row
   const int lcx = (loc % LX) / P, lcy = (loc / LX % LY) / P, lcz = loc / (LX * LY) / P;
@@ -1319,7 +1317,7 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
       for (int y = 0; y < N1; ++y) tile[(z * N1 + y) * N1 + j] = out[z][y];
   }
   __syncthreads();
-  brick_assemble<T, C>(tiles, rows, halo, nhalo);
+  brick_assemble<T, C>(tiles, rows, ends, halo, nhalo);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1343,7 +1341,8 @@ __device__ __forceinline__ void tile_body(const int brick, BrickArgs br, const T
   const int c0 = br.cell_off[brick], nc = br.cell_off[brick + 1] - c0, f0 = br.face_off[brick];
   const int loc = tid < nc ? br.cell_loc[c0 + tid] : 0, info_ = tid < nc ? 2 * br.cell_face[c0 + tid] + 1 : 0;
   if (tid < C::MAXC) s_info[tid] = 0;
-  rows.fill(br, brick, nc == C::MAXC, v, halo, nhalo);
+  int32_t ends[2] = {0, 0};
+  rows.fill(br, brick, nc == C::MAXC, v, halo, nhalo, ends);
   __syncthreads();
   if (tid < nc) s_info[(loc / (LX * LY) / P * BY + (loc / LX % LY) / P) * BX + (loc % LX) / P] = info_;
   __syncthreads();
@@ -1395,7 +1394,7 @@ __device__ __forceinline__ void tile_body(const int brick, BrickArgs br, const T
     for (int i = 0; i < N1; ++i) A[N1 * t + i] = out[i] + frow[i];
   }
   __syncthreads();
-  brick_assemble<T, C>(smem, rows, halo, nhalo);
+  brick_assemble<T, C>(smem, rows, ends, halo, nhalo);
 }
 
 template <typename T, int D, int N1, bool CELLS>
