@@ -161,7 +161,7 @@ sbm_status sbm_apply(sbm_handle h, const void *u, void *v, int prec, void *strea
  * sbm_apply_noalloc -- sbm_apply for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same operator,
  * kernels, arguments and result as sbm_apply (bitwise equal with the default extension), but
- * the apply's scratch is taken from a static device array of 96 MiB held by the library on
+ * the apply's scratch is taken from a static device array (288 MiB) held by the library on
  * each device it runs on (until the process ends) instead of the handle's own buffers.  The
  * call allocates nothing and never synchronises.  Every call on one device shares that array
  * and leaves its contents behind: calls that overlap on one device (other streams or threads)
@@ -169,8 +169,9 @@ sbm_status sbm_apply(sbm_handle h, const void *u, void *v, int prec, void *strea
  * device looks up that device's array address (that device must be current).
  * Errors: EINVAL (as sbm_apply, or the handle needs more scratch than 96 MiB in this
  * precision -- the CG brick-boundary sums take 2^dim x boundary DoFs values and the
- * surrogate faces 2 (p+1)^(dim-1) values each: a 64^3 Q4 sphere needs 67 MB in FP64; the
- * message states the size), EHIP.
+ * surrogate faces 2 (p+1)^(dim-1) values each: a 64^3 Q4 sphere needs 67 MB in FP64; 3D CG of
+ * degree 1 to 3 counts the DoFs on the boundaries of bricks of 8x8x8, 8x4x4 and 4x4x4 cells,
+ * whatever bricks the apply uses; the message states the size), EHIP.
  */
 sbm_status sbm_apply_noalloc(sbm_handle h, const void *u, void *v, int prec, void *stream);
 

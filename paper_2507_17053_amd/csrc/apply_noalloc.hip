@@ -17,7 +17,18 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)96 << 20;  // 96 MiB per device
+// An operator is accepted by the bytes its scratch would take with one fixed brick shape per degree
+// (noalloc_brick), so that what is accepted does not follow the shape in use, and the array holds the
+// scratch of every accepted operator whatever its bricks.  Three times the limit is enough.  Let L be
+// the DoFs on the fixed shape's planes (L_a those normal to axis a) and F the surrogate faces.  A DoF on
+// a plane in use that is normal to a and not one of L_a's touches an active cell; following that cell's
+// column along a both ways, each way ends on a DoF of L_a or on a surrogate face.  Between two planes of
+// the fixed shape lies at most one other plane in use (8x4x4 against 8x8x8 cells, 7x6x4 against 8x4x4,
+// 8x4x2 against 4x4x4), so a DoF of L_a ends at most two ways and a face at most (p+1)^2: the DoFs of
+// those planes are at most |L_a| + (p+1)^2 |F| / 2.  Planes are added along at most two axes, so the halo
+// takes at most 3 times its bytes on L and twice the faces' 2 (p+1)^2 values each.
+constexpr size_t kLimitBytes = (size_t)96 << 20;
+constexpr size_t kScratchBytes = 3 * kLimitBytes + 256;  // per device
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -74,19 +85,17 @@ extern "C" sbm_status sbm_apply_noalloc(sbm_handle h, const void *u, void *v, in
   const size_t halo_bytes = h->disc == SBM_CG ? ((size_t)1 << h->dim) * (size_t)h->n_halo_dofs * s : 0;
   const size_t limit_bytes = h->disc == SBM_CG ? ((size_t)1 << h->dim) * (size_t)h->n_halo_limit * s : 0;
   const size_t need = own - (halo_bytes + 255) / 256 * 256 + (limit_bytes + 255) / 256 * 256;
-  if (need > kScratchBytes) {
+  if (need > kLimitBytes || own > kScratchBytes) {
     set_error("sbm_apply_noalloc: the operator needs " + std::to_string(need) +
-              " bytes of scratch, more than the " + std::to_string(kScratchBytes) +
-              " bytes of the static device scratch; use sbm_apply");
+              " bytes of scratch, more than the " + std::to_string(kLimitBytes) +
+              " bytes it may take of the static device scratch; use sbm_apply");
     return SBM_EINVAL;
   }
-  sbm::Scratch scr{};  // (an accepted operator whose bricks need more than that has the scratch it was set up with)
-  if (own <= kScratchBytes) {
-    void *base = nullptr;
-    SBM_HIP_CHECK(scratch_address(&base));
-    scr.halo = base;
-    scr.fbuf = (unsigned char *)base + (halo_bytes + 255) / 256 * 256;
-  }
+  void *base = nullptr;
+  SBM_HIP_CHECK(scratch_address(&base));
+  sbm::Scratch scr;
+  scr.halo = base;
+  scr.fbuf = (unsigned char *)base + (halo_bytes + 255) / 256 * 256;
   SBM_HIP_CHECK(sbm::launch_operator(h, u, v, prec, SBM_PART_ALL, (hipStream_t)stream, &scr));
   sbm::note_work(h, (hipStream_t)stream);
   return SBM_OK;
