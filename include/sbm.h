@@ -272,9 +272,20 @@ sbm_status sbm_rhs_points(sbm_handle h, double *cell_qp, double *bdry_pts);
 /*
  * sbm_rhs -- right-hand side of Eq. (1): b_i = int f psi_i - int_{Gam~} (dpsi_i/dn~) g
  * + int_{Gam~} sigma g psi_i, from f at cell_qp and g at bdry_pts (host arrays laid out
- * as sbm_rhs_points).  b is a device FP64 vector of n_dofs entries.  Synchronous.
+ * as sbm_rhs_points).  b is a device FP64 vector of n_dofs entries.  Synchronous.  Assembled on
+ * the device, with at most 64 MB of f and the face data in device scratch for the call, or on a
+ * host thread where that is faster (the smallest operators) or the scratch cannot be had.
+ * Errors: EINVAL, ENOMEM (host memory), EHIP.
  */
 sbm_status sbm_rhs(sbm_handle h, const double *f_qp, const double *g_bp, double *b, void *stream);
+
+/*
+ * sbm_rhs_form -- sbm_rhs by a chosen form, to check and time each: the host form, or the device
+ * form with f in pieces of at most `cells` cells (0: of 64 MB; ENOMEM without device scratch).
+ */
+enum { SBM_RHS_AUTO = 0, SBM_RHS_HOST = 1, SBM_RHS_DEVICE = 2 };
+sbm_status sbm_rhs_form(sbm_handle h, const double *f_qp, const double *g_bp, double *b, int form,
+                        int64_t cells, void *stream);
 
 /*
  * sbm_l2_error -- the L2 error ||u_h - u*|| on the surrogate domain of the FP64 device vector x

@@ -1,4 +1,4 @@
-// Right-hand side of Eq. (1) on the device:
+// Right-hand side of Eq. (1), on the device and, for the smallest operators, on the host:
 //   b_i = int f psi_i - int_{Gam~} (dpsi_i/dn~) g + int_{Gam~} sigma g psi_i
 // from f at the cells' Gauss points and g at the true-boundary points (host arrays).
 //
@@ -13,10 +13,13 @@
 // by the setup (by chunk, then parity), with no atomics and no scratch beyond the data.
 //
 // What bounds it: the copy of f from the caller's memory (8 (p+1)^d bytes per cell, 28 GB/s from
-// ordinary host memory); the kernels take a few microseconds each.  The same sums on 16 host
-// threads took 2.76 ms for 40^3 Q4, 0.36 ms here.  f goes to the device in chunks of at most 64 MB,
-// so that the scratch stays small beside the operator at any size.
+// ordinary host memory) and, for CG, 2^d launches of which each covers one cell in 2^d.  The same sums
+// on 16 host threads took 2.76 ms for 40^3 Q4, 0.36 ms here (0.08 ms of it kernels).  f goes to the
+// device in chunks of at most 64 MB, so that the scratch stays small beside the operator at any size.
+// An operator of few cells is assembled on the calling thread (host_work).
 #include <algorithm>
+#include <new>
+#include <vector>
 
 #include "sbm_internal.h"
 
@@ -236,39 +239,147 @@ hipError_t rhs_on(const sbm_ctx *c, const double *f_qp, const double *g_bp, doub
   return e;
 }
 
+// out = N^T in along one axis of a tensor of n1 points per axis (first axis fastest)
+void contract(const Rules1D &R, int n1, const double *in, double *out, int dims, int axis) {
+  int st = 1, outer = 1;
+  for (int m = 0; m < axis; ++m) st *= n1;
+  for (int m = axis + 1; m < dims; ++m) outer *= n1;
+  for (int o = 0; o < outer; ++o) {
+    const double *src = in + (size_t)o * n1 * st;
+    double *dst = out + (size_t)o * n1 * st;
+    for (int i = 0; i < n1; ++i)
+      for (int l = 0; l < st; ++l) {
+        double acc = 0.0;
+        for (int q = 0; q < n1; ++q) acc += R.N[q * n1 + i] * src[q * st + l];
+        dst[i * st + l] = acc;
+      }
+  }
+}
+
+// All of it on one host thread: the cells in rank order, then the faces in face order.
+void rhs_host(const sbm_ctx *h, const double *f_qp, const double *g_bp, double *b) {
+  const int d = h->dim, n1 = h->n1, nb = h->nb, np = h->nq_face, P = h->p;
+  const Rules1D &R = h->rules;
+  std::vector<double> A(nb), B(nb);
+  double *src = A.data(), *dst = B.data();
+  std::vector<double> w(nb), wf(np);  // quadrature weights of a cell and of a face
+  for (int q = 0; q < nb; ++q) {
+    const int qk[3] = {q % n1, (q / n1) % n1, q / (n1 * n1)};
+    w[q] = 1.0;
+    for (int m = 0; m < d; ++m) w[q] *= R.w[qk[m]] * h->h;
+    if (q < np) {
+      wf[q] = 1.0;
+      for (int m = 0; m < d - 1; ++m) wf[q] *= R.w[qk[m]] * h->h;
+    }
+  }
+  std::fill(b, b + h->n_dofs, 0.0);
+  // local entry i of cell r, i = n1 t + k
+  auto run = [&](int64_t r, int t) { return b + (h->disc == SBM_CG ? (int64_t)h->runs[r * np + t] : r * nb + n1 * t); };
+  for (int64_t r = 0; r < h->n_cells; ++r) {
+    for (int q = 0; q < nb; ++q) src[q] = f_qp[r * nb + q] * w[q];
+    for (int m = 0; m < d; ++m) {
+      contract(R, n1, src, dst, d, m);
+      std::swap(src, dst);
+    }
+    for (int t = 0; t < np; ++t) {
+      double *to = run(r, t);
+      for (int k = 0; k < n1; ++k) to[k] += src[n1 * t + k];
+    }
+  }
+  for (int64_t f = 0; f < h->n_sbm; ++f) {
+    const int32_t *fc = &h->faces[3 * f];
+    const int a = fc[1], s = fc[2];
+    const double *Ds = s ? R.D1.data() : R.D0.data();
+    const double sgn = s ? 1.0 : -1.0;
+    for (int q = 0; q < np; ++q) src[q] = wf[q] * g_bp[f * np + q];
+    for (int m = 0; m < d - 1; ++m) {
+      contract(R, n1, src, dst, d - 1, m);
+      std::swap(src, dst);
+    }
+    auto row = [&](int ia) { return (ia == s * P ? h->sigma_gamma : 0.0) - sgn / h->h * Ds[ia]; };
+    for (int t = 0; t < np; ++t) {
+      const int t0 = t % n1, t1 = t / n1;
+      double *to = run(fc[0], t);
+      for (int k = 0; k < n1; ++k)
+        to[k] += a == 0 ? row(k) * src[t] : (a == 1 ? row(t0) * src[d == 3 ? k + n1 * t1 : k] : row(t1) * src[k + n1 * t0]);
+    }
+  }
+}
+
+sbm_status by_host(const sbm_ctx *h, const double *f_qp, const double *g_bp, double *b, hipStream_t s) {
+  try {
+    std::vector<double> bh(h->n_dofs);
+    rhs_host(h, f_qp, g_bp, bh.data());
+    const hipError_t e = hipMemcpyAsync(b, bh.data(), sizeof(double) * bh.size(), hipMemcpyHostToDevice, s);
+    SBM_HIP_CHECK(hipStreamSynchronize(s));
+    SBM_HIP_CHECK(e);
+  } catch (const std::bad_alloc &) {
+    set_error("sbm_rhs: out of host memory");
+    return SBM_ENOMEM;
+  }
+  return SBM_OK;
+}
+
+// On the device, f in pieces of at most `chunk` cells.
+sbm_status by_device(const sbm_ctx *h, const double *f_qp, const double *g_bp, double *b, int64_t chunk, hipStream_t s) {
+  const int64_t nc = h->n_cells, nf = h->n_sbm;
+  const size_t need[5] = {sizeof(int32_t) * nc * h->dim, sizeof(int32_t) * 3 * nf, sizeof(int2) * nc,
+                          sizeof(double) * nf * h->nq_face, sizeof(double) * chunk * h->nb};
+  size_t off[5], bytes = 0;
+  for (int k = 0; k < 5; ++k) {
+    off[k] = bytes;
+    bytes += (need[k] + 255) / 256 * 256;
+  }
+  void *scratch = nullptr;
+  const hipError_t ea = dev_alloc(&scratch, bytes);
+  if (ea != hipSuccess) {
+    (void)hipGetLastError();
+    set_error(std::string("sbm_rhs: scratch allocation failed: ") + hipGetErrorString(ea));
+    return ea == hipErrorOutOfMemory ? SBM_ENOMEM : SBM_EHIP;
+  }
+  const hipError_t e = rhs_on(h, f_qp, g_bp, b, (char *)scratch, off, chunk, s);
+  const hipError_t es = hipStreamSynchronize(s);  // the scratch is free, and b ready
+  dev_free(scratch);
+  SBM_HIP_CHECK(e);
+  SBM_HIP_CHECK(es);
+  return SBM_OK;
+}
+
+// Multiply-adds of the host form, with 50 (d - 1) more per cell for its loops: it takes 20 us and
+// 0.23 us per thousand.  The device form takes 70 us and more for CG (its launches and copies), 33 us and
+// more for DG.  Host / device in us at sizes about the lines drawn here: CG 2D Q1, 5,771 cells (384 k)
+// 105 / 95, 3D Q3, 112 cells (130 k) 60 / 149, 2D Q2, 1,399 cells (149 k) 60 / 84; DG 2D Q1, 1,399 cells
+// (94 k) 39 / 48, 3D Q6, 7 cells (82 k) 41 / 55, 3D Q3, 7 cells (12 k) 24 / 37.
+int64_t host_work(const sbm_ctx *h) {
+  return h->n_cells * (h->nb * h->dim * h->n1 + 50 * (h->dim - 1)) +
+         h->n_sbm * (h->nq_face * (h->dim - 1) * h->n1 + h->nb);
+}
+constexpr int64_t kHostWork[2] = {250000, 80000};  // SBM_CG, SBM_DG
+
 }  // namespace
 }  // namespace sbm
 
-extern "C" sbm_status sbm_rhs(sbm_handle h, const double *f_qp, const double *g_bp, double *b, void *stream) {
+extern "C" sbm_status sbm_rhs_form(sbm_handle h, const double *f_qp, const double *g_bp, double *b, int form,
+                                   int64_t cells, void *stream) {
   using namespace sbm;
-  if (!h || !f_qp || !b || (h->n_sbm > 0 && !g_bp) || h->host_only) {
+  if (!h || !f_qp || !b || (h->n_sbm > 0 && !g_bp) || h->host_only || cells < 0 || form < SBM_RHS_AUTO ||
+      form > SBM_RHS_DEVICE) {
     set_error("sbm_rhs: NULL argument or host-only handle");
     return SBM_EINVAL;
   }
   const hipStream_t s = (hipStream_t)stream;
-  if (h->n_cells > 0) {
-    const int64_t nc = h->n_cells, nf = h->n_sbm;
-    const int64_t chunk = std::min<int64_t>(nc, std::max<int64_t>(1, (int64_t)(kChunkBytes / (sizeof(double) * h->nb))));
-    const size_t need[5] = {sizeof(int32_t) * nc * h->dim, sizeof(int32_t) * 3 * nf, sizeof(int2) * nc,
-                            sizeof(double) * nf * h->nq_face, sizeof(double) * chunk * h->nb};
-    size_t off[5], bytes = 0;
-    for (int k = 0; k < 5; ++k) {
-      off[k] = bytes;
-      bytes += (need[k] + 255) / 256 * 256;
-    }
-    void *scratch = nullptr;
-    const hipError_t ea = dev_alloc(&scratch, bytes);
-    if (ea != hipSuccess) {
-      set_error(std::string("sbm_rhs: scratch allocation failed: ") + hipGetErrorString(ea));
-      return ea == hipErrorOutOfMemory ? SBM_ENOMEM : SBM_EHIP;
-    }
-    const hipError_t e = rhs_on(h, f_qp, g_bp, b, (char *)scratch, off, chunk, s);
-    const hipError_t es = hipStreamSynchronize(s);  // the scratch is free, and b ready
-    dev_free(scratch);
-    SBM_HIP_CHECK(e);
-    SBM_HIP_CHECK(es);
+  if (h->n_cells == 0) {
+    SBM_HIP_CHECK(hipStreamSynchronize(s));
     return SBM_OK;
   }
-  SBM_HIP_CHECK(hipStreamSynchronize(s));
-  return SBM_OK;
+  if (form == SBM_RHS_HOST || (form == SBM_RHS_AUTO && host_work(h) <= kHostWork[h->disc == SBM_DG]))
+    return by_host(h, f_qp, g_bp, b, s);
+  const int64_t most = std::max<int64_t>(1, (int64_t)(kChunkBytes / (sizeof(double) * h->nb)));
+  const sbm_status st = by_device(h, f_qp, g_bp, b, std::min(h->n_cells, cells > 0 ? std::min(cells, most) : most), s);
+  // (no room on the device beside its other contents: the host form needs none)
+  return st == SBM_ENOMEM && form == SBM_RHS_AUTO ? by_host(h, f_qp, g_bp, b, s) : st;
+}
+
+extern "C" sbm_status sbm_rhs(sbm_handle h, const double *f_qp, const double *g_bp, double *b, void *stream) {
+  return sbm_rhs_form(h, f_qp, g_bp, b, SBM_RHS_AUTO, 0, stream);
 }

@@ -87,6 +87,7 @@ _lib.sbm_batch_destroy.argtypes = [_P]
 _lib.sbm_dof_points.argtypes = [_P, _P]
 _lib.sbm_rhs_points.argtypes = [_P, _P, _P]
 _lib.sbm_rhs.argtypes = [_P, _P, _P, _P, _P]
+_lib.sbm_rhs_form.argtypes = [_P, _P, _P, _P, ctypes.c_int, ctypes.c_int64, _P]
 _lib.sbm_solve.argtypes = [_P, _P, _P, ctypes.c_double, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                            _P, ctypes.POINTER(SolveInfo)]
 _lib.sbm_solve_batch.argtypes = [ctypes.c_int, ctypes.POINTER(_P), ctypes.POINTER(_P), ctypes.POINTER(_P),
@@ -106,7 +107,7 @@ _lib.sbm_layout_stats.argtypes = [_P, _I64P, _I64P, _I64P]
 EXPORTED = ["sbm_setup", "sbm_info", "sbm_destroy", "sbm_last_error", "sbm_apply", "sbm_apply_noalloc",
             "sbm_apply_parts",
             "sbm_apply_batch", "sbm_batch_create", "sbm_batch_run", "sbm_batch_destroy", "sbm_layout_stats",
-            "sbm_dof_points", "sbm_rhs_points", "sbm_rhs", "sbm_l2_error", "sbm_solve", "sbm_solve_batch", "sbm_diagonal",
+            "sbm_dof_points", "sbm_rhs_points", "sbm_rhs", "sbm_rhs_form", "sbm_l2_error", "sbm_solve", "sbm_solve_batch", "sbm_diagonal",
             "sbm_footprint_estimate", "sbm_export_cells", "sbm_export_sbm_faces", "sbm_export_face_xi",
             "sbm_export_cell_dofs"]
 
@@ -309,6 +310,13 @@ class Operator:
         f_qp = np.ascontiguousarray(f_qp, dtype=np.float64)
         g_bp = np.ascontiguousarray(g_bp, dtype=np.float64)
         _check(_lib.sbm_rhs(self._h, _hptr(f_qp), _hptr(g_bp), _dptr(out), _stream_ptr(stream)), "sbm_rhs")
+
+    def rhs_form(self, f_qp: np.ndarray, g_bp: np.ndarray, out, form, cells=0, stream=None):
+        """sbm_rhs_form: rhs() by the "host" or the "device" form (f in pieces of `cells` cells)."""
+        f_qp = np.ascontiguousarray(f_qp, dtype=np.float64)
+        g_bp = np.ascontiguousarray(g_bp, dtype=np.float64)
+        _check(_lib.sbm_rhs_form(self._h, _hptr(f_qp), _hptr(g_bp), _dptr(out), {"host": 1, "device": 2}[form],
+                                 int(cells), _stream_ptr(stream)), "sbm_rhs_form")
 
     def l2_error(self, x, ustar_qp):
         """sbm_l2_error: ||u_h - u*|| for the FP64 device vector x, u* given at the cell Gauss
