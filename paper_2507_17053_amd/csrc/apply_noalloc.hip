@@ -27,7 +27,7 @@ namespace {
 // 8x4x2 against 4x4x4), so a DoF of L_a ends at most two ways and a face at most (p+1)^2: the DoFs of
 // those planes are at most |L_a| + (p+1)^2 |F| / 2.  Planes are added along at most two axes, so the halo
 // takes at most 3 times its bytes on L and twice the faces' 2 (p+1)^2 values each.
-constexpr size_t kLimitBytes = (size_t)96 << 20;
+constexpr size_t kLimitBytes = sbm::kNoallocBytes;
 constexpr size_t kScratchBytes = 3 * kLimitBytes + 256;  // per device
 constexpr int kMaxDevices = 64;
 

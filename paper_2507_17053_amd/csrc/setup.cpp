@@ -465,10 +465,10 @@ static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx,
       ++fill[b];
     }
   }
-  // run bases of the cells in brick order (the kernel reads them without the cell rank)
+  // run bases of the cells in brick order (the sweeps read them without the cell rank)
   const int npr = (d == 3) ? (p + 1) * (p + 1) : (p + 1);
-  c->brick_runs.resize((size_t)nc * npr);
-  for (int64_t i = 0; i < nc; ++i)
+  c->brick_runs.resize(c->by_cells ? 0 : (size_t)nc * npr);
+  for (int64_t i = 0; !c->by_cells && i < nc; ++i)
     std::copy(c->runs.begin() + (size_t)c->brick_cells[i] * npr, c->runs.begin() + (size_t)(c->brick_cells[i] + 1) * npr,
               c->brick_runs.begin() + (size_t)i * npr);
   const int64_t nf = c->n_sbm;
@@ -476,19 +476,19 @@ static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx,
   for (int64_t f = 0; f < nf; ++f) ++c->brick_face_off[bid[bkey[c->faces[3 * f]]] + 1];
   for (int32_t b = 0; b < nb; ++b) c->brick_face_off[b + 1] += c->brick_face_off[b];
   c->brick_faces.assign(nf, 0);
-  c->brick_face_loc.assign(nf, 0);
+  c->brick_face_loc.assign(c->by_cells ? 0 : nf, 0);
   {
     std::vector<int32_t> fill(c->brick_face_off.begin(), c->brick_face_off.end() - 1);
     for (int64_t f = 0; f < nf; ++f) {
       const int64_t r = c->faces[3 * f];
       const int32_t b = bid[bkey[r]];
       c->brick_faces[fill[b]] = (int32_t)f;
-      c->brick_face_loc[fill[b]] = cell_loc(r, bkey[r]);
+      if (!c->by_cells) c->brick_face_loc[fill[b]] = cell_loc(r, bkey[r]);
       ++fill[b];
     }
   }
-  c->brick_cell_face.assign(nc, 0);
-  {
+  c->brick_cell_face.assign(c->by_cells ? nc : 0, 0);
+  if (c->by_cells) {
     std::vector<int32_t> at(nc);
     for (int64_t i = 0; i < nc; ++i) at[c->brick_cells[i]] = (int32_t)i;
     for (int64_t i = 0; i < nf; ++i) {
@@ -562,12 +562,12 @@ static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx,
   const uint32_t edge = 1u | (1u << (LX - 1));
   auto boundary_row = [&](int y, int z) { return y == 0 || y == LY - 1 || (d == 3 && (z == 0 || z == LZ - 1)); };
   auto boundary_mask = [&](int y, int z, uint32_t gm) { return boundary_row(y, z) ? gm : (gm & edge); };
-  const int64_t BYP = BY * p, nyb = ly / BYP + 1;
-  std::vector<int32_t> hidx(c->n_dofs, -1), sidx((nbx + 1) * nyb * BYP * lz, -1);
+  const int64_t BYP = BY * p, yrows = std::min(BYP, ly);
+  std::vector<int32_t> hidx(c->n_dofs, -1), sidx((nbx + 1) * nby * yrows * lz, -1);
   std::vector<unsigned char> kind(c->n_dofs, 0);  // 1: on an x plane, 2: not
   auto end_slot = [&](int32_t b, int side, int y, int z) {
     const int64_t key = key_of[b], Y = (key / nbx) % nby * BYP + y, Z = d == 3 ? key / (nbx * nby) * BZ * p + z : 0;
-    return Y % BYP + BYP * (key % nbx + side + (nbx + 1) * (Y / BYP + nyb * Z));
+    return Y % BYP + yrows * (key % nbx + side + (nbx + 1) * (Y / BYP + nby * Z));
   };
   for (int32_t b = 0; b < nb; ++b)
     for (int z = 0; z < LZ; ++z)
@@ -637,7 +637,7 @@ static void build_bricks(sbm_ctx *c, const std::vector<int32_t> &id, int64_t lx,
   c->n_halo_slots = slots;
   c->n_halo_limit = c->n_halo_dofs;
   int lb[3];
-  if (noalloc_brick(d, p, lb)) {
+  if (noalloc_counts(c, c->n_dofs) && noalloc_brick(d, p, lb)) {
     c->n_halo_limit = 0;
     for (int64_t z = 0; z < lz; ++z)
       for (int64_t y = 0; y < ly; ++y)
@@ -1280,8 +1280,8 @@ size_t sbm_footprint_estimate(const sbm_mesh *mesh, int p, int disc, int64_t n_c
       for (int k = 0; k < d; ++k) places *= (mesh->n[k] + B[k] - 1) / B[k];
       nrows = std::max(nbricks * (p <= 2 ? 81 : 169), std::min(nbricks, places) * rows);
     }
-    b += up(4 * nc * np) * 2;                                          // runs, brick_runs
-    b += up(4 * (nbricks + 1)) * 2 + up(4 * nc) * 2 + up(4 * nf);      // offsets, cell/face locations
+    b += up(4 * nc * np) + (by_cells ? up(4 * nc) : up(4 * nc * np) + up(4 * nf));  // runs, per-cell tables
+    b += up(4 * (nbricks + 1)) * 2 + up(4 * nc);                       // offsets, cell locations
     b += up(4 * nf * np);                                              // face_runs
     b += 4 * up(4 * nrows) + up(8 * nrows);                                            // row descriptors
     b += up(4 * halo) + up(halo);                                      // halo DoF ids and masks

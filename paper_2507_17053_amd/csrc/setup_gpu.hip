@@ -221,32 +221,28 @@ __global__ void brick_count_kernel(Geo g, Bricks bk, int64_t nc, int64_t nf, con
 }
 
 // A brick's cells in rank order: the position of a cell is the number of active cells of its
-// brick that come before it (z, then y, then x, as the ranks).
+// brick that come before it (z, then y, then x, as the ranks).  Of the last two tables an operator has
+// one (brick_cell_face: zero here, brick_faces_kernel fills in the cells with faces).
 __global__ void brick_cells_kernel(Geo g, Bricks bk, int64_t nc, const int32_t *cells, const int32_t *rank_grid,
-                                   const int32_t *sflag, const int32_t *bid, const int32_t *cell_off,
-                                   const int32_t *runs, int32_t *brick_cell_loc, int32_t *brick_cell_face,
-                                   int32_t *brick_runs) {
+                                   const int32_t *bid, const int32_t *cell_off, const int32_t *runs,
+                                   int32_t *brick_cell_loc, int32_t *brick_cell_face, int32_t *brick_runs) {
   GRID_LOOP(r, nc) {
     const int32_t *cc = cells + r * g.d;
     const int64_t key = brick_key(g, bk, cc);
     const int64_t x0 = cc[0] - cc[0] % bk.BX, y0 = cc[1] - cc[1] % bk.BY;
     const int64_t z0 = g.d == 3 ? cc[2] - cc[2] % bk.BZ : 0;
     const int64_t me = ((g.d == 3 ? cc[2] : 0) - z0) * bk.BY * bk.BX + (cc[1] - y0) * bk.BX + (cc[0] - x0);
-    const int ncode = 2 * g.d;
-    int pos = 0, fpos = 0;
+    int pos = 0;
     for (int64_t q = 0; q < me; ++q) {
       const int64_t ox = q % bk.BX, oy = (q / bk.BX) % bk.BY, oz = q / (bk.BX * bk.BY);
-      if (!cell_active(g, rank_grid, x0 + ox, y0 + oy, z0 + oz)) continue;
-      const int64_t rr = rank_grid[((z0 + oz) * g.ny + y0 + oy) * g.nx + x0 + ox];
-      ++pos;
-      for (int c2 = 0; c2 < ncode; ++c2) fpos += sflag[rr * ncode + c2];
+      pos += cell_active(g, rank_grid, x0 + ox, y0 + oy, z0 + oz) ? 1 : 0;
     }
     const int64_t i = cell_off[bid[key]] + pos;
     brick_cell_loc[i] = cell_loc(g, bk, cc);
-    int32_t mask = 0;
-    for (int c2 = 0; c2 < ncode; ++c2) mask |= sflag[r * ncode + c2] ? 1 << c2 : 0;
-    brick_cell_face[i] = mask ? fpos << 6 | mask : 0;
-    for (int t = 0; t < g.np; ++t) brick_runs[i * g.np + t] = runs[r * g.np + t];
+    if (brick_cell_face)
+      brick_cell_face[i] = 0;
+    else
+      for (int t = 0; t < g.np; ++t) brick_runs[i * g.np + t] = runs[r * g.np + t];
   }
 }
 
@@ -254,9 +250,10 @@ __global__ void brick_cells_kernel(Geo g, Bricks bk, int64_t nc, const int32_t *
 // the earlier faces of the same cell.
 __global__ void brick_faces_kernel(Geo g, Bricks bk, int64_t nf, const int32_t *cells, const int32_t *rank_grid,
                                    const int32_t *faces, const int32_t *sflag, const int32_t *fidx,
-                                   const int32_t *bid, const int32_t *face_off, const int32_t *runs,
-                                   const double *xi_host, int32_t *face_loc, int32_t *dface_cell,
-                                   int32_t *dface_code, double *dface_xi, int32_t *face_runs) {
+                                   const int32_t *bid, const int32_t *face_off, const int32_t *cell_off,
+                                   const int32_t *runs, const double *xi_host, int32_t *face_loc,
+                                   int32_t *brick_cell_face, int32_t *dface_cell, int32_t *dface_code,
+                                   double *dface_xi, int32_t *face_runs) {
   const int ncode = 2 * g.d;
   GRID_LOOP(f, nf) {
     const int32_t r = faces[3 * f];
@@ -265,15 +262,23 @@ __global__ void brick_faces_kernel(Geo g, Bricks bk, int64_t nf, const int32_t *
     const int64_t x0 = cc[0] - cc[0] % bk.BX, y0 = cc[1] - cc[1] % bk.BY;
     const int64_t z0 = g.d == 3 ? cc[2] - cc[2] % bk.BZ : 0;
     const int64_t me = ((g.d == 3 ? cc[2] : 0) - z0) * bk.BY * bk.BX + (cc[1] - y0) * bk.BX + (cc[0] - x0);
-    int64_t pos = f - fidx[(int64_t)r * ncode];  // earlier faces of the same cell
+    const int64_t in_cell = f - fidx[(int64_t)r * ncode];  // earlier faces of the same cell
+    int64_t pos = in_cell, cpos = 0;
     for (int64_t q = 0; q < me; ++q) {
       const int64_t ox = x0 + q % bk.BX, oy = y0 + (q / bk.BX) % bk.BY, oz = z0 + q / (bk.BX * bk.BY);
       if (!cell_active(g, rank_grid, ox, oy, oz)) continue;
       const int64_t rr = rank_grid[(oz * g.ny + oy) * g.nx + ox];
+      ++cpos;
       for (int c2 = 0; c2 < ncode; ++c2) pos += sflag[rr * ncode + c2];
     }
     const int64_t i = face_off[bid[key]] + pos;
-    face_loc[i] = cell_loc(g, bk, cc);
+    if (!brick_cell_face) {
+      face_loc[i] = cell_loc(g, bk, cc);
+    } else if (in_cell == 0) {
+      int32_t m = (int32_t)pos << 6;
+      for (int c2 = 0; c2 < ncode; ++c2) m |= sflag[(int64_t)r * ncode + c2] ? 1 << c2 : 0;
+      brick_cell_face[cell_off[bid[key]] + cpos] = m;
+    }
     dface_cell[i] = r;
     dface_code[i] = 2 * faces[3 * f + 1] + faces[3 * f + 2];
     for (int e = 0; e < g.np * g.d; ++e) dface_xi[i * g.np * g.d + e] = xi_host[f * g.np * g.d + e];
@@ -314,17 +319,18 @@ __device__ __forceinline__ uint32_t boundary_mask(const Geo &g, const Bricks &bk
 
 // Halo numbering (see build_bricks): flags, then their exclusive prefix sums, of the points on x planes
 // only (side, by end_slot), and by DoF of the other boundary points on x planes (end) and off them (in).
+// The three follow each other, each with a zero behind it, and are scanned as one: end starts at the
+// number of side points, in at that of both.
 struct HaloScan {
   int32_t *side, *end, *in;
-  int32_t n_side;
 };
 
 // Place of lattice row (Y, Z)'s point on the x plane to the low (side 0) or high side of a brick: by the
 // row within its bricks, then x plane, then row of bricks.
 __device__ __forceinline__ int64_t end_slot(const Bricks &bk, const Lat &lt, int64_t key, int side, int64_t Y,
                                             int64_t Z) {
-  const int64_t B = bk.LY - 1, nb = lt.ly / B + 1;
-  return Y % B + B * (key % bk.nbx + side + (bk.nbx + 1) * (Y / B + nb * Z));
+  const int64_t B = bk.LY - 1, rows = std::min<int64_t>(B, lt.ly);
+  return Y % B + rows * (key % bk.nbx + side + (bk.nbx + 1) * (Y / B + bk.nby * Z));
 }
 
 __global__ void rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, const int64_t *key_of,
@@ -369,23 +375,27 @@ __global__ void rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, const int
   }
 }
 
-// DoFs on the lattice planes x % px = 0, y % py = 0 or z % pz = 0
-__global__ void plane_dofs_kernel(Lat lt, int64_t n, int px, int py, int pz, const int32_t *lflag,
-                                  unsigned long long *count) {
-  int mine = 0;
-  GRID_LOOP(m, n) {
-    if (!lflag[m]) continue;
-    const int64_t x = m % lt.lx, q = m / lt.lx, y = q % lt.ly, z = q / lt.ly;
-    mine += x % px == 0 || y % py == 0 || z % pz == 0;
+// DoFs on the lattice planes x % px = 0, y % py = 0 or z % pz = 0: one lattice row per wavefront and
+// step, one addition per block (one per wavefront of a point-wise loop took 1.06 ms for 260^3 Q1, all of
+// them to one address).
+__global__ __launch_bounds__(kT) void plane_dofs_kernel(Lat lt, int px, int py, int pz,
+                                                        const int32_t *__restrict__ lflag,
+                                                        unsigned long long *count) {
+  __shared__ unsigned long long part[kT / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  unsigned long long mine = 0;
+  for (int64_t row = blockIdx.x * (int64_t)(kT / 64) + wave; row < lt.ly * lt.lz; row += gridDim.x * (int64_t)(kT / 64)) {
+    const int64_t y = row % lt.ly, z = row / lt.ly;
+    const int step = y % py == 0 || z % pz == 0 ? 1 : px;
+    for (int64_t x = (int64_t)lane * step; x < lt.lx; x += 64 * step) mine += lflag[row * lt.lx + x] != 0;
   }
   for (int off = 32; off > 0; off >>= 1) mine += __shfl_down(mine, off, 64);
-  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(count, (unsigned long long)mine);
-}
-
-__global__ void halo_totals_kernel(HaloScan hs, int64_t n_ends, int64_t n_dofs, int32_t *out) {
-  out[0] = hs.side[n_ends];
-  out[1] = hs.end[n_dofs];
-  out[2] = hs.in[n_dofs];
+  if (lane == 0) part[wave] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kT / 64; ++w) mine += part[w];
+    if (mine) atomicAdd(count, mine);
+  }
 }
 
 __global__ void halo_rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, int64_t n_dofs, const int64_t *key_of,
@@ -403,12 +413,12 @@ __global__ void halo_rows_kernel(Geo g, Bricks bk, Lat lt, int64_t nbricks, int6
     const uint32_t inner = hgm & ~(1u | (1u << (bk.LX - 1)));
     const int32_t base = row_base[e];
     const bool brow = boundary_row(g, bk, y, z);
-    int32_t first_end = 0, first_in = 0;  // of the lattice row
+    int32_t first_end = 0, first_in = 0;  // of the lattice row, added to its points' sums
     if (hgm && brow) {
       const int64_t m = (Z * lt.ly + Y) * lt.lx;
       const int64_t r0 = lpre[m], r1 = m + lt.lx < lt.lx * lt.ly * lt.lz ? lpre[m + lt.lx] : n_dofs;
-      first_end = hs.n_side + hs.in[r0];
-      first_in = hs.n_side + hs.end[r1];
+      first_end = hs.in[r0] - hs.in[0];
+      first_in = hs.end[r1] - hs.in[0];
     }
     auto index = [&](int x) {
       const int32_t dof = base + __popc(gm & ((1u << x) - 1u));
@@ -474,22 +484,22 @@ struct Temps {
   }
 };
 
-// exclusive prefix sum of n int32 (in place allowed); returns the total through *total (host), unless
-// that is null: then nothing is waited for
+// exclusive prefix sum of n int32 (in place allowed); returns the total through *total (host)
 hipError_t exclusive_scan(Temps &tmp, const int32_t *in, int32_t *out, int64_t n, int64_t *total) {
-  if (total) *total = 0;
+  *total = 0;
   if (n == 0) return hipSuccess;
   size_t bytes = 0;
-  hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, (int)n, tmp.s);
+  auto scan = [&](void *ws) {  // (the halo's flags are up to three lists of DoFs)
+    return n <= INT32_MAX ? hipcub::DeviceScan::ExclusiveSum(ws, bytes, in, out, (int)n, tmp.s)
+                          : hipcub::DeviceScan::ExclusiveSum(ws, bytes, in, out, (size_t)n, tmp.s);
+  };
+  hipError_t e = scan(nullptr);
   if (e != hipSuccess) return e;
   void *ws = tmp.get<char>((int64_t)bytes);
   if (!ws) return tmp.err;
   int32_t last_in = 0, last_out = 0;
-  if (total)  // before out replaces it
-    e = hipMemcpyAsync(&last_in, in + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);
-  if (e != hipSuccess) return e;
-  e = hipcub::DeviceScan::ExclusiveSum(ws, bytes, in, out, (int)n, tmp.s);
-  if (!total) return e;
+  e = hipMemcpyAsync(&last_in, in + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);  // before out replaces it
+  if (e == hipSuccess) e = scan(ws);
   if (e == hipSuccess) e = hipMemcpyAsync(&last_out, out + n - 1, sizeof(int32_t), hipMemcpyDeviceToHost, tmp.s);
   if (e == hipSuccess) e = hipStreamSynchronize(tmp.s);
   *total = (int64_t)last_in + last_out;
@@ -696,7 +706,9 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     DS_CHECK(hipMemcpyAsync(d_bid, bid.data(), sizeof(int32_t) * nslot, hipMemcpyHostToDevice, s), "upload");
     if (nbk)
       DS_CHECK(hipMemcpyAsync(d_key_of, key_of.data(), sizeof(int64_t) * nbk, hipMemcpyHostToDevice, s), "upload");
-    n_ends = (bk.nbx + 1) * (lt.ly / (bk.LY - 1) + 1) * (bk.LY - 1) * lt.lz;
+    // (fewer than 2^31 with the meshes taken above: more than the lattice's points only where the mesh is
+    // one cell wide in x, and there by less than the vertices' share of them)
+    n_ends = (bk.nbx + 1) * bk.nby * std::min<int64_t>(bk.LY - 1, lt.ly) * lt.lz;
     const int64_t n_scan = n_ends + 2 * n_dofs + 3;
     hs.side = tmp.get<int32_t>(n_scan);
     DS_CHECK(tmp.err, "allocation");
@@ -712,12 +724,12 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
   if (cg) {
     cv.add(c->d_runs, nc * g.np);
     cv.add(c->d_brick_cell_off, nbk + 1);
-    cv.add(c->d_brick_runs, nc * g.np);
+    cv.add(c->d_brick_runs, c->by_cells ? 0 : nc * g.np);
     cv.add(c->d_face_runs, nf * g.np);
     cv.add(c->d_brick_cell_loc, nc);
     cv.add(c->d_brick_face_off, nbk + 1);
-    cv.add(c->d_brick_face_loc, nf);
-    cv.add(c->d_brick_cell_face, nc);
+    cv.add(c->d_brick_face_loc, c->by_cells ? 0 : nf);
+    cv.add(c->d_brick_cell_face, c->by_cells ? nc : 0);
     cv.add(c->d_row_base, nrow_all);
     cv.add(c->d_row_gmask, nrow_all);
     cv.add(c->d_row_bmask, nrow_all);
@@ -741,16 +753,7 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     if (nrow_all > 0)
       hipLaunchKernelGGL(rows_kernel, dim3(grid_for(nrow_all)), dim3(kT), 0, s, g, bk, lt, nbk, d_key_of, rank_grid,
                          lflag, lpre, t_row_base, t_row_gmask, t_row_bmask, hs);
-    DS_CHECK(exclusive_scan(tmp, hs.side, hs.side, n_ends + 1, nullptr), "halo scan");
-    DS_CHECK(exclusive_scan(tmp, hs.end, hs.end, n_dofs + 1, nullptr), "halo scan");
-    DS_CHECK(exclusive_scan(tmp, hs.in, hs.in, n_dofs + 1, nullptr), "halo scan");
-    int32_t *last = tmp.get<int32_t>(3), totals[3] = {0, 0, 0};
-    DS_CHECK(tmp.err, "allocation");
-    hipLaunchKernelGGL(halo_totals_kernel, dim3(1), dim3(1), 0, s, hs, n_ends, n_dofs, last);
-    DS_CHECK(hipMemcpyAsync(totals, last, sizeof(totals), hipMemcpyDeviceToHost, s), "download");
-    DS_CHECK(hipStreamSynchronize(s), "synchronise");
-    hs.n_side = totals[0];
-    n_halo = (int64_t)totals[0] + totals[1] + totals[2];
+    DS_CHECK(exclusive_scan(tmp, hs.side, hs.side, n_ends + 2 * n_dofs + 3, &n_halo), "halo scan");
     c->n_halo_dofs = n_halo;
     cv.add(c->d_halo_dof, n_halo);
     cv.add(c->d_halo_mask, n_halo);
@@ -769,14 +772,13 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
              "upload");
     if (nc > 0) {
       DS_CHECK(hipMemcpyAsync(c->d_runs, runs, sizeof(int32_t) * nc * g.np, hipMemcpyDeviceToDevice, s), "copy");
-      hipLaunchKernelGGL(brick_cells_kernel, dim3(grid_for(nc)), dim3(kT), 0, s, g, bk, nc, cells, rank_grid, sflag,
-                         d_bid, c->d_brick_cell_off, runs, c->d_brick_cell_loc, c->d_brick_cell_face,
-                         c->d_brick_runs);
+      hipLaunchKernelGGL(brick_cells_kernel, dim3(grid_for(nc)), dim3(kT), 0, s, g, bk, nc, cells, rank_grid, d_bid,
+                         c->d_brick_cell_off, runs, c->d_brick_cell_loc, c->d_brick_cell_face, c->d_brick_runs);
     }
     if (nf > 0)
       hipLaunchKernelGGL(brick_faces_kernel, dim3(grid_for(nf)), dim3(kT), 0, s, g, bk, nf, cells, rank_grid, faces,
-                         sflag, fidx, d_bid, c->d_brick_face_off, runs, xi_h, c->d_brick_face_loc, c->d_face_cell,
-                         c->d_face_code, c->d_face_xi, c->d_face_runs);
+                         sflag, fidx, d_bid, c->d_brick_face_off, c->d_brick_cell_off, runs, xi_h, c->d_brick_face_loc,
+                         c->d_brick_cell_face, c->d_face_cell, c->d_face_code, c->d_face_xi, c->d_face_runs);
     if (nrow_all > 0) {
       DS_CHECK(hipMemcpyAsync(c->d_row_base, t_row_base, sizeof(int32_t) * nrow_all, hipMemcpyDeviceToDevice, s), "copy");
       DS_CHECK(hipMemcpyAsync(c->d_row_gmask, t_row_gmask, sizeof(uint32_t) * nrow_all, hipMemcpyDeviceToDevice, s),
@@ -790,12 +792,10 @@ sbm_status device_setup_impl(sbm_ctx *c, Temps &tmp) {
     DS_CHECK(hipMemsetAsync(hmask32, 0, sizeof(uint32_t) * std::max<int64_t>(1, n_halo), s), "memset");
     DS_CHECK(hipMemsetAsync(slots, 0, 2 * sizeof(unsigned long long), s), "memset");
     int lb[3];
-    const bool limit = noalloc_brick(d, g.p, lb);
-    if (limit) {
-      const int64_t nl = lt.lx * lt.ly * lt.lz;
-      hipLaunchKernelGGL(plane_dofs_kernel, dim3(grid_for(nl)), dim3(kT), 0, s, lt, nl, lb[0] * g.p, lb[1] * g.p,
-                         lb[2] * g.p, lflag, slots + 1);
-    }
+    const bool limit = noalloc_counts(c, n_dofs) && noalloc_brick(d, g.p, lb);
+    if (limit)
+      hipLaunchKernelGGL(plane_dofs_kernel, dim3((unsigned)std::min<int64_t>((lt.ly * lt.lz + kT / 64 - 1) / (kT / 64), 1024)),
+                         dim3(kT), 0, s, lt, lb[0] * g.p, lb[1] * g.p, lb[2] * g.p, lflag, slots + 1);
     if (nrow_all > 0)
       hipLaunchKernelGGL(halo_rows_kernel, dim3(grid_for(nrow_all)), dim3(kT), 0, s, g, bk, lt, nbk, n_dofs, d_key_of,
                          lpre, c->d_row_base, c->d_row_gmask, c->d_row_bmask, hs, c->d_row_hbase, c->d_row_hend,
