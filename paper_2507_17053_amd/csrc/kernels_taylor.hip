@@ -259,10 +259,12 @@ __global__ __launch_bounds__(kTaylorThreads) void sbm_face_taylor_kernel(
 // face point at M = 1 (180 at M = 2) against 600 (2,800) when every point contracts the whole cell,
 // and no cell values in LDS.  One thread per face node and face point, EPB faces per workgroup; FP64
 // inside.  Bound by latency (five short phases); 64^3 Q4 sphere, 10,176 faces, m = 1, FP64: 32.4 -> 11.8 us.
+// (sized by degree and order: at 2.5 KB for all of them, the launch of 2D Q2 cost the host 1 us more)
+template <int N1, int M>
 struct TaylorLowTab {
-  double G[3][kMaxN1 * kMaxN1];  // G[k][q N1 + j] = l_j^(k)(g_q) / k!
-  double E[2][3][kMaxN1];        // E[s][k][j] = l_j^(k)(s) / k!
-  double g[kMaxN1], w[kMaxN1];   // Gauss points and weights
+  double G[M + 1][N1 * N1];  // G[k][q N1 + j] = l_j^(k)(g_q) / k!
+  double E[2][M + 1][N1];    // E[s][k][j] = l_j^(k)(s) / k!
+  double g[N1], w[N1];       // Gauss points and weights
 };
 
 // l_j^(k)(x) / k!, k <= 2: coefficients of prod_{l != j} (x - z_l + t) / (z_j - z_l)
@@ -278,18 +280,18 @@ void lagrange_jet(const Rules1D &r, int j, double x, double (&c)[3]) {
   }
 }
 
-TaylorLowTab make_taylor_low_tab(const Rules1D &r) {
-  TaylorLowTab t{};
-  const int n1 = r.p + 1;
+template <int N1, int M>
+TaylorLowTab<N1, M> make_taylor_low_tab(const Rules1D &r) {
+  TaylorLowTab<N1, M> t;
   double c[3];
-  for (int j = 0; j < n1; ++j) {
-    for (int q = 0; q < n1; ++q) {
+  for (int j = 0; j < N1; ++j) {
+    for (int q = 0; q < N1; ++q) {
       lagrange_jet(r, j, r.g[q], c);
-      for (int k = 0; k < 3; ++k) t.G[k][q * n1 + j] = c[k];
+      for (int k = 0; k <= M; ++k) t.G[k][q * N1 + j] = c[k];
     }
     for (int s = 0; s < 2; ++s) {
       lagrange_jet(r, j, (double)s, c);
-      for (int k = 0; k < 3; ++k) t.E[s][k][j] = c[k];
+      for (int k = 0; k <= M; ++k) t.E[s][k][j] = c[k];
     }
     t.g[j] = r.g[j];
     t.w[j] = r.w[j];
@@ -312,7 +314,7 @@ template <typename T, int D, int N1, int M>
 __global__ __launch_bounds__(kTaylorThreads) void sbm_face_taylor_low_kernel(
     int n_faces, int disc_dg, int m, const int32_t *__restrict__ face_cell, const int32_t *__restrict__ face_code,
     const double *__restrict__ face_xi, const int32_t *__restrict__ face_runs, const T *__restrict__ u,
-    T *__restrict__ fbuf, TaylorLowTab tt, double h, double sigma) {
+    T *__restrict__ fbuf, TaylorLowTab<N1, M> tt, double h, double sigma) {
   constexpr int NP = D == 3 ? N1 * N1 : N1, NB = NP * N1, EPB = low_faces_per_block<D, N1>(), P = N1 - 1;
   constexpr int NY = pair_ix<M>(M, 0) + 1;  // pairs (a, b) with a + b <= M
   __shared__ double sG[M + 1][N1 * N1], sE[2][M + 1][N1], sg[N1], sw[N1];
@@ -543,11 +545,11 @@ hipError_t taylor_faces(const sbm_ctx *c, const T *u, T *fbuf, hipStream_t s) {
   if (c->taylor_m <= 1)
     hipLaunchKernelGGL((sbm_face_taylor_low_kernel<T, D, N1, 1>), grid, block, 0, s, nf, c->disc == SBM_DG, c->taylor_m,
                        c->d_face_cell, c->d_face_code, c->d_face_xi, c->d_face_runs, u, fbuf,
-                       make_taylor_low_tab(c->rules), c->h, c->sigma_gamma);
+                       make_taylor_low_tab<N1, 1>(c->rules), c->h, c->sigma_gamma);
   else if (c->taylor_m == 2)
     hipLaunchKernelGGL((sbm_face_taylor_low_kernel<T, D, N1, 2>), grid, block, 0, s, nf, c->disc == SBM_DG, c->taylor_m,
                        c->d_face_cell, c->d_face_code, c->d_face_xi, c->d_face_runs, u, fbuf,
-                       make_taylor_low_tab(c->rules), c->h, c->sigma_gamma);
+                       make_taylor_low_tab<N1, 2>(c->rules), c->h, c->sigma_gamma);
   else
     hipLaunchKernelGGL((sbm_face_taylor_kernel<T, D, N1, N1>), dim3(nf), dim3(NT), 0, s, nf, c->disc == SBM_DG,
                        c->taylor_m, c->d_face_cell, c->d_face_code, c->d_face_xi, c->d_runs, u, fbuf,
