@@ -1840,92 +1840,67 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
   // surrogate faces (-2 - nbr): the rows of their (Rv, Rg), in face order.  The thread holds the
   // line along the last axis, so a face of another axis meets it in one node line of the face.
   constexpr int aL = D - 1;
-  // Few cells: every load ahead of the first use (256 registers at most), the faces' also where there is
+  // Few cells: every load ahead of the first use (192 registers at most), the faces' also where there is
   // none.  Axis after axis and face after face they took 3D Q3, 7 cells, FP64, 7.9 us on the device against
   // 6.5 (replayed apply), 3D Q2, 373 cells, 7.7 against 6.2.
-  constexpr bool AHEAD = EPB < C::full() && ((3 * D + 4 * (D - 1)) * N1 + 4) * sizeof(T) <= 1024;
+  constexpr bool AHEAD = EPB < C::full() && ((3 * D + 4 * (D - 1)) * N1 + 4) * sizeof(T) <= 768;
   T rv[2 * D][N1], rg[2 * D][N1];
-  auto load_face = [&](int code) {
-    const bool has = use_sbm && nbs[code] < -1;
-    const T *Rv = has ? fbuf + (int64_t)(-2 - nbs[code]) * 2 * NP : u;  // (u has a cell's values at least)
-    if ((code >> 1) == aL) {
-      rv[code][0] = Rv[t];
-      rg[code][0] = Rv[NP + t];
-    } else {
-      const int n0 = (D == 3) ? ((code >> 1) == 0 ? t1 : t0) : 0;
-#pragma unroll
-      for (int i = 0; i < N1; ++i) {
-        rv[code][i] = Rv[(D == 3) ? n0 + N1 * i : i];
-        rg[code][i] = Rv[NP + ((D == 3) ? n0 + N1 * i : i)];
-      }
-    }
-  };
-  auto face_rows = [&](int code) {
-    if (!use_sbm || nbs[code] >= -1) return;
-    const int a = code >> 1, s = code & 1;
-    if (a == aL) {
-#pragma unroll
-      for (int i = 0; i < N1; ++i) out[i] += (i == s * P ? rv[code][0] : T(0)) + (s ? tab.D1[i] : tab.D0[i]) * rg[code][0];
-    } else {
-      const int ia = a == 0 ? t0 : t1;  // the line's place along the face's normal
-      T dia = T(0);
-#pragma unroll
-      for (int i = 0; i < N1; ++i) dia = i == ia ? (s ? tab.D1[i] : tab.D0[i]) : dia;
-#pragma unroll
-      for (int i = 0; i < N1; ++i) out[i] += (ia == s * P ? rv[code][i] : T(0)) + dia * rg[code][i];
-    }
-  };
   if constexpr (AHEAD) {
 #pragma unroll
-    for (int code = 0; code < 2 * D; ++code) load_face(code);
+    for (int code = 0; code < 2 * D; ++code) {
+      const bool has = use_sbm && nbs[code] < -1;
+      const T *Rv = has ? fbuf + (int64_t)(-2 - nbs[code]) * 2 * NP : u;  // (u has a cell's values at least)
+      const int a = code >> 1, n0 = a == aL ? t : (D == 3 ? (a == 0 ? t1 : t0) : 0);
+#pragma unroll
+      for (int i = 0; i < (a == aL ? 1 : N1); ++i) {
+        rv[code][i] = Rv[n0 + (D == 3 ? N1 * i : i)];
+        rg[code][i] = Rv[NP + n0 + (D == 3 ? N1 * i : i)];
+      }
+    }
   }
   if (use_int) {
     const int64_t own = (int64_t)(act ? cell : 0) * NB;
-    auto load = [&](int a, T (&x)[N1], T (&l)[N1], T (&r)[N1]) {
+    T xs[AHEAD ? D : 1][N1], ls[AHEAD ? D : 1][N1], rs[AHEAD ? D : 1][N1];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int a = 0; a < D; ++a)
+#pragma unroll
+        for (int i = 0; i < N1; ++i) {
+          xs[a][i] = u[own + g0[a] + i * gs[a]];
+          ls[a][i] = u[(nbs[2 * a] >= 0 ? (int64_t)nbs[2 * a] * NB : own) + g0[a] + i * gs[a]];
+          rs[a][i] = u[(nbs[2 * a + 1] >= 0 ? (int64_t)nbs[2 * a + 1] * NB : own) + g0[a] + i * gs[a]];
+        }
+#pragma unroll
+      for (int a = 0; a < D; ++a)
+#pragma unroll
+        for (int i = 0; i < N1; ++i) {
+          settle(xs[a][i]);
+          settle(ls[a][i]);
+          settle(rs[a][i]);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
       const bool has_l = nbs[2 * a] >= 0, has_r = nbs[2 * a + 1] >= 0;
       // (a missing neighbour reads the cell itself; what is made of it is dropped)
       const T *up = u + own + g0[a];
       const T *lp = u + (has_l ? (int64_t)nbs[2 * a] * NB : own) + g0[a];
       const T *rp = u + (has_r ? (int64_t)nbs[2 * a + 1] * NB : own) + g0[a];
+      T x[N1], l[N1], r[N1], w[N1];
 #pragma unroll
       for (int i = 0; i < N1; ++i) {
-        x[i] = up[i * gs[a]];
-        l[i] = lp[i * gs[a]];
-        r[i] = rp[i * gs[a]];
+        x[i] = AHEAD ? xs[AHEAD ? a : 0][i] : up[i * gs[a]];
+        l[i] = AHEAD ? ls[AHEAD ? a : 0][i] : lp[i * gs[a]];
+        r[i] = AHEAD ? rs[AHEAD ? a : 0][i] : rp[i * gs[a]];
       }
-    };
-    auto line = [&](int a, const T (&x)[N1], const T (&l)[N1], const T (&r)[N1]) {
-      T w[N1];
-      dg_line<T, N1>(tab, sh, x, nbs[2 * a] >= 0, l, nbs[2 * a + 1] >= 0, r, w);
+      dg_line<T, N1>(tab, sh, x, has_l, l, has_r, r, w);
       T *dst = (a == 0 ? A : (a == 1 ? B : Z)) + s0[a];
 #pragma unroll
       for (int i = 0; i < N1; ++i) dst[i * ss[a]] = w[i];
-    };
-    if constexpr (AHEAD) {
-      T x[D][N1], l[D][N1], r[D][N1];
-#pragma unroll
-      for (int a = 0; a < D; ++a) load(a, x[a], l[a], r[a]);
-#pragma unroll
-      for (int a = 0; a < D; ++a)
-#pragma unroll
-        for (int i = 0; i < N1; ++i) {
-          settle(x[a][i]);
-          settle(l[a][i]);
-          settle(r[a][i]);
-        }
-#pragma unroll
-      for (int a = 0; a < D; ++a) line(a, x[a], l[a], r[a]);
-    } else {
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        T x[N1], l[N1], r[N1];
-        load(a, x, l, r);
-        line(a, x, l, r);
-      }
     }
     C::sync();
     auto sweep = [&](T *tile, int a) {  // the tile's line t along axis a times M, in place
-      T x[N1], y[N1];
+      T x[N1], y[N1] = {};
 #pragma unroll
       for (int i = 0; i < N1; ++i) x[i] = tile[s0[a] + i * ss[a]];
       eo_mul<T, N1>(tab.EM, tab.OM, x, y);
@@ -1938,7 +1913,7 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
       sweep(Z, 0);
       C::sync();
       sweep(Z, 1);
-      T x[N1], y[N1];
+      T x[N1], y[N1] = {};
 #pragma unroll
       for (int i = 0; i < N1; ++i) x[i] = A[s0[2] + i * ss[2]] + B[s0[2] + i * ss[2]];
       eo_mul<T, N1>(tab.EM, tab.OM, x, y);
@@ -1947,7 +1922,7 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
       for (int i = 0; i < N1; ++i) out[i] = scale * (y[i] + Z[s0[2] + i * ss[2]]);
     } else {
       sweep(B, 0);
-      T x[N1], y[N1];
+      T x[N1], y[N1] = {};
 #pragma unroll
       for (int i = 0; i < N1; ++i) x[i] = A[s0[1] + i * ss[1]];
       eo_mul<T, N1>(tab.EM, tab.OM, x, y);
@@ -1957,13 +1932,34 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
     }
   }
   if (!act) return;
+  if (use_sbm) {
 #pragma unroll
-  for (int code = 0; code < 2 * D; ++code) {
-    if constexpr (!AHEAD) {
-      if (!use_sbm || nbs[code] >= -1) continue;
-      load_face(code);
+    for (int code = 0; code < 2 * D; ++code) {
+      if (nbs[code] >= -1) continue;
+      const int a = code >> 1, s = code & 1;
+      const T *Rv = fbuf + (int64_t)(-2 - nbs[code]) * 2 * NP, *Rg = Rv + NP;
+      if (a == aL) {
+        const T rv0 = AHEAD ? rv[code][0] : Rv[t], rg0 = AHEAD ? rg[code][0] : Rg[t];
+#pragma unroll
+        for (int i = 0; i < N1; ++i) out[i] += (i == s * P ? rv0 : T(0)) + (s ? tab.D1[i] : tab.D0[i]) * rg0;
+      } else {
+        const int ia = a == 0 ? t0 : t1;  // the line's place along the face's normal
+        const int n0 = (D == 3) ? (a == 0 ? t1 : t0) : 0;
+        T dia = T(0);
+#pragma unroll
+        for (int i = 0; i < N1; ++i) dia = i == ia ? (s ? tab.D1[i] : tab.D0[i]) : dia;
+        if constexpr (AHEAD) {
+#pragma unroll
+          for (int i = 0; i < N1; ++i) out[i] += (ia == s * P ? rv[code][i] : T(0)) + dia * rg[code][i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < N1; ++i) {
+            const int node = (D == 3) ? n0 + N1 * i : i;
+            out[i] += (ia == s * P ? Rv[node] : T(0)) + dia * Rg[node];
+          }
+        }
+      }
     }
-    face_rows(code);
   }
   T *vp = v + (int64_t)cell * NB + g0[aL];
 #pragma unroll
