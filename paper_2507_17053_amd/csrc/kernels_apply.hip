@@ -2106,8 +2106,8 @@ struct BatchShape {
   static constexpr bool SLAB = D == 3 && NB <= 256;
   static constexpr int EFD = SLAB ? 256 / NB : epb<T, D, N1, 1, 0>();
   static constexpr int TFD = SLAB ? EFD * NB : EFD * NP;
-  static constexpr int EC = DgCell<T, D, N1>::full();  // DG cells per workgroup
-  static constexpr int TC = EC * NP;
+  // DG cells per workgroup, as for the single apply: few where full ones leave the device without two each
+  static constexpr int EC = DgCell<T, D, N1>::full(), EC1 = DgCell<T, D, N1>::few();
 };
 
 template <typename T, int D, int N1, bool CELLS>
@@ -2154,23 +2154,23 @@ __global__ __launch_bounds__(256) void sbm_face_dg_batch_kernel(const BatchItem 
                                     (T *)it->fbuf, tab, it->sc);
 }
 
-template <typename T, int D, int N1>
+template <typename T, int D, int N1, int EPB>
 __global__ __launch_bounds__(256) void dg_cell_batch_kernel(const BatchItem *__restrict__ items,
                                                             const int32_t *__restrict__ blk_item, KTab<T, N1> tab) {
-  using S = BatchShape<T, D, N1>;
   const int g = xcd_block();
   const BatchItem *it = items + blk_item[g];
   const int b = g - it->blk0[1];
   const T scale = T(D == 3 ? it->sc.h : 1.0);
-  dg_cell_body<T, D, N1, S::EC>(b, it->nc, it->nbr, (const T *)it->u, (const T *)it->fbuf, (T *)it->v, tab, it->sc,
+  dg_cell_body<T, D, N1, EPB>(b, it->nc, it->nbr, (const T *)it->u, (const T *)it->fbuf, (T *)it->v, tab, it->sc,
                                 scale, SBM_PART_ALL);
 }
 
 // Workgroups of each stage for one item (faces: 0 when the item's surrogate faces are computed
 // elsewhere, i.e. by a truncated extension).
 template <typename T, int D, int N1>
-void batch_blocks_impl(const sbm_ctx *c, bool own_faces, int32_t nb[3]) {
+void batch_blocks_impl(const sbm_ctx *c, bool own_faces, bool few, int32_t nb[3]) {
   using S = BatchShape<T, D, N1>;
+  const int ec = few ? S::EC1 : S::EC;
   const int64_t nf = own_faces ? c->n_sbm : 0;
   if (c->disc == SBM_CG) {
     nb[0] = (int32_t)((nf + S::EF - 1) / S::EF);
@@ -2178,7 +2178,7 @@ void batch_blocks_impl(const sbm_ctx *c, bool own_faces, int32_t nb[3]) {
     nb[2] = (int32_t)((c->n_halo_dofs + kHaloPerThread * 256 - 1) / (kHaloPerThread * 256));
   } else {
     nb[0] = (int32_t)((nf + S::EFD - 1) / S::EFD);
-    nb[1] = (int32_t)((c->n_cells + S::EC - 1) / S::EC);
+    nb[1] = (int32_t)((c->n_cells + ec - 1) / ec);
     nb[2] = 0;
   }
 }
@@ -2208,8 +2208,15 @@ hipError_t batch_launch_impl(const BatchGroup &g, const unsigned char *base, hip
   } else {
     if (g.nblk[0] > 0)
       hipLaunchKernelGGL((sbm_face_dg_batch_kernel<T, D, N1>), dim3(g.nblk[0]), dim3(S::TFD), 0, s, items, bi[0], tab);
-    if (g.nblk[1] > 0)
-      hipLaunchKernelGGL((dg_cell_batch_kernel<T, D, N1>), dim3(g.nblk[1]), dim3(S::TC), 0, s, items, bi[1], tab);
+    auto cells = [&](auto epb) {
+      constexpr int E = decltype(epb)::value;
+      if (g.nblk[1] > 0)
+        hipLaunchKernelGGL((dg_cell_batch_kernel<T, D, N1, E>), dim3(g.nblk[1]), dim3(E * S::NP), 0, s, items, bi[1], tab);
+    };
+    if (g.few)
+      cells(std::integral_constant<int, S::EC1>{});
+    else
+      cells(std::integral_constant<int, S::EC>{});
   }
   return hipGetLastError();
 }
@@ -2354,8 +2361,8 @@ hipError_t diag_dim(const sbm_ctx *c, T *diag, hipStream_t s) {
   }
 
 template <typename T, int D>
-bool batch_blocks_dim(const sbm_ctx *c, bool own_faces, int32_t nb[3]) {
-#define SBM_BB(N1_) (batch_blocks_impl<T, D, N1_>(c, own_faces, nb), true)
+bool batch_blocks_dim(const sbm_ctx *c, bool own_faces, bool few, int32_t nb[3]) {
+#define SBM_BB(N1_) (batch_blocks_impl<T, D, N1_>(c, own_faces, few, nb), true)
   SBM_P_SWITCH(c->p, SBM_BB)
 #undef SBM_BB
   return false;
@@ -2430,15 +2437,25 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
   std::vector<BatchItem> items(cs.size());
   std::vector<int32_t> blk[3];
   int64_t tot[3] = {0, 0, 0};
+  auto blocks = [&](const sbm_ctx *c, bool own, bool few, int32_t (&nb)[3]) {
+    return g.prec == SBM_F64 ? (c->dim == 3 ? batch_blocks_dim<double, 3>(c, own, few, nb)
+                                            : batch_blocks_dim<double, 2>(c, own, few, nb))
+                             : (c->dim == 3 ? batch_blocks_dim<float, 3>(c, own, few, nb)
+                                            : batch_blocks_dim<float, 2>(c, own, few, nb));
+  };
+  int64_t full = 0;
   for (size_t i = 0; i < cs.size(); ++i) {
     const sbm_ctx *c = cs[i];
     if (c->disc != c0->disc || c->dim != c0->dim || c->p != c0->p || c->by_cells != c0->by_cells) return hipErrorInvalidValue;
     int32_t nb[3] = {0, 0, 0};
-    const bool ok = g.prec == SBM_F64 ? (c->dim == 3 ? batch_blocks_dim<double, 3>(c, own_faces[i] != 0, nb)
-                                                     : batch_blocks_dim<double, 2>(c, own_faces[i] != 0, nb))
-                                      : (c->dim == 3 ? batch_blocks_dim<float, 3>(c, own_faces[i] != 0, nb)
-                                                     : batch_blocks_dim<float, 2>(c, own_faces[i] != 0, nb));
-    if (!ok) return hipErrorInvalidValue;
+    if (!blocks(c, false, false, nb)) return hipErrorInvalidValue;
+    full += nb[1];
+  }
+  g.few = c0->disc == SBM_DG && full < two_per_cu();
+  for (size_t i = 0; i < cs.size(); ++i) {
+    const sbm_ctx *c = cs[i];
+    int32_t nb[3] = {0, 0, 0};
+    if (!blocks(c, own_faces[i] != 0, g.few, nb)) return hipErrorInvalidValue;
     BatchItem &it = items[i];
     it.br = BrickArgs{c->d_brick_cell_off, c->d_brick_runs, c->d_brick_cell_loc, c->d_brick_face_off,
                       c->d_brick_face_loc, c->d_face_code,  c->d_brick_cell_face, c->d_row_base,       c->d_row_gmask,

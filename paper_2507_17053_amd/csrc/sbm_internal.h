@@ -178,6 +178,7 @@ struct BatchGroup {
   int prec = SBM_F64;
   int n_items = 0;
   int nblk[3] = {0, 0, 0};  // workgroups per stage: surrogate faces, cells or bricks, brick-boundary sums
+  bool few = false;  // DG: the few cells' workgroups
   size_t off_items = 0, off_blk[3] = {0, 0, 0};
 };
 hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &cs,
