@@ -33,6 +33,12 @@ struct sbm_batch_s {
   std::vector<std::vector<int>> lanes;  // per stream: its groups
   hipEvent_t fork = nullptr;
   std::vector<hipEvent_t> join;
+  // per group: a stream of its own for the bricks of the second form, where it has both
+  struct Side {
+    hipStream_t s = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+  };
+  std::vector<Side> sides;
 };
 
 namespace {
@@ -70,6 +76,11 @@ void release(sbm_batch b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   for (hipStream_t st : b->streams) (void)hipStreamDestroy(st);
   for (hipEvent_t e : b->join) (void)hipEventDestroy(e);
+  for (const sbm_batch_s::Side &d : b->sides) {
+    if (d.s) (void)hipStreamDestroy(d.s);
+    if (d.fork) (void)hipEventDestroy(d.fork);
+    if (d.join) (void)hipEventDestroy(d.join);
+  }
   if (b->fork) (void)hipEventDestroy(b->fork);
   if (b->d_tables) dev_free(b->d_tables);
   if (b->done) (void)hipEventDestroy(b->done);
@@ -118,8 +129,8 @@ sbm_status build(int n, const sbm_handle *hs, const void *const *u, void *const 
     set_error("sbm_batch_create: no device");
     return SBM_EHIP;
   }
-  // groups by (discretisation, dimension, degree, brick-kernel form), in order of first appearance
-  std::map<std::tuple<int, int, int, int>, int> gid;
+  // groups by (discretisation, dimension, degree), in order of first appearance
+  std::map<std::tuple<int, int, int>, int> gid;
   std::vector<std::vector<int>> members;
   for (int i = 0; i < n; ++i) {
     sbm_ctx *c = hs[i];
@@ -129,7 +140,7 @@ sbm_status build(int n, const sbm_handle *hs, const void *const *u, void *const 
     b->u.push_back(u[i]);
     b->v.push_back(v[i]);
     if (c->taylor_m >= 0) b->taylor.push_back(k);
-    auto key = std::make_tuple(c->disc, c->dim, c->p, (int)c->by_cells);
+    auto key = std::make_tuple(c->disc, c->dim, c->p);
     auto it = gid.find(key);
     if (it == gid.end()) {
       it = gid.emplace(key, (int)members.size()).first;
@@ -208,6 +219,24 @@ sbm_status build(int n, const sbm_handle *hs, const void *const *u, void *const 
       return SBM_EHIP;
     }
   }
+  // streams left over: the two forms of a group's bricks side by side
+  b->sides.resize(b->groups.size());
+  int left = max_streams - k;
+  bool ok = true;
+  for (size_t gi = 0; ok && gi < b->groups.size(); ++gi) {
+    const BatchGroup &g = b->groups[gi];
+    if (g.first->disc != SBM_CG || g.nblk[1] == 0 || g.nblk[3] == 0 || left < 1) continue;
+    --left;
+    sbm_batch_s::Side &d = b->sides[gi];
+    ok = hipStreamCreateWithFlags(&d.s, hipStreamNonBlocking) == hipSuccess &&
+         hipEventCreateWithFlags(&d.fork, hipEventDisableTiming) == hipSuccess &&
+         hipEventCreateWithFlags(&d.join, hipEventDisableTiming) == hipSuccess;
+  }
+  if (!ok) {
+    release(b);
+    set_error("sbm_batch_create: streams");
+    return SBM_EHIP;
+  }
   *out = b;
   return SBM_OK;
 }
@@ -221,7 +250,19 @@ hipError_t enqueue_group(sbm_batch b, int gi, hipStream_t s) {
     hipError_t e = launch_taylor_faces(c, b->u[k], c->d_fbuf, b->prec, s);
     if (e != hipSuccess) return e;
   }
-  return launch_batch_group(g, b->d_tables, s);
+  const sbm_batch_s::Side &d = b->sides[gi];
+  if (!d.join) return launch_batch_group(g, b->d_tables, s, kBatchAll);
+  hipError_t e = launch_batch_group(g, b->d_tables, s, kBatchFaces);
+  if (e == hipSuccess) e = hipEventRecord(d.fork, s);
+  if (e == hipSuccess) e = hipStreamWaitEvent(d.s, d.fork, 0);
+  if (e != hipSuccess) return e;
+  const hipError_t ec = launch_batch_group(g, b->d_tables, d.s, kBatchCells);
+  e = launch_batch_group(g, b->d_tables, s, kBatchSweeps);
+  // (joined also after a failed launch, as the batch's streams are)
+  hipError_t ej = hipEventRecord(d.join, d.s);
+  if (ej == hipSuccess) ej = hipStreamWaitEvent(s, d.join, 0);
+  if (e == hipSuccess) e = ec == hipSuccess ? ej : ec;
+  return e == hipSuccess ? launch_batch_group(g, b->d_tables, s, kBatchSums) : e;
 }
 
 // Every launch of the batch: on s, or forked over the batch's streams and joined back to s.

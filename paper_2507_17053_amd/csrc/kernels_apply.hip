@@ -476,7 +476,7 @@ struct BatchItem {
   void *v, *fbuf, *halo;
   KScal sc;
   int nf, nc, nh;
-  int blk0[3];  // first workgroup of the item in each stage's launch
+  int blk0[4];  // first workgroup of the item in each stage's launch
 };
 
 // ------------------------------------------------------------------------------------
@@ -2116,7 +2116,7 @@ __global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_batch_k
                                                                               KTab<T, N1> tab) {
   const int g = xcd_block();
   const BatchItem *it = items + blk_item[g];
-  brick_body<T, D, N1, CELLS>(g - it->blk0[1], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v, (T *)it->halo,
+  brick_body<T, D, N1, CELLS>(g - it->blk0[CELLS ? 3 : 1], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v, (T *)it->halo,
                        it->nh, tab, T(D == 3 ? it->sc.h : 1.0), SBM_PART_ALL);
 }
 
@@ -2168,41 +2168,46 @@ __global__ __launch_bounds__(256) void dg_cell_batch_kernel(const BatchItem *__r
 // Workgroups of each stage for one item (faces: 0 when the item's surrogate faces are computed
 // elsewhere, i.e. by a truncated extension).
 template <typename T, int D, int N1>
-void batch_blocks_impl(const sbm_ctx *c, bool own_faces, bool few, int32_t nb[3]) {
+void batch_blocks_impl(const sbm_ctx *c, bool own_faces, bool few, int32_t nb[4]) {
   using S = BatchShape<T, D, N1>;
   const int ec = few ? S::EC1 : S::EC;
   const int64_t nf = own_faces ? c->n_sbm : 0;
   if (c->disc == SBM_CG) {
     nb[0] = (int32_t)((nf + S::EF - 1) / S::EF);
-    nb[1] = (int32_t)c->n_bricks;
+    nb[1] = c->by_cells ? 0 : (int32_t)c->n_bricks;
+    nb[3] = c->by_cells ? (int32_t)c->n_bricks : 0;
     nb[2] = (int32_t)((c->n_halo_dofs + kHaloPerThread * 256 - 1) / (kHaloPerThread * 256));
   } else {
     nb[0] = (int32_t)((nf + S::EFD - 1) / S::EFD);
     nb[1] = (int32_t)((c->n_cells + ec - 1) / ec);
-    nb[2] = 0;
+    nb[2] = nb[3] = 0;
   }
 }
 
 template <typename T, int D, int N1>
-hipError_t batch_launch_impl(const BatchGroup &g, const unsigned char *base, hipStream_t s) {
+hipError_t batch_launch_impl(const BatchGroup &g_, const unsigned char *base, hipStream_t s, int stages) {
+  BatchGroup g = g_;
+  for (int k = 0; k < 4; ++k)
+    if (!((stages >> k) & 1)) g.nblk[k] = 0;
   using S = BatchShape<T, D, N1>;
   const KTab<T, N1> tab = make_ktab<T, N1>(g.first->rules);
   const BatchItem *items = reinterpret_cast<const BatchItem *>(base + g.off_items);
-  const int32_t *bi[3];
-  for (int k = 0; k < 3; ++k) bi[k] = reinterpret_cast<const int32_t *>(base + g.off_blk[k]);
+  const int32_t *bi[4];
+  for (int k = 0; k < 4; ++k) bi[k] = reinterpret_cast<const int32_t *>(base + g.off_blk[k]);
   if (g.first->disc == SBM_CG) {
     if (g.nblk[0] > 0)
       hipLaunchKernelGGL((sbm_face_cg_batch_kernel<T, D, N1, S::EF>), dim3(g.nblk[0]), dim3(S::EF * S::NP), 0, s,
                          items, bi[0], tab);
-    auto bricks = [&](auto by_cells) {
+    // the bricks of either form: two launches between one of the faces and one of the boundary sums (a
+    // chain of its own for each form took 110 against 99 us for 6 balls of 16^3 to 52^3 Q4, FP64)
+    auto bricks = [&](auto by_cells, int k) {
       constexpr bool CELLS = decltype(by_cells)::value;
-      if (g.nblk[1] > 0)
-        hipLaunchKernelGGL((brick_batch_kernel<T, D, N1, CELLS>), dim3(g.nblk[1]), dim3(BrickCfg<T, D, N1, CELLS>::NT),
-                           0, s, items, bi[1], tab);
+      if (g.nblk[k] > 0)
+        hipLaunchKernelGGL((brick_batch_kernel<T, D, N1, CELLS>), dim3(g.nblk[k]), dim3(BrickCfg<T, D, N1, CELLS>::NT),
+                           0, s, items, bi[k], tab);
     };
-    if (g.first->by_cells) bricks(std::true_type{});
-    if constexpr (has_sweeps<D, N1>())
-      if (!g.first->by_cells) bricks(std::false_type{});
+    if constexpr (has_sweeps<D, N1>()) bricks(std::false_type{}, 1);
+    bricks(std::true_type{}, 3);
     if (g.nblk[2] > 0)
       hipLaunchKernelGGL((halo_reduce_batch_kernel<T, D>), dim3(g.nblk[2]), dim3(256), 0, s, items, bi[2]);
   } else {
@@ -2361,7 +2366,7 @@ hipError_t diag_dim(const sbm_ctx *c, T *diag, hipStream_t s) {
   }
 
 template <typename T, int D>
-bool batch_blocks_dim(const sbm_ctx *c, bool own_faces, bool few, int32_t nb[3]) {
+bool batch_blocks_dim(const sbm_ctx *c, bool own_faces, bool few, int32_t nb[4]) {
 #define SBM_BB(N1_) (batch_blocks_impl<T, D, N1_>(c, own_faces, few, nb), true)
   SBM_P_SWITCH(c->p, SBM_BB)
 #undef SBM_BB
@@ -2369,8 +2374,8 @@ bool batch_blocks_dim(const sbm_ctx *c, bool own_faces, bool few, int32_t nb[3])
 }
 
 template <typename T, int D>
-hipError_t batch_launch_dim(const BatchGroup &g, const unsigned char *base, hipStream_t s) {
-#define SBM_BL(N1_) batch_launch_impl<T, D, N1_>(g, base, s)
+hipError_t batch_launch_dim(const BatchGroup &g, const unsigned char *base, hipStream_t s, int stages) {
+#define SBM_BL(N1_) batch_launch_impl<T, D, N1_>(g, base, s, stages)
   SBM_P_SWITCH(g.first->p, SBM_BL)
 #undef SBM_BL
   return hipErrorInvalidValue;
@@ -2435,9 +2440,9 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
   g.first = c0;
   g.n_items = (int)cs.size();
   std::vector<BatchItem> items(cs.size());
-  std::vector<int32_t> blk[3];
-  int64_t tot[3] = {0, 0, 0};
-  auto blocks = [&](const sbm_ctx *c, bool own, bool few, int32_t (&nb)[3]) {
+  std::vector<int32_t> blk[4];
+  int64_t tot[4] = {0, 0, 0, 0};
+  auto blocks = [&](const sbm_ctx *c, bool own, bool few, int32_t (&nb)[4]) {
     return g.prec == SBM_F64 ? (c->dim == 3 ? batch_blocks_dim<double, 3>(c, own, few, nb)
                                             : batch_blocks_dim<double, 2>(c, own, few, nb))
                              : (c->dim == 3 ? batch_blocks_dim<float, 3>(c, own, few, nb)
@@ -2446,15 +2451,15 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
   int64_t full = 0;
   for (size_t i = 0; i < cs.size(); ++i) {
     const sbm_ctx *c = cs[i];
-    if (c->disc != c0->disc || c->dim != c0->dim || c->p != c0->p || c->by_cells != c0->by_cells) return hipErrorInvalidValue;
-    int32_t nb[3] = {0, 0, 0};
+    if (c->disc != c0->disc || c->dim != c0->dim || c->p != c0->p) return hipErrorInvalidValue;
+    int32_t nb[4] = {0, 0, 0, 0};
     if (!blocks(c, false, false, nb)) return hipErrorInvalidValue;
     full += nb[1];
   }
   g.few = c0->disc == SBM_DG && full < two_per_cu();
   for (size_t i = 0; i < cs.size(); ++i) {
     const sbm_ctx *c = cs[i];
-    int32_t nb[3] = {0, 0, 0};
+    int32_t nb[4] = {0, 0, 0, 0};
     if (!blocks(c, own_faces[i] != 0, g.few, nb)) return hipErrorInvalidValue;
     BatchItem &it = items[i];
     it.br = BrickArgs{c->d_brick_cell_off, c->d_brick_runs, c->d_brick_cell_loc, c->d_brick_face_off,
@@ -2475,7 +2480,7 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
     it.nf = (int)c->n_sbm;
     it.nc = (int)c->n_cells;
     it.nh = (int)c->n_halo_dofs;
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 4; ++k) {
       it.blk0[k] = (int)tot[k];
       blk[k].insert(blk[k].end(), (size_t)nb[k], (int32_t)i);
       tot[k] += nb[k];
@@ -2489,18 +2494,18 @@ hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &
     return off;
   };
   g.off_items = put(items.data(), items.size() * sizeof(BatchItem));
-  for (int k = 0; k < 3; ++k) {
+  for (int k = 0; k < 4; ++k) {
     g.nblk[k] = (int)tot[k];
     g.off_blk[k] = put(blk[k].data(), blk[k].size() * sizeof(int32_t));
   }
   return hipSuccess;
 }
 
-hipError_t launch_batch_group(const BatchGroup &g, const void *base, hipStream_t s) {
+hipError_t launch_batch_group(const BatchGroup &g, const void *base, hipStream_t s, int stages) {
   const unsigned char *b = static_cast<const unsigned char *>(base);
   if (g.prec == SBM_F64)
-    return g.first->dim == 3 ? batch_launch_dim<double, 3>(g, b, s) : batch_launch_dim<double, 2>(g, b, s);
-  return g.first->dim == 3 ? batch_launch_dim<float, 3>(g, b, s) : batch_launch_dim<float, 2>(g, b, s);
+    return g.first->dim == 3 ? batch_launch_dim<double, 3>(g, b, s, stages) : batch_launch_dim<double, 2>(g, b, s, stages);
+  return g.first->dim == 3 ? batch_launch_dim<float, 3>(g, b, s, stages) : batch_launch_dim<float, 2>(g, b, s, stages);
 }
 
 hipError_t launch_apply(const sbm_ctx *c, const void *u, void *v, int prec, int parts, hipStream_t s,

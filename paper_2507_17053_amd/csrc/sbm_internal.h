@@ -177,15 +177,18 @@ struct BatchGroup {
   const sbm_ctx *first = nullptr;
   int prec = SBM_F64;
   int n_items = 0;
-  int nblk[3] = {0, 0, 0};  // workgroups per stage: surrogate faces, cells or bricks, brick-boundary sums
+  // workgroups per stage: surrogate faces, cells or bricks by sweeps, brick-boundary sums, bricks by cells
+  int nblk[4] = {0, 0, 0, 0};
   bool few = false;  // DG: the few cells' workgroups
-  size_t off_items = 0, off_blk[3] = {0, 0, 0};
+  size_t off_items = 0, off_blk[4] = {0, 0, 0, 0};
 };
 hipError_t batch_group_build(BatchGroup &g, const std::vector<const sbm_ctx *> &cs,
                              const std::vector<const void *> &u, const std::vector<void *> &v,
                              const std::vector<int> &own_faces, std::vector<unsigned char> &image);
-// Launches a group's stages; base = device address of the plan's tables (the uploaded image).
-hipError_t launch_batch_group(const BatchGroup &g, const void *base, hipStream_t s);
+// Launches a group's stages, or some of them; base = device address of the plan's tables (the uploaded
+// image).
+enum { kBatchFaces = 1, kBatchSweeps = 2, kBatchSums = 4, kBatchCells = 8, kBatchAll = 15 };
+hipError_t launch_batch_group(const BatchGroup &g, const void *base, hipStream_t s, int stages);
 // The truncated extension's surrogate-face results (Rv, Rg per face node) of u into fbuf
 // (kernels_taylor.hip); nothing to do for an operator without surrogate faces.
 hipError_t launch_taylor_faces(const sbm_ctx *c, const void *u, void *fbuf, int prec, hipStream_t s);

@@ -1,8 +1,10 @@
-"""DG batches by both workgroup sizes: every result is bitwise the single apply's, replayed on new
-inputs."""
+"""One batch over CG operators whose bricks take different forms (cell by cell, lattice sweeps) at one
+degree, with the full and a truncated extension, and DG batches by both workgroup sizes: every result is
+bitwise the single apply's, on one stream, on several, and replayed on new inputs."""
 
 import pytest
 
+from layout_util import brick_form
 from paper_2507_17053_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -28,6 +30,20 @@ def _check(ops, dtype, streams, graph):
                     o.apply(u, ref)
                     torch.cuda.synchronize()
                     assert torch.equal(v, ref), (o.n_dofs, rep)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("d,p,ns", [(3, 4, (12, 44, 20)), (3, 8, (6, 30)), (2, 3, (20, 180, 60)), (2, 1, (180, 9))],
+                         ids=lambda v: str(v))
+def test_batch_of_both_brick_forms(d, p, ns, dtype):
+    ops = [sbm.Operator(d, n, -1.0, 1.0, inputs.sphere((0.02, -0.01, 0.03)[:d], 0.9), p, taylor_order=o)
+           for n in ns for o in (None, 1)]
+    print(f"case d={d} p={p} cells={[o.n_cells for o in ops]} dtype={dtype}", flush=True)
+    assert {brick_form(o) for o in ops} == {"cells", "sweeps"}
+    for streams, graph in ((1, False), (4, True)):
+        _check(ops, dtype, streams, graph)
+    for o in ops:
+        o.close()
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
