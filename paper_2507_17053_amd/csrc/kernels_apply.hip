@@ -555,17 +555,34 @@ constexpr bool has_sweeps() {
   return kCellsMax[D - 2][N1 - 1] != kAll;
 }
 
-// Bricks by cell places, (p+1)^(d-1) threads each
-template <typename T, int D, int N1>
+// Bricks by cell places, (p+1)^(d-1) threads each, all at once or (SPLIT > 1) a part of the brick's cells
+// at a time
+template <typename T, int D, int N1, int SPLIT = 1>
 struct TileBrickCfg {
   static constexpr int DIM = D, P = N1 - 1, NP = Shape<D, N1>::NP, NB = Shape<D, N1>::NB;
   static constexpr int BX = BrickDims<D, P, false>::BX, BY = BrickDims<D, P, false>::BY,
                        BZ = BrickDims<D, P, false>::BZ;
   static constexpr int LX = BX * P + 1, LY = BY * P + 1, LZ = (D == 3) ? BZ * P + 1 : 1, NROWS = LY * LZ;
-  static constexpr int MAXC = BX * BY * BZ;
-  static constexpr int NW = (MAXC * NP + 63) / 64, NT = 64 * NW;
+  static constexpr int MAXC = BX * BY * BZ, PASS = MAXC / SPLIT;
+  static constexpr int NW = (PASS * NP + 63) / 64, NT = 64 * NW;
   static constexpr int TILE = NB;
 };
+
+// SPLIT of a batch of many bricks by cells (1: none), and the bricks that it takes.  3D p=4 and 5: all
+// at once four and three bricks are on a CU, and a batch of several times as many is slower than it was
+// by sweeps, which a batch may not take as its results are those of the single applies.  Prepared
+// batches of 16 balls, us by sweeps / by cells at once / in four parts, FP64 and FP32:
+//   p=4  1,531 bricks  52 / 49 / 51   40 / 38 / 39    2,664  68 / 68 / 70   50 / 53 / 49    6,139  105 / 117 / 110   74 /  88 / 76
+//   p=5    821 bricks  53 / 53 / 53   38 / 38 / 38    1,531  77 / 77 / 72   51 / 54 / 49    4,170  140 / 161 / 127   85 / 100 / 87
+// (p=6, in two parts: 8,200 bricks 155 / 151 / 167 and 89 / 92 / 97; p=7 and 8 are faster at once at any size.)
+template <int D, int N1>
+constexpr int tile_split() {
+  return D == 3 && (N1 == 5 || N1 == 6) ? 4 : 1;
+}
+template <typename T, int N1>
+constexpr int tile_split_from() {
+  return N1 == 5 ? (sizeof(T) == 8 ? 4096 : 2048) : 1024;
+}
 
 template <typename T, int N1>
 struct CellBrickCfg {
@@ -1320,6 +1337,36 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
   brick_assemble<T, C>(tiles, rows, ends, halo, nhalo);
 }
 
+// The rows of a cell's surrogate faces for its x-run t, in code order, from their (Rv, Rg) per face node:
+// cf is the cell's entry of cell_face, F the results of the brick's first face.
+template <typename T, int D, int N1>
+__device__ __forceinline__ void tile_face_rows(const KTab<T, N1> &tab, const T *__restrict__ F, int cf, int t,
+                                               T (&frow)[N1]) {
+  constexpr int P = N1 - 1, NP = Shape<D, N1>::NP;
+  const int t0 = (D == 3) ? t % N1 : t, t1 = (D == 3) ? t / N1 : 0;
+  const T *Rq = F + (int64_t)(cf >> 6) * 2 * NP;
+#pragma unroll
+  for (int code = 0; code < 2 * D; ++code) {
+    if (!((cf >> code) & 1)) continue;
+    const int a = code >> 1, s = code & 1;
+    const T *Rv = Rq, *Rg = Rq + NP;
+    Rq += 2 * NP;
+    if (a == 0) {
+      const T rv = Rv[t], rg = Rg[t];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) frow[i] += (i == s * P ? rv : T(0)) + (s ? tab.D1[i] : tab.D0[i]) * rg;
+    } else {
+      const int ia = a == 1 ? t0 : t1, n0 = (D == 3) ? N1 * (a == 1 ? t1 : t0) : 0;
+      T da = T(0);
+#pragma unroll
+      for (int i = 0; i < N1; ++i) da = i == ia ? (s ? tab.D1[i] : tab.D0[i]) : da;
+      const bool on = ia == s * P;
+#pragma unroll
+      for (int i = 0; i < N1; ++i) frow[i] += (on ? Rv[n0 + i] : T(0)) + da * Rg[n0 + i];
+    }
+  }
+}
+
 // ------------------------------------------------------------------------------------
 // Small operators of 3D p >= 4 and of 2D: all of a brick's cell places at once, (p+1)^(d-1) threads
 // each, two tiles of LDS per place; every lattice point then sums its cells' values as it is stored.
@@ -1363,30 +1410,8 @@ __device__ __forceinline__ void tile_body(const int brick, BrickArgs br, const T
   T frow[N1];
 #pragma unroll
   for (int i = 0; i < N1; ++i) frow[i] = T(0);
-  if ((parts & SBM_PART_SBM_FACES) && (info >> 1)) {
-    const int cf = info >> 1;
-    const T *Rq = fbuf + (int64_t)(f0 + (cf >> 6)) * 2 * NP;
-#pragma unroll
-    for (int code = 0; code < 2 * D; ++code) {
-      if (!((cf >> code) & 1)) continue;
-      const int a = code >> 1, s = code & 1;
-      const T *Rv = Rq, *Rg = Rq + NP;
-      Rq += 2 * NP;
-      if (a == 0) {
-        const T rv = Rv[t], rg = Rg[t];
-#pragma unroll
-        for (int i = 0; i < N1; ++i) frow[i] += (i == s * P ? rv : T(0)) + (s ? tab.D1[i] : tab.D0[i]) * rg;
-      } else {
-        const int ia = a == 1 ? t0 : t1, n0 = (D == 3) ? N1 * (a == 1 ? t1 : t0) : 0;
-        T da = T(0);
-#pragma unroll
-        for (int i = 0; i < N1; ++i) da = i == ia ? (s ? tab.D1[i] : tab.D0[i]) : da;
-        const bool on = ia == s * P;
-#pragma unroll
-        for (int i = 0; i < N1; ++i) frow[i] += (on ? Rv[n0 + i] : T(0)) + da * Rg[n0 + i];
-      }
-    }
-  }
+  if ((parts & SBM_PART_SBM_FACES) && (info >> 1))
+    tile_face_rows<T, D, N1>(tab, fbuf + (int64_t)f0 * 2 * NP, info >> 1, t, frow);
   T *const A = smem + (place ? le : 0) * C::TILE, *const B = smem + C::MAXC * C::TILE + (place ? le : 0) * NB;
   kron_cell<T, D, N1>(tab, t, x, A, B, scale, out, work, work);
   if (place) {  // (the thread's own x-run of the tile, which it alone has read)
@@ -1394,6 +1419,67 @@ __device__ __forceinline__ void tile_body(const int brick, BrickArgs br, const T
     for (int i = 0; i < N1; ++i) A[N1 * t + i] = out[i] + frow[i];
   }
   __syncthreads();
+  brick_assemble<T, C>(smem, rows, ends, halo, nhalo);
+}
+
+// The same bricks, cells and sums, bit for bit, with PASS of the brick's cells at a time, for batches
+// whose bricks fill the device several times over (tile_split): a quarter of the threads and half of the
+// tiles of all places at once, so that two to three times as many bricks are on the device, the next
+// cells' values under way while a pass is swept, and no work for places without a cell.
+template <typename T, int N1, int SPLIT>
+__device__ __forceinline__ void tile_split_body(const int brick, BrickArgs br, const T *__restrict__ fbuf,
+                                                const T *__restrict__ u, T *__restrict__ v, T *__restrict__ halo,
+                                                int nhalo, KTab<T, N1> tab, T scale) {
+  using C = TileBrickCfg<T, 3, N1, SPLIT>;
+  constexpr int P = N1 - 1, NP = C::NP, NB = C::NB, BX = C::BX, BY = C::BY, LX = C::LX, LY = C::LY, PASS = C::PASS;
+  __shared__ T smem[C::MAXC * C::TILE + PASS * NB];
+  __shared__ BrickRows<T, C> rows;
+  __shared__ int32_t s_cell[C::MAXC];  // per cell: 64 x its faces (cell_face) + its place
+  static_assert(C::MAXC <= 64, "a place fits six bits");
+  const int tid = threadIdx.x;
+  const int c0 = br.cell_off[brick], nc = br.cell_off[brick + 1] - c0;
+  const T *const F = fbuf + (int64_t)br.face_off[brick] * 2 * NP;
+  if (tid < nc) {
+    const int loc = br.cell_loc[c0 + tid];
+    s_cell[tid] = br.cell_face[c0 + tid] * 64 + (loc / (LX * LY) / P * BY + (loc / LX % LY) / P) * BX + (loc % LX) / P;
+  }
+  int32_t ends[2] = {0, 0};
+  rows.fill(br, brick, nc == C::MAXC, v, halo, nhalo, ends);
+  if (nc < C::MAXC)
+    for (int i = tid; i < C::MAXC * C::TILE; i += C::NT) smem[i] = T(0);
+  __syncthreads();
+  const int le = tid / NP, t = tid - le * NP, t0 = t % N1, t1 = t / N1;
+  auto fetch = [&](int c, int &cell, T (&x)[N1]) {
+    const bool on = le < PASS && c < nc;
+    cell = on ? s_cell[c] : -1;
+    const int pl = on ? cell & 63 : 0;
+#pragma unroll
+    for (int k = 0; k < N1; ++k)
+      x[k] = on ? u[(int64_t)rows.run(pl % BX, pl / BX % BY, pl / (BX * BY), t1, k) + t0] : T(0);
+  };
+  int cell, next = -1;
+  T x[N1], y[N1] = {};
+  fetch(le, cell, x);
+  for (int c = 0; c < nc; c += PASS) {
+    if (c + PASS < nc) fetch(c + PASS + le, next, y);
+    const bool on = cell >= 0;
+    T out[N1], frow[N1];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) out[i] = frow[i] = T(0);
+    if (on && (cell >> 6)) tile_face_rows<T, 3, N1>(tab, F, cell >> 6, t, frow);
+    T *const A = smem + (on ? cell & 63 : 0) * C::TILE, *const B = smem + C::MAXC * C::TILE + (on ? le : 0) * NB;
+    kron_cell<T, 3, N1>(tab, t, x, A, B, scale, out, on, on);
+#pragma unroll
+    for (int i = 0; i < N1; ++i) settle(out[i]);  // (rounded before the sum, as in tile_body)
+    if (on) {
+#pragma unroll
+      for (int i = 0; i < N1; ++i) A[N1 * t + i] = out[i] + frow[i];
+    }
+    __syncthreads();
+    cell = next;
+#pragma unroll
+    for (int i = 0; i < N1; ++i) x[i] = y[i];
+  }
   brick_assemble<T, C>(smem, rows, ends, halo, nhalo);
 }
 
@@ -2110,6 +2196,15 @@ struct BatchShape {
   static constexpr int EC = DgCell<T, D, N1>::full(), EC1 = DgCell<T, D, N1>::few();
 };
 
+template <typename T, int D, int N1>
+__global__ __launch_bounds__((TileBrickCfg<T, D, N1, tile_split<D, N1>()>::NT)) void brick_split_batch_kernel(
+    const BatchItem *__restrict__ items, const int32_t *__restrict__ blk_item, KTab<T, N1> tab) {
+  const int g = xcd_block();
+  const BatchItem *it = items + blk_item[g];
+  tile_split_body<T, N1, tile_split<D, N1>()>(g - it->blk0[3], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v,
+                                              (T *)it->halo, it->nh, tab, T(it->sc.h));
+}
+
 template <typename T, int D, int N1, bool CELLS>
 __global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_batch_kernel(const BatchItem *__restrict__ items,
                                                                               const int32_t *__restrict__ blk_item,
@@ -2207,6 +2302,14 @@ hipError_t batch_launch_impl(const BatchGroup &g_, const unsigned char *base, hi
                            0, s, items, bi[k], tab);
     };
     if constexpr (has_sweeps<D, N1>()) bricks(std::false_type{}, 1);
+    constexpr int SPLIT = tile_split<D, N1>();
+    if constexpr (SPLIT > 1) {
+      if (g.nblk[3] > tile_split_from<T, N1>()) {
+        hipLaunchKernelGGL((brick_split_batch_kernel<T, D, N1>), dim3(g.nblk[3]), dim3(TileBrickCfg<T, D, N1, SPLIT>::NT),
+                           0, s, items, bi[3], tab);
+        g.nblk[3] = 0;
+      }
+    }
     bricks(std::true_type{}, 3);
     if (g.nblk[2] > 0)
       hipLaunchKernelGGL((halo_reduce_batch_kernel<T, D>), dim3(g.nblk[2]), dim3(256), 0, s, items, bi[2]);

@@ -47,6 +47,20 @@ def test_batch_of_both_brick_forms(d, p, ns, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("p,n,count", [(4, 36, 6), (5, 24, 8)])
+def test_batch_of_many_bricks_by_cells(p, n, count, dtype):
+    """More bricks than the device holds several times over: a part of a brick's cells at a time."""
+    ops = [sbm.Operator(3, n, -1.0, 1.0, inputs.sphere((0.02, -0.01, 0.03), 0.84 + 0.01 * k), p, taylor_order=(None, 1)[k % 2])
+           for k in range(count)]
+    bricks = sum(o.layout_stats()[0] for o in ops)
+    print(f"case p={p} bricks={bricks} dtype={dtype}", flush=True)
+    assert {brick_form(o) for o in ops} == {"cells"} and bricks > (4096 if p == 4 else 1024)
+    _check(ops, dtype, 1, True)
+    for o in ops:
+        o.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
 @pytest.mark.parametrize("d,p,ns", [(3, 2, (5, 8, 6)), (3, 2, (5, 40, 44)), (2, 8, (9, 12)), (3, 7, (4, 5))],
                          ids=lambda v: str(v))
 def test_dg_batch_of_few_and_many_cells(d, p, ns, dtype):
