@@ -920,16 +920,6 @@ __device__ __forceinline__ void sweeps_body(const int blk, BrickArgs br, const T
   // on the box boundary go to plane k = [x == 0] + 2 [y == 0] + 4 [z == 0] of the halo (the
   // brick's side of the point; bricks sharing the point differ in k), at the point's halo
   // index; halo_reduce_kernel sums the planes.
-  // The rows' ends: y fastest, as their halo indices.
-#pragma unroll
-  for (int m = 0; m < NE; ++m) {
-    const int i = tid + m * nthr, side = i >= NROWS ? 1 : 0, r = i < 2 * NROWS ? i - side * NROWS : 0;
-    const int y = r % LY, z = r / LY, x = side ? LX - 1 : 0;
-    const uint32_t bm = full ? ~0u : s_bmask[r];
-    const int plane = (side ? 0 : 1) | (y == 0 ? 2 : 0) | ((D == 3 && z == 0) ? 4 : 0);
-    const T val = acc[r * LX + x];
-    if (i < 2 * NROWS && ((bm >> x) & 1u)) halo[(int64_t)plane * nhalo + hend[m]] = val;
-  }
   // The points 0 < x < LX - 1, x fastest: stores are row-contiguous.  Each wavefront takes RPW whole
   // rows per pass, so a lane's x is fixed, and a pass only advances the row; (y, z) of the row
   // advance by a constant.  The passes are unrolled, every LDS read first, so that one wait covers
@@ -976,6 +966,17 @@ __device__ __forceinline__ void sweeps_body(const int blk, BrickArgs br, const T
         }
       }
     }
+  }
+  // The rows' ends: y fastest, as their halo indices.  (Ahead of the rows' other points they held up the
+  // stores of large 2D operators: 3692^2 Q1 FP32 apply 71.5 against 66.6 us, 1230^2 Q3 44.5 against 43.0.)
+#pragma unroll
+  for (int m = 0; m < NE; ++m) {
+    const int i = tid + m * nthr, side = i >= NROWS ? 1 : 0, r = i < 2 * NROWS ? i - side * NROWS : 0;
+    const int y = r % LY, z = r / LY, x = side ? LX - 1 : 0;
+    const uint32_t bm = full ? ~0u : s_bmask[r];
+    const int plane = (side ? 0 : 1) | (y == 0 ? 2 : 0) | ((D == 3 && z == 0) ? 4 : 0);
+    const T val = acc[r * LX + x];
+    if (i < 2 * NROWS && ((bm >> x) & 1u)) halo[(int64_t)plane * nhalo + hend[m]] = val;
   }
 }
 
