@@ -479,6 +479,44 @@ struct BatchItem {
   int blk0[4];  // first workgroup of the item in each stage's launch
 };
 
+// A pointer that a kernel reads from memory or LDS is generic to the compiler: its loads and stores are
+// flat ones, which wait on LDS too.
+template <typename T>
+using GlobalT = __attribute__((address_space(1))) T;
+
+// The item of a workgroup of a batched kernel, its pointers marked global.
+__device__ __forceinline__ BatchItem batch_item(const BatchItem *__restrict__ items, int i) {
+  BatchItem it = items[i];
+  auto global = [](auto *&p) {
+    using P = std::remove_pointer_t<std::remove_reference_t<decltype(p)>>;
+    p = (P *)(GlobalT<P> *)(uintptr_t)p;  // (the compiler drops a cast there and back)
+  };
+  global(it.br.cell_off);
+  global(it.br.runs);
+  global(it.br.cell_loc);
+  global(it.br.face_off);
+  global(it.br.face_loc);
+  global(it.br.face_code);
+  global(it.br.cell_face);
+  global(it.br.row_base);
+  global(it.br.row_gmask);
+  global(it.br.row_bmask);
+  global(it.br.row_hbase);
+  global(it.br.row_hend);
+  global(it.face_code);
+  global(it.face_runs);
+  global(it.face_cell);
+  global(it.nbr);
+  global(it.halo_dof);
+  global(it.halo_mask);
+  global(it.face_xi);
+  global(it.u);
+  global(it.v);
+  global(it.fbuf);
+  global(it.halo);
+  return it;
+}
+
 // ------------------------------------------------------------------------------------
 // CG brick kernel
 // ------------------------------------------------------------------------------------
@@ -1062,10 +1100,6 @@ struct BrickRows {
   }
 };
 
-// (a pointer read from LDS is generic otherwise, and its stores wait on LDS too)
-template <typename T>
-using GlobalT = __attribute__((address_space(1))) T;
-
 // Assembly and write-out of a brick's cells, one tile of results [z][y][x] per cell place (zero
 // where there is no cell): every lattice point sums its cells' values (z, then y, then x from the
 // low side: a fixed order) and is stored once.
@@ -1152,7 +1186,7 @@ __device__ __forceinline__ void brick_assemble(const T *tiles, const BrickRows<T
         for (int k = 0; k < CH; ++k) settle(sum[k]);
 #pragma unroll
         for (int k = 0; k < CH; ++k)
-          if ((bm[k] >> x) & 1u) ((GlobalT<T> *)dst[k])[__popc(gm[k] & below)] = sum[k];
+          if ((bm[k] >> x) & 1u) ((GlobalT<T> *)dst[k])[__popc(gm[k] & below)] = sum[k];  // (generic: see GlobalT)
       }
     }
   };
@@ -2201,9 +2235,9 @@ template <typename T, int D, int N1>
 __global__ __launch_bounds__((TileBrickCfg<T, D, N1, tile_split<D, N1>()>::NT)) void brick_split_batch_kernel(
     const BatchItem *__restrict__ items, const int32_t *__restrict__ blk_item, KTab<T, N1> tab) {
   const int g = xcd_block();
-  const BatchItem *it = items + blk_item[g];
-  tile_split_body<T, N1, tile_split<D, N1>()>(g - it->blk0[3], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v,
-                                              (T *)it->halo, it->nh, tab, T(it->sc.h));
+  const BatchItem it = batch_item(items, blk_item[g]);
+  tile_split_body<T, N1, tile_split<D, N1>()>(g - it.blk0[3], it.br, (const T *)it.fbuf, (const T *)it.u, (T *)it.v,
+                                              (T *)it.halo, it.nh, tab, T(it.sc.h));
 }
 
 template <typename T, int D, int N1, bool CELLS>
@@ -2211,17 +2245,39 @@ __global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_batch_k
                                                                               const int32_t *__restrict__ blk_item,
                                                                               KTab<T, N1> tab) {
   const int g = xcd_block();
-  const BatchItem *it = items + blk_item[g];
-  brick_body<T, D, N1, CELLS>(g - it->blk0[CELLS ? 3 : 1], it->br, (const T *)it->fbuf, (const T *)it->u, (T *)it->v, (T *)it->halo,
-                       it->nh, tab, T(D == 3 ? it->sc.h : 1.0), SBM_PART_ALL);
+  BatchItem it = batch_item(items, blk_item[g]);
+  // The sweeps of the high degrees fill the scalar registers with the 1D tables, and what does not fit is
+  // kept in lanes of vector registers: the item's pointers go to vector registers instead (3D Q6 FP64:
+  // 978 reads of such lanes of 2,967 instructions, 158 of 2,207 now).  By cells they cost 3D Q8 a resident
+  // workgroup, and the low degrees have no such spill.  With the pointers marked global, a prepared batch of
+  // one ball (disk), us, flat and scalar / now: 40^3 Q6 FP64 90.5 / 80.0, 50^3 Q5 85.1 / 80.1, 66^3 Q4 83.7 /
+  // 78.5, 30^3 Q8 113.5 / 110.1 and FP32 66.3 / 61.6, 260^2 Q6 33.7 / 30.0
+  if constexpr (!CELLS && sizeof(T) * N1 * N1 >= 256) {
+    auto vec = [](auto *&p) {
+      using P = std::remove_pointer_t<std::remove_reference_t<decltype(p)>>;
+      uintptr_t a = (uintptr_t)p;
+      settle(a);
+      p = (P *)(GlobalT<P> *)a;
+    };
+    vec(it.u);
+    vec(it.v);
+    vec(it.fbuf);
+    vec(it.halo);
+    vec(it.br.runs);
+    vec(it.br.cell_loc);
+    vec(it.br.face_loc);
+    vec(it.br.face_code);
+  }
+  brick_body<T, D, N1, CELLS>(g - it.blk0[CELLS ? 3 : 1], it.br, (const T *)it.fbuf, (const T *)it.u, (T *)it.v, (T *)it.halo,
+                       it.nh, tab, T(D == 3 ? it.sc.h : 1.0), SBM_PART_ALL);
 }
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void halo_reduce_batch_kernel(const BatchItem *__restrict__ items,
                                                                 const int32_t *__restrict__ blk_item) {
   const int g = blockIdx.x;
-  const BatchItem *it = items + blk_item[g];
-  halo_reduce_body<T, D, false>(g - it->blk0[2], it->nh, it->halo_dof, it->halo_mask, (const T *)it->halo, (T *)it->v);
+  const BatchItem it = batch_item(items, blk_item[g]);
+  halo_reduce_body<T, D, false>(g - it.blk0[2], it.nh, it.halo_dof, it.halo_mask, (const T *)it.halo, (T *)it.v);
 }
 
 template <typename T, int D, int N1, int EPB>
@@ -2229,9 +2285,9 @@ __global__ __launch_bounds__(256, 4) void sbm_face_cg_batch_kernel(const BatchIt
                                                                    const int32_t *__restrict__ blk_item,
                                                                    KTab<T, N1> tab) {
   const int g = xcd_block();
-  const BatchItem *it = items + blk_item[g];
-  sbm_face_cg_body<T, D, N1, EPB>(g - it->blk0[0], it->nf, it->face_code, it->face_runs, it->face_xi,
-                                  (const T *)it->u, (T *)it->fbuf, tab, it->sc);
+  const BatchItem it = batch_item(items, blk_item[g]);
+  sbm_face_cg_body<T, D, N1, EPB>(g - it.blk0[0], it.nf, it.face_code, it.face_runs, it.face_xi,
+                                  (const T *)it.u, (T *)it.fbuf, tab, it.sc);
 }
 
 template <typename T, int D, int N1>
@@ -2240,24 +2296,24 @@ __global__ __launch_bounds__(256) void sbm_face_dg_batch_kernel(const BatchItem 
                                                                 KTab<T, N1> tab) {
   using S = BatchShape<T, D, N1>;
   const int g = xcd_block();
-  const BatchItem *it = items + blk_item[g];
-  const int b = g - it->blk0[0];
+  const BatchItem it = batch_item(items, blk_item[g]);
+  const int b = g - it.blk0[0];
   if constexpr (S::SLAB)
-    sbm_face_slab_body<T, N1, S::EFD>(b, it->nf, it->face_cell, it->face_code, it->face_xi, (const int32_t *)nullptr,
-                                      (const T *)it->u, (T *)it->fbuf, tab, it->sc);
+    sbm_face_slab_body<T, N1, S::EFD>(b, it.nf, it.face_cell, it.face_code, it.face_xi, (const int32_t *)nullptr,
+                                      (const T *)it.u, (T *)it.fbuf, tab, it.sc);
   else
-    sbm_face_body<T, D, N1, S::EFD>(b, it->nf, it->face_cell, it->face_code, it->face_xi, (const T *)it->u,
-                                    (T *)it->fbuf, tab, it->sc);
+    sbm_face_body<T, D, N1, S::EFD>(b, it.nf, it.face_cell, it.face_code, it.face_xi, (const T *)it.u,
+                                    (T *)it.fbuf, tab, it.sc);
 }
 
 template <typename T, int D, int N1, int EPB>
 __global__ __launch_bounds__(256) void dg_cell_batch_kernel(const BatchItem *__restrict__ items,
                                                             const int32_t *__restrict__ blk_item, KTab<T, N1> tab) {
   const int g = xcd_block();
-  const BatchItem *it = items + blk_item[g];
-  const int b = g - it->blk0[1];
-  const T scale = T(D == 3 ? it->sc.h : 1.0);
-  dg_cell_body<T, D, N1, EPB>(b, it->nc, it->nbr, (const T *)it->u, (const T *)it->fbuf, (T *)it->v, tab, it->sc,
+  const BatchItem it = batch_item(items, blk_item[g]);
+  const int b = g - it.blk0[1];
+  const T scale = T(D == 3 ? it.sc.h : 1.0);
+  dg_cell_body<T, D, N1, EPB>(b, it.nc, it.nbr, (const T *)it.u, (const T *)it.fbuf, (T *)it.v, tab, it.sc,
                                 scale, SBM_PART_ALL);
 }
 
