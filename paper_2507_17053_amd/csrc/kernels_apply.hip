@@ -610,8 +610,8 @@ struct TileBrickCfg {
 // at once four and three bricks are on a CU, and a batch of several times as many is slower than it was
 // by sweeps, which a batch may not take as its results are those of the single applies.  Prepared
 // batches of 16 balls, us by sweeps / by cells at once / in four parts, FP64 and FP32:
-//   p=4  1,531 bricks  52 / 49 / 51   40 / 38 / 39    2,664  68 / 68 / 70   50 / 53 / 49    6,139  105 / 117 / 110   74 /  88 / 76
-//   p=5    821 bricks  53 / 53 / 53   38 / 38 / 38    1,531  77 / 77 / 72   51 / 54 / 49    4,170  140 / 161 / 127   85 / 100 / 87
+//   p=4  1,220 bricks  44 / 41 / 45   35 / 33 / 36    3,475  77 / 79 / 79   57 / 61 / 58    8,167  134 / 146 / 135   87 / 106 /  89
+//   p=5  1,220 bricks  67 / 64 / 62   42 / 43 / 42    2,035  89 / 93 / 83   59 / 62 / 60    5,499  186 / 210 / 166  100 / 120 / 102
 // (p=6, in two parts: 8,200 bricks 155 / 151 / 167 and 89 / 92 / 97; p=7 and 8 are faster at once at any size.)
 template <int D, int N1>
 constexpr int tile_split() {
@@ -632,9 +632,9 @@ struct CellBrickCfg {
   static constexpr int CPW = 64 / N1;                    // cells per wavefront
   static constexpr int NW = (MAXC + CPW - 1) / CPW, NT = 64 * NW;
   // The transposes between x-runs and y-lines: four planes in flight per wavefront, plane-major,
-  // cells SC apart, the rows of a plane RP apart.  They use the LDS of the wavefront's share of the
+  // cells SC apart.  They use the LDS of the wavefront's share of the
   // cells' (p+1)^3 results, which follow.  (The strides with the fewest LDS bank conflicts.)
-  static constexpr int RP = N1 == 6 ? 7 : N1, SC = N1 == 4 ? 17 : RP * N1;
+  static constexpr int SC = N1 == 4 ? 17 : NP;
   static constexpr int TILE = (NB > 4 * SC ? NB : 4 * SC) | (N1 == 4 ? 0 : 1);
 };
 
@@ -1262,16 +1262,16 @@ __device__ __forceinline__ void cells_body(const int brick, BrickArgs br, const 
         eo_combine<T, N1>(ab.ye, ab.yo, T(1), b);
 #pragma unroll
         for (int i = 0; i < N1; ++i) {
-          dst[C::RP * j + i] = a[i];
-          dst[PL + C::RP * j + i] = b[i];
+          dst[N1 * j + i] = a[i];
+          dst[PL + N1 * j + i] = b[i];
         }
       };
       auto ysweep = [&](const T *src, T (&cc)[N1], T (&e)[N1]) {  // c = M a, e = K a + M b of y-line j
         T a[N1], b[N1];
 #pragma unroll
         for (int i = 0; i < N1; ++i) {
-          a[i] = src[C::RP * i + j];
-          b[i] = src[PL + C::RP * i + j];
+          a[i] = src[N1 * i + j];
+          b[i] = src[PL + N1 * i + j];
         }
         const EvenOdd<T, N1> ea(a), eb(b);
         EOAcc<T, N1> ac, ae;
@@ -1758,13 +1758,10 @@ __global__ __launch_bounds__(256) void sbm_face_kernel(int n_faces, const int32_
 // sums are added in slab order, as in sbm_face_eval; the face-node phases (normal
 // derivative, Gauss interpolation, integration) run in every slab with identical results;
 // slab 0 stores the face's (Rv, Rg) as sbm_face_kernel does.  For p <= 5 ((p+1)^3 <= 256).
-// face_runs != nullptr (CG): the cell's values are gathered through its x-run bases
-// (face_runs[f][t] is the first DoF of run t); otherwise (DG) the cell block is contiguous.
 template <typename T, int N1, int EPB>
 __device__ __forceinline__ void sbm_face_slab_body(const int blk, int n_faces, const int32_t *__restrict__ face_cell,
                                                             const int32_t *__restrict__ face_code,
                                                             const double *__restrict__ face_xi,
-                                                            const int32_t *__restrict__ face_runs,
                                                             const T *__restrict__ u, T *__restrict__ fbuf,
                                                             KTab<T, N1> tab, KScal sc) {
   constexpr int D = 3, NP = N1 * N1, NB = NP * N1;
@@ -1781,11 +1778,7 @@ __device__ __forceinline__ void sbm_face_slab_body(const int blk, int n_faces, c
 #pragma unroll
   for (int k = 0; k < D; ++k) xp[k] = act ? face_xi[((int64_t)f * NP + t) * D + k] : 0.0;
   const FaceAxes<D, N1> fa(act ? face_code[f] : 0);
-  if (act) {
-    const int64_t at = face_runs ? (int64_t)face_runs[(int64_t)f * NP + r / N1] + r % N1
-                                 : (int64_t)face_cell[f] * NB + r;
-    su[r] = u[at];
-  }
+  if (act) su[r] = u[(int64_t)face_cell[f] * NB + r];
   __syncthreads();
   const T h = T(sc.h), sig = T(sc.sigma_gamma);
   const T sh = (fa.s ? T(1) : T(-1)) / h;
@@ -1842,10 +1835,9 @@ template <typename T, int N1, int EPB>
 __global__ __launch_bounds__(256) void sbm_face_slab_kernel(int n_faces, const int32_t *__restrict__ face_cell,
                                                             const int32_t *__restrict__ face_code,
                                                             const double *__restrict__ face_xi,
-                                                            const int32_t *__restrict__ face_runs,
                                                             const T *__restrict__ u, T *__restrict__ fbuf,
                                                             KTab<T, N1> tab, KScal sc) {
-  sbm_face_slab_body<T, N1, EPB>(xcd_block(), n_faces, face_cell, face_code, face_xi, face_runs, u, fbuf, tab, sc);
+  sbm_face_slab_body<T, N1, EPB>(xcd_block(), n_faces, face_cell, face_code, face_xi, u, fbuf, tab, sc);
 }
 
 // ------------------------------------------------------------------------------------
@@ -2021,7 +2013,7 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
     }
     C::sync();
     auto sweep = [&](T *tile, int a) {  // the tile's line t along axis a times M, in place
-      T x[N1], y[N1] = {};
+      T x[N1], y[N1];
 #pragma unroll
       for (int i = 0; i < N1; ++i) x[i] = tile[s0[a] + i * ss[a]];
       eo_mul<T, N1>(tab.EM, tab.OM, x, y);
@@ -2034,7 +2026,7 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
       sweep(Z, 0);
       C::sync();
       sweep(Z, 1);
-      T x[N1], y[N1] = {};
+      T x[N1], y[N1];
 #pragma unroll
       for (int i = 0; i < N1; ++i) x[i] = A[s0[2] + i * ss[2]] + B[s0[2] + i * ss[2]];
       eo_mul<T, N1>(tab.EM, tab.OM, x, y);
@@ -2043,7 +2035,7 @@ __device__ __forceinline__ void dg_cell_body(const int blk, int n_cells, const i
       for (int i = 0; i < N1; ++i) out[i] = scale * (y[i] + Z[s0[2] + i * ss[2]]);
     } else {
       sweep(B, 0);
-      T x[N1], y[N1] = {};
+      T x[N1], y[N1];
 #pragma unroll
       for (int i = 0; i < N1; ++i) x[i] = A[s0[1] + i * ss[1]];
       eo_mul<T, N1>(tab.EM, tab.OM, x, y);
@@ -2179,11 +2171,10 @@ hipError_t apply_impl(const sbm_ctx *c, const T *u, T *v, int parts, hipStream_t
         constexpr int NB = Shape<D, N1>::NB, E = 256 / NB, E1 = (64 / NB < 1) ? 1 : 64 / NB;
         if ((nf + E - 1) / E >= two_per_cu())
           hipLaunchKernelGGL((sbm_face_slab_kernel<T, N1, E>), dim3((nf + E - 1) / E), dim3(E * NB), 0, s, nf,
-                             c->d_face_cell, c->d_face_code, c->d_face_xi, (const int32_t *)nullptr, u, fbuf, tab, sc);
+                             c->d_face_cell, c->d_face_code, c->d_face_xi, u, fbuf, tab, sc);
         else
           hipLaunchKernelGGL((sbm_face_slab_kernel<T, N1, E1>), dim3((nf + E1 - 1) / E1), dim3(E1 * NB), 0, s,
-                             nf, c->d_face_cell, c->d_face_code, c->d_face_xi, (const int32_t *)nullptr, u, fbuf, tab,
-                             sc);
+                             nf, c->d_face_cell, c->d_face_code, c->d_face_xi, u, fbuf, tab, sc);
       } else {
         constexpr int E = epb<T, D, N1, 1, 0>(), E1 = epb_one_wave<T, D, N1, 1>();
         if ((nf + E - 1) / E >= two_per_cu())
@@ -2299,8 +2290,8 @@ __global__ __launch_bounds__(256) void sbm_face_dg_batch_kernel(const BatchItem 
   const BatchItem it = batch_item(items, blk_item[g]);
   const int b = g - it.blk0[0];
   if constexpr (S::SLAB)
-    sbm_face_slab_body<T, N1, S::EFD>(b, it.nf, it.face_cell, it.face_code, it.face_xi, (const int32_t *)nullptr,
-                                      (const T *)it.u, (T *)it.fbuf, tab, it.sc);
+    sbm_face_slab_body<T, N1, S::EFD>(b, it.nf, it.face_cell, it.face_code, it.face_xi, (const T *)it.u, (T *)it.fbuf,
+                                      tab, it.sc);
   else
     sbm_face_body<T, D, N1, S::EFD>(b, it.nf, it.face_cell, it.face_code, it.face_xi, (const T *)it.u,
                                     (T *)it.fbuf, tab, it.sc);
