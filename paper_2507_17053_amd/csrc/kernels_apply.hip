@@ -585,6 +585,11 @@ struct SweepBrickCfg {
 // (the balls hold about 0.22 n^3 cells); 2D, FP64 and FP32:
 //   p=2  16^2 10.8 ->  9.9, 10.4 ->  9.2   p=6 300^2 16.3 -> 15.3, 13.0 -> 12.0   p=8 200^2 19.2 -> 16.1, 12.9 -> 11.7
 //   p=4 512^2 17.7 -> 18.3, 13.8 -> 15.9   p=5 400^2 17.2 -> 18.1, 13.0 -> 15.0   p=8 600^2 91 -> 106, 48 -> 62
+// The form is fixed at setup, so one line holds for both precisions: below the first size at which either
+// loses, which in 3D is FP32 (p=8 at 36^3 would gain 14 % by cells in FP64 and lose 29 % in FP32).  It is
+// drawn in cells, which the caller knows: 16,384 cells are about 1,100 bricks at 3D p=4, 4,096 about 1,100
+// at p=6.  All degrees of 2D share one line, below the first that loses (p=4); p=6 at 300^2 and p=8 at 200^2
+// would still gain 6 to 16 %.
 constexpr int64_t kAll = INT64_MAX;
 constexpr int64_t kCellsMax[2][9] = {{0, 16384, 16384, 16384, 16384, 16384, 16384, 16384, 16384},
                                      {0, (int64_t)1 << 22, kAll, kAll, 16384, 8192, 4096, 8192, 4096}};
@@ -1026,11 +1031,11 @@ __device__ __forceinline__ void sweeps_body(const int blk, BrickArgs br, const T
 // cells' results go to LDS once, and every lattice point then sums its cells' values as it is
 // stored.
 // What bounds it: the latency of a brick's phases on small meshes, and with the device full half of
-// the HBM rate (150^3 Q2 FP64: 6 M DoFs in 69 us).  The lattice sweeps, which take a brick with a
-// missing cell batch by batch with a barrier for each cell and each face of a batch, spent their
-// time in those bricks: these have up to 168 cells, and small meshes hold no others (brick
-// kernel, 45^3 Q2 FP32: 28.3 -> 9.6 us; 30^3 Q1 FP64: 70 -> 8 us; 96^3 Q3 FP64: 73 -> 52 us; 150^3
-// Q2 FP64: 74 -> 69 us).  The x-runs' first DoFs come from the row descriptors: reading them from
+// the HBM rate (150^3 Q2 FP64, 5.8 M DoFs).  The lattice sweeps, which take a brick with a missing
+// cell batch by batch with a barrier for each cell and each face of a batch, spent their time in
+// those bricks: these have up to 168 cells, and small meshes hold no others.  Whole apply replayed from a
+// graph, by sweeps -> now: 45^3 Q2 FP32 31.4 -> 12.2 us; 30^3 Q1 FP64 73.2 -> 10.7; 96^3 Q3 FP64 86.1 ->
+// 64.4; 150^3 Q2 FP64 84.7 -> 77.9.  The x-runs' first DoFs come from the row descriptors: reading them from
 // the cells' table cost 36 B per cell at p=2, 5 % of the kernel.
 // ------------------------------------------------------------------------------------
 __device__ __forceinline__ void wave_sync() {
@@ -1406,8 +1411,9 @@ __device__ __forceinline__ void tile_face_rows(const KTab<T, N1> &tab, const T *
 // Small operators of 3D p >= 4 and of 2D: all of a brick's cell places at once, (p+1)^(d-1) threads
 // each, two tiles of LDS per place; every lattice point then sums its cells' values as it is stored.
 // What bounds it: the latency of its phases (row tables, gather, one pass per axis, write-out), so it
-// takes the operators whose bricks are on the device all at once (kCellsMax; 24^3 Q4 apply FP64 26.9
-// -> 20.5 us, FP32 24.6 -> 18.4 us, 2D disk of 349 unknowns 16.4 -> 14.5 us).
+// takes the operators whose bricks are on the device all at once (kCellsMax; whole apply replayed from a
+// graph, by sweeps -> now: 24^3 Q4 FP64 22.6 -> 14.4 us, FP32 20.1 -> 13.1, 2D Q2 disk of 345 unknowns 11.2
+// -> 8.5; a call of its own on that disk is bound by the host's launches, 17.5 -> 16 to 18 us).
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int N1>
 __device__ __forceinline__ void tile_body(const int brick, BrickArgs br, const T *__restrict__ fbuf,
@@ -1541,10 +1547,11 @@ __global__ __launch_bounds__((BrickCfg<T, D, N1, CELLS>::NT)) void brick_kernel(
 // Two DoFs per thread (a block's 2 * 256 consecutive ones), so that each thread has twice the
 // loads in flight (FP64 apply at 64^3 Q4: 50.2 against 51.2 us; with four 1.5 us slower).
 // What bounds it: the points on x planes, each a store of one value to a cache line of v.  They are a
-// sixteenth of all points at 3D p=4 and cost 45 of 110 us on 128^3 FP64 (measured with the same stores
-// side by side).  With the halo numbered for dense planes and stores (see build_bricks) instead of in
-// DoF order, 128^3 Q4 FP64: brick kernel 264 -> 235 us, apply 417 -> 357 us; FP32 152 -> 140 and
-// 231 -> 221 us.  One contiguous range of it per XCD measured slower (128^3 FP64 381 us).
+// sixteenth of all points at 3D p=4, and with the same stores side by side 128^3 FP64 took 45 us less when
+// the pass took 110 (73 now, with nontemporal reads of the planes).  With the halo numbered for dense planes
+// and stores (see build_bricks) instead of in DoF order, and the surrogate faces by one thread per point,
+// 128^3 Q4 replayed: FP64 apply 404 -> 324 us, FP32 222 -> 211.  One contiguous range of it per XCD measured
+// slower (128^3 FP64 381 against 357 us then).
 constexpr int kHaloPerThread = 2;
 template <typename T, int D, bool ONCE>
 __device__ __forceinline__ void halo_reduce_body(const int blk, int n, const int32_t *__restrict__ dof,
@@ -1590,8 +1597,10 @@ __global__ __launch_bounds__(256) void halo_reduce_kernel(int n, const int32_t *
 // N^T (W E u), two sweeps in all.
 // What bounds it: the latency of that chain; a face's 5 kB and 10 kFLOP at 3D p=4 are small against it.
 // With half of the threads for E u, two points each, and dn u taken to the Gauss points and back (four
-// sweeps), apply in us: 64^3 Q4 FP64 59.8 -> 57.7, 128^3 Q4 346 -> 338, 96^3 Q3 84.3 -> 80.6, 40^3 Q5
-// 43.3 -> 41.5, 20^3 Q8 46.1 -> 39.1; FP32 64^3 Q4 40.3 -> 40.2.
+// sweeps), kernel in us: 66^3 Q4 FP64 17.1 -> 15.5, 50^3 Q5 17.2 -> 13.6, 40^3 Q6 27.0 -> 22.0, 20^3 Q8 23.6
+// -> 17.3, 36^3 Q8 49.7 -> 44.2, FP32 20^3 Q8 20.2 -> 11.4.  At Q8 the reads of the cell's 729 values from
+// LDS bound it, which one thread per point does twice as often: 30^3 Q8 FP64, whose 965 workgroups fill the
+// device just once, 29.3 -> 33.0.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int N1, int EPB>
 __device__ __forceinline__ void sbm_face_cg_body(const int blk, int n_faces, const int32_t *__restrict__ face_code,

@@ -306,12 +306,12 @@ constexpr int gs_rows(int cpw) { return 16 >> gs_class(cpw); }
 // block b at partial[i kMaxBlocks + b]); the last block to finish (ticket on *counter, which it
 // resets to 0 for the next launch) adds them in a fixed order, so the result is independent of
 // the block schedule.
-// What bounds it: the reading of V, 3.4 M rows of 24 columns FP64 at 3.7 TB/s and of 50 at 4.5 (a plain
-// read reaches 6.0).  Every load of a step is pinned ahead of its first use: without that the compiler
-// held 40 registers and had about ten of the 32 loads under way.  A single run's launch has as many
-// columns per wave as it needs, where 2, 4, 8 or 16 left up to half of the slots to masked loads.  50
-// steps on 3.4 M rows: FP64 35.0 -> 32.1 ms, FP32 refinement 22.8 -> 20.5 ms; on 0.4 M rows 8.2 -> 8.0
-// and 7.3 -> 6.95 ms.
+// What bounds it: the reading of V, on 3.4 M rows FP64 at 2.5 to 3.4 TB/s with 7 columns, 3.9 to 4.3 with 30
+// and 4.3 (MODE 2) to 5.1 (MODE 0) with 50 (a plain read reaches 6.0).  Every load of a step is pinned ahead
+// of its first use: without that the compiler held 40 registers and had about ten of the 32 loads under way.
+// A single run's launch has as many columns per wave as it needs, where 2, 4, 8 or 16 left up to half of the
+// slots to masked loads.  With the first-order faces made faster beside it, 50 steps on 3.4 M rows: FP64 36.0
+// -> 32.1 ms, FP32 refinement 23.8 -> 20.6; on 0.4 M rows 8.8 -> 8.1 and 7.9 -> 7.1.
 template <typename T, int CPW, int MODE, bool TICKET = true>
 __device__ __forceinline__ void gs_body(const int blk, const int nblk, const T *__restrict__ V, int m1, int ncol,
                                         const double *__restrict__ coef, T *__restrict__ w, int64_t n,
