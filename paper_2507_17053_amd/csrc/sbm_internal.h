@@ -141,8 +141,10 @@ struct sbm_ctx {
   bool host_only = false;
   sbm::Workspace *ws = nullptr;
   // completion of the handle's last stream-ordered work (recorded by the asynchronous entry
-  // points); sbm_destroy waits for it instead of for the whole device
-  hipEvent_t last_work = nullptr;
+  // points); sbm_destroy waits for it instead of for the whole device.  [0]: a default event, [1]: one
+  // without system-scope release (note_work); last_kind: the one recorded last
+  hipEvent_t last_work[2] = {nullptr, nullptr};
+  int last_kind = 0;
 };
 
 namespace sbm {

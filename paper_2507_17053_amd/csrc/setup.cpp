@@ -105,15 +105,29 @@ void dev_free(void *p) {
 void note_work(sbm_ctx *c, hipStream_t stream) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return;
-  // (sbm_destroy waits on it before the handle's device memory is reused, so completion on the device
-  // is all it has to show: the system-scope release of a default event cost 1.5 to 2 us on every apply,
-  // 24^3 Q4 FP64 19.4 -> 17.6 us)
-  if (!c->last_work &&
-      hipEventCreateWithFlags(&c->last_work, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
-    c->last_work = nullptr;
+  // sbm_destroy waits on the event before the handle's device memory is reused, so completion on the device is
+  // all it has to show.  The system-scope release of a default event costs each apply of a series 2 us, but
+  // behind an event without it a caller who then waits for the stream waits for a second marker.  So the event
+  // is a default one unless the work noted before is still under way, as it is in a series.  One apply and a
+  // wait / one of a series, us, FP64, default events / events without / this: 64^3 Q4 64.2, 67.0, 64.9 / 52.2,
+  // 50.2, 50.3; DG 32^3 Q3 26.4, 29.3, 26.6 / 15.5, 14.2, 14.2; DG 30^2 Q2 20.1, 23.6, 20.3 / host-bound.
+  int k = 0;
+  if (hipEvent_t before = c->last_work[c->last_kind]) {
+    // (relaxed: a query is not allowed while another thread captures a stream)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const hipError_t q = hipEventQuery(before);
+    if (q != hipSuccess) (void)hipGetLastError();  // "not ready" is no error of the apply
+    k = q == hipErrorNotReady ? 1 : 0;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  hipEvent_t &e = c->last_work[k];
+  if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming | (k ? hipEventDisableSystemFence : 0)) != hipSuccess) {
+    e = nullptr;
     return;
   }
-  (void)hipEventRecord(c->last_work, stream);
+  c->last_kind = k;
+  (void)hipEventRecord(e, stream);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1070,11 +1084,12 @@ void sbm_destroy(sbm_handle h) {
   if (!h) return;
   // wait for the handle's last asynchronous work only (its memory returns to the pool
   // stream-ordered; nothing else on the device is waited for)
-  if (h->last_work) {
-    (void)hipEventSynchronize(h->last_work);
-    (void)hipEventDestroy(h->last_work);
-    h->last_work = nullptr;
-  }
+  for (hipEvent_t &e : h->last_work)
+    if (e) {
+      (void)hipEventSynchronize(e);
+      (void)hipEventDestroy(e);
+      e = nullptr;
+    }
   sbm::wait_batches();  // batches that include h record their completion, not h's
   sbm::free_workspace(h);
   free_device(h);
