@@ -73,8 +73,10 @@ def test_close_waits_for_the_applies(name, dtype):
             ref = got
 
 
-def test_applies_beside_another_threads_capture():
-    """A series of applies on one thread while another captures a graph: neither disturbs the other."""
+@pytest.mark.parametrize("other_thread", [True, False], ids=["other_thread", "same_thread"])
+def test_applies_beside_a_capture(other_thread):
+    """A series of applies on a stream of its own while a graph is captured on another, by another thread or
+    by the same: neither disturbs the other."""
     op = sbm.Operator(3, 24, -1.0, 1.0, inputs.sphere((0, 0, 0), 0.8), 4)
     u = torch.from_numpy(inputs.uniform_vector(op.n_dofs, seed=1)).to("cuda")
     ref, v = torch.empty_like(u), torch.full_like(u, float("nan"))
@@ -94,9 +96,12 @@ def test_applies_beside_another_threads_capture():
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         x.add_(1.0)
-        th = threading.Thread(target=series)
-        th.start()
-        th.join()
+        if other_thread:
+            th = threading.Thread(target=series)
+            th.start()
+            th.join()
+        else:
+            series()
         x.add_(1.0)
     for rep in range(3):
         g.replay()
