@@ -202,9 +202,10 @@ void brick_dims(int dim, int p, bool by_cells, int *bx, int *by, int *bz);
 // shape (8x8x8, 8x4x4, 4x4x4), whatever shape its form takes: false for the other operators, where
 // the bricks' own count decides.
 constexpr size_t kNoallocBytes = (size_t)96 << 20;
-// Whether those DoFs need counting: not where even all DoFs would be within the limit in FP64.
+// Whether those DoFs need counting: not where even all DoFs would be within the limit in FP64 (the halo and
+// the faces' results are each rounded up to 256 bytes).
 inline bool noalloc_counts(const sbm_ctx *c, int64_t n_dofs) {
-  return ((size_t)8 << c->dim) * (size_t)n_dofs + (size_t)c->n_sbm * 16 * c->nq_face + 256 > kNoallocBytes;
+  return ((size_t)8 << c->dim) * (size_t)n_dofs + (size_t)c->n_sbm * 16 * c->nq_face + 2 * 256 > kNoallocBytes;
 }
 inline bool noalloc_brick(int dim, int p, int b[3]) {
   if (dim != 3 || p > 3) return false;
